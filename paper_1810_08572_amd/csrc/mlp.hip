@@ -3,7 +3,7 @@
 // count).  A dense network n_in -> width (x n_hidden, SiLU) -> 1 (linear)
 // maps per-cell features to the next pressure increment.
 //
-//   training   FP32: tiled GEMMs (deterministic split-K over the rows),
+//   training   FP32 matrix cores (deterministic split-K over the rows),
 //              SiLU, mean-squared-error gradient, Adam;
 //   inference  the width x width hidden layers on BF16 MFMA
 //              (v_mfma_f32_32x32x8bf16_1k, FP32 accumulation), the first and
@@ -13,6 +13,7 @@
 // Parameters are FP32, packed layer by layer: W ([out][in], row-major), b.
 #include "common.h"
 
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 #include <string>
@@ -24,7 +25,8 @@ struct ppe_mlp {
   std::vector<int> dims;                 // n_in, width, ..., width, 1
   std::vector<int64_t> woff, boff;       // offsets of W_l, b_l in the packed vector
   ppe::DevBuf params, grad, m, v, bf16;  // bf16: hidden weight matrices in BF16
-  ppe::DevBuf act, pre, gbuf, gbuf2, part, lossbuf;
+  ppe::DevBuf act, pre, gbuf, part, lossbuf;
+  double* loss_h = nullptr;  // pinned: the last batch's loss
   int64_t adam_t = 0;
   size_t lds_max = 0;  // LDS one workgroup may use (0: not queried yet)
   int cus = 0;         // compute units of the device
@@ -40,112 +42,280 @@ __device__ __forceinline__ float dsilu_f(float z) {
   return s + z * s * (1.0f - s);
 }
 
-// C (+)= op(A) op(B): op(A)(i,k) = A[i*ari + k*ack], op(B)(k,j) = B[k*brk + j*bcj].
-// Block (64 x 64 outputs, 256 threads, 4 x 4 per thread); blockIdx.z selects
-// a chunk of `kc` values of k and writes its own partial C + z*M*N (split-K;
-// the chunks are added afterwards in chunk order).
-constexpr int TM = 64, TN = 64, TK = 16;
-__global__ void __launch_bounds__(256) k_sgemm(int M, int N, int K, int kc, const float* __restrict__ A,
-                                               int64_t ari, int64_t ack, const float* __restrict__ B,
-                                               int64_t brk, int64_t bcj, float* __restrict__ C) {
-  __shared__ float As[TK][TM + 1];
-  __shared__ float Bs[TK][TN + 1];
-  const int t = threadIdx.x, tx = t % 16, ty = t / 16;
-  const int i0 = blockIdx.y * TM, j0 = blockIdx.x * TN;
-  const int k_begin = blockIdx.z * kc, k_end = min(K, k_begin + kc);
-  float acc[4][4] = {};
-  for (int k0 = k_begin; k0 < k_end; k0 += TK) {
-    for (int e = t; e < TM * TK; e += 256) {
-      const int ii = e / TK, kk = e % TK;
-      const int i = i0 + ii, k = k0 + kk;
-      As[kk][ii] = (i < M && k < k_end) ? A[i * ari + k * ack] : 0.0f;
-    }
-    for (int e = t; e < TN * TK; e += 256) {
-      const int kk = e / TN, jj = e % TN;
-      const int j = j0 + jj, k = k0 + kk;
-      Bs[kk][jj] = (j < N && k < k_end) ? B[k * brk + j * bcj] : 0.0f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < TK; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) a[r] = As[kk][ty * 4 + r];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) b[c] = Bs[kk][tx * 4 + c];
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[r][c] = acc[r][c] + a[r] * b[c];
-    }
-    __syncthreads();
-  }
-  float* Cz = C + (size_t)blockIdx.z * M * N;
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int i = i0 + ty * 4 + r, j = j0 + tx * 4 + c;
-      if (i < M && j < N) Cz[(size_t)i * N + j] = acc[r][c];
-    }
+// ---- training and FP32 inference
+// A batch is a handful of thin products (8,192 rows, width 128: 1.7 GFLOP
+// with the gradients, 26 MB of activations), so what bounds it is the number
+// of dispatches and how many compute units each one fills.  Every product
+// runs on the FP32 matrix cores (v_mfma_f32_32x32x2f32: FP32 products and
+// sums, the vector ALUs' accuracy) in 32 x 32 tiles, one per wave, and takes
+// what follows it along: bias and SiLU with the forward layers, silu' with
+// the backward ones, the whole output layer with the loss.  The weight and
+// bias gradients of all layers are one dispatch over (tile, chunk of rows),
+// their chunks added in order by a second: eight dispatches for three hidden
+// layers.  Loss and gradient of 8,192 rows take 102 us; the vector-ALU tiles
+// this replaces (64 x 64 outputs per workgroup, eight workgroups for a weight
+// gradient, a separate pass for every bias, activation and column sum) took
+// 3.87 ms.
+typedef float float16_t __attribute__((ext_vector_type(16)));
+
+constexpr int kTile = 32;  // rows and columns of one wave's product tile
+constexpr int kTileN = 4 * kTile;  // columns of a workgroup's tile (4 waves)
+constexpr int kTileK = 64;         // depth staged in LDS at a time
+
+// Operands of v_mfma_f32_32x32x2f32: lane l holds A[l % 32][l / 32] and
+// B[l / 32][l % 32]; accumulator r of lane l is
+// C[8 (r / 4) + 4 (l / 32) + r % 4][l % 32].
+__device__ __forceinline__ int acc_row(int r, int lane) {
+  return 8 * (r / 4) + 4 * (lane / 32) + r % 4;
 }
 
-// out[e] = sum over z of parts[z * len + e], in z order
-__global__ void k_sum_chunks(int64_t len, int nz, const float* __restrict__ parts,
-                             float* __restrict__ out) {
+// A ROWS x COLS tile of a row-major matrix on its way through 256 threads into
+// LDS: fetch requests it all (zeros past `rows` and `cols`), put stores it.
+// Four columns per load where the matrix allows it (vec: its leading
+// dimension and address are multiples of four floats; one by one, a layer of
+// width 128 takes 14.4 us, with them 11.5).
+template <int ROWS, int COLS>
+struct Staged {
+  static constexpr int U = ROWS * COLS / 1024, kRow = COLS / 4, kStep = 256 / kRow;
+  static_assert(U * 1024 == ROWS * COLS && kStep * kRow == 256, "whole rounds only");
+  float4 v[U];
+  __device__ __forceinline__ void fetch(const float* __restrict__ src, int ld, int rows, int cols,
+                                        bool vec) {
+    const int r0 = (int)threadIdx.x / kRow, c = 4 * ((int)threadIdx.x % kRow);
+    if (vec) {  // no branch inside, so the loads issue together
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int r = r0 + u * kStep;
+        const bool ok = r < rows && c < cols;  // cols is a multiple of four too
+        v[u] = *reinterpret_cast<const float4*>(src + (ok ? r * ld + c : 0));
+        if (!ok) v[u] = float4{0.0f, 0.0f, 0.0f, 0.0f};
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int r = r0 + u * kStep;
+        float w[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const bool ok = r < rows && c + q < cols;
+          w[q] = src[ok ? r * ld + c + q : 0];
+          if (!ok) w[q] = 0.0f;
+        }
+        v[u] = float4{w[0], w[1], w[2], w[3]};
+      }
+    }
+  }
+  __device__ __forceinline__ void put(float* dst, int pitch) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      float* d = dst + ((int)threadIdx.x / kRow + u * kStep) * pitch + 4 * ((int)threadIdx.x % kRow);
+      d[0] = v[u].x;
+      d[1] = v[u].y;
+      d[2] = v[u].z;
+      d[3] = v[u].w;
+    }
+  }
+};
+__device__ __forceinline__ bool vec4(const float* p, int ld) {
+  return ld % 4 == 0 && reinterpret_cast<uintptr_t>(p) % 16 == 0;
+}
+
+// One layer over rows of a batch.  Forward (BACK = false): z = X W^T + b with
+// W [N][K]; z (if wanted) and silu(z) are stored.  Backward (BACK = true):
+// Z = (X W) silu'(Z) in place, W [K][N].  A workgroup takes 32 rows and 128
+// columns, one 32 x 32 tile per wave: 256 workgroups for 8,192 rows and a
+// width up to 128.
+template <bool BACK>
+__global__ void __launch_bounds__(256) k_layer(int n, int N, int K, const float* __restrict__ X,
+                                               const float* __restrict__ W,
+                                               const float* __restrict__ bias,
+                                               float* __restrict__ Z, float* __restrict__ H) {
+  // rows of X and (forward) of W are stored one word apart from a multiple of
+  // the bank count: a tile's 32 lanes read 32 rows at one depth
+  __shared__ float Xs[kTile][kTileK + 1];
+  __shared__ float Ws[kTileN * (kTileK + 1)];
+  const int t = threadIdx.x, lane = t % 64, wv = t / 64, c = lane % 32, half = lane / 32;
+  const int64_t i0 = (int64_t)blockIdx.x * kTile;
+  const int j0 = blockIdx.y * kTileN, jw = wv * kTile;
+  const bool live = j0 + jw < N;
+  const int rows = (int)min((int64_t)kTile, n - i0);
+  const bool vx = vec4(X, K), vw = vec4(W, BACK ? N : K);
+  float16_t acc = {0};
+  for (int k0 = 0; k0 < K; k0 += kTileK) {
+    const int kn = min(kTileK, K - k0);  // entries past it are stored as zeros
+    Staged<kTile, kTileK> xs;
+    Staged<BACK ? kTileK : kTileN, BACK ? kTileN : kTileK> ws;
+    xs.fetch(X + i0 * K + k0, K, rows, kn, vx);
+    if (BACK)
+      ws.fetch(W + (int64_t)k0 * N + j0, N, kn, N - j0, vw);
+    else
+      ws.fetch(W + (int64_t)j0 * K + k0, K, N - j0, kn, vw);
+    __syncthreads();  // the last chunk's readers are done
+    xs.put(&Xs[0][0], kTileK + 1);
+    ws.put(Ws, BACK ? kTileN : kTileK + 1);
+    __syncthreads();
+    if (live) {
+      for (int kk = 0; kk < kn; kk += 16) {
+#pragma unroll
+        for (int u = 0; u < 16; u += 2) {
+          const int k = kk + u + half;
+          const float b = BACK ? Ws[k * kTileN + jw + c] : Ws[(jw + c) * (kTileK + 1) + k];
+          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(Xs[c][k], b, acc, 0, 0, 0);
+        }
+      }
+    }
+  }
+  const int j = j0 + jw + c;
+  if (!live || j >= N) return;
+  const float bj = BACK ? 0.0f : bias[j];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int64_t i = i0 + acc_row(r, lane);
+    if (i >= n) continue;
+    const int64_t e = i * N + j;
+    if (BACK) {
+      Z[e] = acc[r] * dsilu_f(Z[e]);
+    } else {
+      const float z = acc[r] + bj;
+      if (Z) Z[e] = z;
+      H[e] = silu_f(z);
+    }
+  }
+}
+
+// The output layer y = H w + b, 16 lanes per row.  Training (t given): also
+// g = 2/n (y - t), the gradient g w silu'(Z) of the last hidden layer's
+// pre-activations in place of Z, and the block's share of the squared error.
+constexpr int kOutLanes = 16, kOutRows = kBlock / kOutLanes;
+__global__ void __launch_bounds__(kBlock) k_output(int n, int width, const float* __restrict__ H,
+                                                   const float* __restrict__ w,
+                                                   float* __restrict__ y,
+                                                   const float* __restrict__ t,
+                                                   float* __restrict__ g, float* __restrict__ Z,
+                                                   double* __restrict__ partials) {
+  const int lane = threadIdx.x % kOutLanes, sub = threadIdx.x / kOutLanes;
+  const float b = w[width];
+  double loss = 0.0;
+  const int64_t rows = ((int64_t)n + kOutRows - 1) / kOutRows;
+  for (int64_t q = blockIdx.x; q < rows; q += gridDim.x) {
+    const int64_t i = q * kOutRows + sub;
+    float s = 0.0f;
+    if (i < n)
+      for (int j = lane; j < width; j += kOutLanes) s = s + H[i * width + j] * w[j];
+#pragma unroll
+    for (int o = kOutLanes / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, kOutLanes);
+    if (i >= n) continue;
+    const float yi = s + b;
+    if (!t) {
+      if (lane == 0) y[i] = yi;
+      continue;
+    }
+    const float e = yi - t[i];
+    const float gi = (2.0f / (float)n) * e;
+    if (lane == 0) {
+      g[i] = gi;
+      loss += (double)e * (double)e;
+    }
+    for (int j = lane; j < width; j += kOutLanes) {
+      const int64_t at = i * width + j;
+      Z[at] = gi * w[j] * dsilu_f(Z[at]);
+    }
+  }
+  if (t) {
+    double v[1] = {loss};
+    write_partials<kBlock, 1>(v, partials);
+  }
+}
+
+// Weight and bias gradients of every layer: layer l's dW [M][N] = G^T Hin and
+// db [M] = column sums of G over a chunk of rows (blockIdx.y), as that
+// chunk's copy of the packed gradient.  blockIdx.x counts the layers' tiles of
+// 32 x 128 outputs.
+constexpr int kMaxLayers = 16;  // layers of one k_grads dispatch
+struct GradLayer {
+  const float* G;   // [n][M]
+  const float* Hin; // [n][N]
+  int64_t woff, boff;
+  int M, N, tile0;  // first tile of the layer
+};
+struct GradArgs {
+  GradLayer l[kMaxLayers];
+  int layers;
+};
+__global__ void __launch_bounds__(256) k_grads(GradArgs a, int n, int chunk, int64_t n_params,
+                                               float* __restrict__ parts) {
+  __shared__ float Gs[kTileK][kTile];
+  __shared__ float Hs[kTileK][kTileN];
+  __shared__ float bs[8][kTile];
+  int li = 0;
+  while (li + 1 < a.layers && (int)blockIdx.x >= a.l[li + 1].tile0) ++li;
+  const GradLayer L = a.l[li];
+  const int tn = (L.N + kTileN - 1) / kTileN, tile = blockIdx.x - L.tile0;
+  const int o0 = (tile / tn) * kTile, j0 = (tile % tn) * kTileN;
+  const int t = threadIdx.x, lane = t % 64, wv = t / 64, c = lane % 32, half = lane / 32;
+  const int jw = wv * kTile;
+  const bool live = j0 + jw < L.N;
+  const int64_t r0 = (int64_t)blockIdx.y * chunk, r1 = r0 + chunk < n ? r0 + chunk : n;
+  const bool vg = vec4(L.G, L.M), vh = vec4(L.Hin, L.N);
+  float16_t acc = {0};
+  float db = 0.0f;
+  for (int64_t k0 = r0; k0 < r1; k0 += kTileK) {
+    Staged<kTileK, kTile> gs;
+    Staged<kTileK, kTileN> hs;
+    const int rows = (int)min((int64_t)kTileK, r1 - k0);
+    gs.fetch(L.G + k0 * L.M + o0, L.M, rows, L.M - o0, vg);
+    hs.fetch(L.Hin + k0 * L.N + j0, L.N, rows, L.N - j0, vh);
+    __syncthreads();  // the last chunk's readers are done
+    gs.put(&Gs[0][0], kTile);
+    hs.put(&Hs[0][0], kTileN);
+    __syncthreads();
+    if (j0 == 0)  // eight runs of rows per column, added below
+      for (int kk = t / kTile; kk < kTileK; kk += 8) db = db + Gs[kk][t % kTile];
+    if (live) {
+#pragma unroll 8
+      for (int kk = 0; kk < kTileK; kk += 2)
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(Gs[kk + half][c], Hs[kk + half][jw + c], acc, 0,
+                                                   0, 0);
+    }
+  }
+  float* out = parts + (size_t)blockIdx.y * n_params;
+  if (j0 == 0) {
+    bs[t / kTile][t % kTile] = db;
+    __syncthreads();
+    if (t < kTile && o0 + t < L.M) {
+      float s = 0.0f;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) s = s + bs[k][t];
+      out[L.boff + o0 + t] = s;
+    }
+  }
+  const int j = j0 + jw + c;
+  if (!live || j >= L.N) return;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int o = o0 + acc_row(r, lane);
+    if (o < L.M) out[L.woff + (int64_t)o * L.N + j] = acc[r];
+  }
+}
+
+// grad[e] = sum over the chunks of parts, in chunk order; the last block adds
+// the loss partials.
+__global__ void __launch_bounds__(kBlock) k_sum_grads(int64_t len, int nz,
+                                                      const float* __restrict__ parts,
+                                                      float* __restrict__ grad,
+                                                      const double* __restrict__ partials, int g,
+                                                      int n, double* __restrict__ loss) {
+  if (blockIdx.x == gridDim.x - 1) {
+    const double s = sum_partials<kBlock>(partials, g);
+    if (threadIdx.x == 0) *loss = s / n;
+    return;
+  }
   const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (e >= len) return;
   float s = 0.0f;
+#pragma unroll 8
   for (int z = 0; z < nz; ++z) s = s + parts[(size_t)z * len + e];
-  out[e] = s;
-}
-
-// z = y + b (row broadcast); stores z, and h = silu(z) when silu != 0
-__global__ void k_bias_act(int64_t n, int width, const float* __restrict__ y,
-                           const float* __restrict__ b, float* __restrict__ z,
-                           float* __restrict__ h, int silu) {
-  const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (e >= n * width) return;
-  const float v = y[e] + b[e % width];
-  z[e] = v;
-  h[e] = silu ? silu_f(v) : v;
-}
-
-// output layer: g = 2/n (y - t); partial sums of (y - t)^2 per block
-__global__ void k_loss_grad(int n, const float* __restrict__ y, const float* __restrict__ t,
-                            float* __restrict__ g, double* __restrict__ partials) {
-  double acc = 0.0;
-  for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
-    const float e = y[i] - t[i];
-    g[i] = (2.0f / (float)n) * e;
-    acc += (double)e * (double)e;
-  }
-  double v[1] = {acc};
-  write_partials<kBlock, 1>(v, partials);
-}
-
-__global__ void k_finalize_loss(const double* __restrict__ partials, int g, int n,
-                                double* __restrict__ out) {
-  const double s = sum_partials<kBlock>(partials, g);
-  if (threadIdx.x == 0) *out = s / n;
-}
-
-// g *= silu'(z)
-__global__ void k_dsilu_mul(int64_t len, const float* __restrict__ z, float* __restrict__ g) {
-  const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (e < len) g[e] = g[e] * dsilu_f(z[e]);
-}
-
-// column sums of G [n x w] over rows chunk z: parts[z*w + j]
-constexpr int kColRows = 64, kColChunks = 1024;
-__global__ void k_colsum_chunks(int n, int w, int chunk, const float* __restrict__ G,
-                                float* __restrict__ parts) {
-  const int j = blockIdx.x * kBlock + threadIdx.x;
-  if (j >= w) return;
-  const int r0 = blockIdx.y * chunk, r1 = min(n, r0 + chunk);
-  float s = 0.0f;
-  for (int r = r0; r < r1; ++r) s = s + G[(size_t)r * w + j];
-  parts[(size_t)blockIdx.y * w + j] = s;
+  grad[e] = s;
 }
 
 __global__ void k_adam(int64_t n, float* __restrict__ p, const float* __restrict__ g,
@@ -171,7 +341,6 @@ __global__ void k_to_bf16(int64_t n, const float* __restrict__ a, uint16_t* __re
 
 // ---------------------------------------------------------------- BF16 inference
 typedef short short4_t __attribute__((ext_vector_type(4)));
-typedef float float16_t __attribute__((ext_vector_type(16)));
 
 __device__ __forceinline__ uint16_t f2bf(float f) {
   uint32_t u = __float_as_uint(f);
@@ -557,105 +726,94 @@ ppe_status ws_features(ppe_solver* s, const double* dp_prev, const double* rhs,
   return PPE_OK;
 }
 
-void gemm(ppe_mlp* m, int M, int N, int K, const float* A, int64_t ari, int64_t ack,
-          const float* B, int64_t brk, int64_t bcj, float* C, int chunk_rows = 0) {
-  const int kc = chunk_rows > 0 ? chunk_rows : K;
-  const int nz = (K + kc - 1) / kc;
-  dim3 grid((N + TN - 1) / TN, (M + TM - 1) / TM, nz > 0 ? nz : 1);
-  if (nz <= 1) {
-    hipLaunchKernelGGL(k_sgemm, grid, dim3(256), 0, m->stream, M, N, K, kc, A, ari, ack, B, brk,
-                       bcj, C);
-    PPE_LAUNCH_CHECK();
-    return;
-  }
-  float* parts = m->part.get<float>((size_t)nz * M * N);
-  hipLaunchKernelGGL(k_sgemm, grid, dim3(256), 0, m->stream, M, N, K, kc, A, ari, ack, B, brk, bcj,
-                     parts);
-  PPE_LAUNCH_CHECK();
-  const int64_t len = (int64_t)M * N;
-  hipLaunchKernelGGL(k_sum_chunks, dim3(grid_for(len)), dim3(kBlock), 0, m->stream, len, nz, parts,
-                     C);
-  PPE_LAUNCH_CHECK();
-}
-
-constexpr int kChunkRows = 4096;  // rows per split-K chunk of the weight gradients
-
-// FP32 forward of n rows; keeps pre-activations and activations for backward.
-// Returns the pointer to y [n].
-float* forward_fp32(ppe_mlp* m, int n, const float* x) {
-  const int L = (int)m->dims.size() - 1;
-  int64_t tot = 0;
-  for (int l = 1; l <= L; ++l) tot += (int64_t)n * m->dims[l];
-  float* act = m->act.get<float>(tot);
-  float* pre = m->pre.get<float>(tot);
-  float* tmp = m->gbuf2.get<float>((size_t)n * m->width > (size_t)n ? (size_t)n * m->width : n);
+// The hidden layers of n rows: activations into m->act and, for the backward
+// pass, pre-activations into m->pre.  Returns the last hidden activations.
+const float* hidden_layers(ppe_mlp* m, int n, const float* x, bool keep_pre) {
+  const int64_t len = (int64_t)n * m->width;
+  float* act = m->act.get<float>((size_t)len * m->n_hidden);
+  float* pre = keep_pre ? m->pre.get<float>((size_t)len * m->n_hidden) : nullptr;
   const float* P = m->params.as<float>();
   const float* h = x;
-  int64_t off = 0;
-  for (int l = 0; l < L; ++l) {
-    const int in = m->dims[l], out = m->dims[l + 1];
-    // tmp [n x out] = h [n x in] W^T  (W [out][in])
-    gemm(m, n, out, in, h, in, 1, P + m->woff[l], 1, in, tmp);
-    const int64_t len = (int64_t)n * out;
-    hipLaunchKernelGGL(k_bias_act, dim3(grid_for(len)), dim3(kBlock), 0, m->stream, (int64_t)n, out,
-                       tmp, P + m->boff[l], pre + off, act + off, l < L - 1 ? 1 : 0);
+  for (int l = 0; l < m->n_hidden; ++l) {
+    const dim3 grid((unsigned)((n + (int64_t)kTile - 1) / kTile),
+                    (m->width + kTileN - 1) / kTileN);
+    hipLaunchKernelGGL(k_layer<false>, grid, dim3(256), 0, m->stream, n, m->width, m->dims[l], h,
+                       P + m->woff[l], P + m->boff[l], pre ? pre + l * len : nullptr,
+                       act + l * len);
     PPE_LAUNCH_CHECK();
-    h = act + off;
-    off += len;
+    h = act + l * len;
   }
-  return act + off - n;
+  return h;
 }
 
-// Mean-squared-error loss (host) and the packed gradient into m->grad.
-double loss_grad(ppe_mlp* m, int n, const float* x, const float* t) {
-  const int L = (int)m->dims.size() - 1;
-  float* y = forward_fp32(m, n, x);
-  float* G = m->gbuf.get<float>((size_t)n * m->width > (size_t)n ? (size_t)n * m->width : n);
-  float* G2 = m->gbuf2.get<float>((size_t)n * m->width > (size_t)n ? (size_t)n * m->width : n);
-  const int gl = red_grid(n);
-  double* lp = m->lossbuf.get<double>((size_t)gl + 1);
-  hipLaunchKernelGGL(k_loss_grad, dim3(gl), dim3(kBlock), 0, m->stream, n, y, t, G, lp);
+int output_grid(int n) {
+  const int64_t g = ((int64_t)n + kOutRows - 1) / kOutRows;
+  return (int)std::min<int64_t>(g, kRedBlocks);
+}
+
+// FP32 forward of n rows into y.
+void forward_fp32(ppe_mlp* m, int n, const float* x, float* y) {
+  const float* h = hidden_layers(m, n, x, false);
+  hipLaunchKernelGGL(k_output, dim3(output_grid(n)), dim3(kBlock), 0, m->stream, n, m->width, h,
+                     m->params.as<float>() + m->woff[m->n_hidden], y, (const float*)nullptr,
+                     (float*)nullptr, (float*)nullptr, (double*)nullptr);
   PPE_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_finalize_loss, dim3(1), dim3(kBlock), 0, m->stream, lp, gl, n, lp + gl);
-  PPE_LAUNCH_CHECK();
+}
+
+// Chunks of rows of the weight gradients: at least 128 rows each, at most 64
+// chunks, and at most 128 MB of partial gradients (they are written and read
+// once each; a network that large fills the device with its tiles alone).
+constexpr int kGradRows = 128, kGradChunks = 64;
+int grad_chunk(const ppe_mlp* m, int n) {
+  const int64_t most = std::clamp<int64_t>((int64_t(1) << 25) / m->n_params, 1, kGradChunks);
+  return std::max(kGradRows, (int)((n + most - 1) / most));
+}
+
+// Queues the packed gradient of the mean-squared error into grad and the
+// loss into *m->loss_h (pinned: read it once the stream has been waited for).
+void loss_grad(ppe_mlp* m, int n, const float* x, const float* t, float* grad) {
+  const int L = m->n_hidden;  // the output layer
+  const int64_t len = (int64_t)n * m->width;
+  if (!m->loss_h) PPE_HIP(hipHostMalloc(reinterpret_cast<void**>(&m->loss_h), sizeof(double)));
   const float* P = m->params.as<float>();
-  float* dP = m->grad.get<float>(m->n_params);
-  // offsets of each layer's activations in act/pre
-  std::vector<int64_t> aoff(L + 1, 0);
-  for (int l = 1; l <= L; ++l) aoff[l] = aoff[l - 1] + (int64_t)n * m->dims[l];
-  const float* act = m->act.as<float>();
-  const float* pre = m->pre.as<float>();
-  for (int l = L - 1; l >= 0; --l) {
-    const int in = m->dims[l], out = m->dims[l + 1];
-    const float* hin = l == 0 ? x : act + aoff[l - 1];
-    // dW [out x in] = G^T [out x n] . hin [n x in]   (sum over rows, split-K)
-    gemm(m, out, in, n, G, 1, out, hin, in, 1, dP + m->woff[l], kChunkRows);
-    // db [out] = column sums of G
-    // bias gradient: column sums over chunks of at least kColRows rows (at
-    // most kColChunks chunks), the chunks then added in order
-    const int crow = std::max(kColRows, (n + kColChunks - 1) / kColChunks);
-    const int nz = (n + crow - 1) / crow;
-    float* parts = m->part.get<float>((size_t)nz * out);
-    hipLaunchKernelGGL(k_colsum_chunks, dim3((out + kBlock - 1) / kBlock, nz), dim3(kBlock), 0,
-                       m->stream, n, out, crow, G, parts);
+  const float* h = hidden_layers(m, n, x, true);
+  float* act = m->act.as<float>();
+  float* pre = m->pre.as<float>();
+  float* g = m->gbuf.get<float>(n);
+  const int go = output_grid(n);
+  double* lp = m->lossbuf.get<double>(go);
+  hipLaunchKernelGGL(k_output, dim3(go), dim3(kBlock), 0, m->stream, n, m->width, h,
+                     P + m->woff[L], (float*)nullptr, t, g, pre + (L - 1) * len, lp);
+  PPE_LAUNCH_CHECK();
+  // pre[l] turns into the gradient of layer l's pre-activations, last to first
+  for (int l = L - 1; l > 0; --l) {
+    const dim3 grid((unsigned)((n + (int64_t)kTile - 1) / kTile),
+                    (m->width + kTileN - 1) / kTileN);
+    hipLaunchKernelGGL(k_layer<true>, grid, dim3(256), 0, m->stream, n, m->width, m->width,
+                       pre + l * len, P + m->woff[l], (const float*)nullptr, pre + (l - 1) * len,
+                       (float*)nullptr);
     PPE_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_sum_chunks, dim3(grid_for(out)), dim3(kBlock), 0, m->stream, (int64_t)out,
-                       nz, parts, dP + m->boff[l]);
-    PPE_LAUNCH_CHECK();
-    if (l > 0) {
-      // G2 [n x in] = G [n x out] . W [out x in], then times silu'(z_{l-1})
-      gemm(m, n, in, out, G, out, 1, P + m->woff[l], in, 1, G2);
-      const int64_t len = (int64_t)n * in;
-      hipLaunchKernelGGL(k_dsilu_mul, dim3(grid_for(len)), dim3(kBlock), 0, m->stream, len,
-                         pre + aoff[l - 1], G2);
-      PPE_LAUNCH_CHECK();
-      std::swap(G, G2);
-    }
   }
-  double loss = 0.0;
-  PPE_HIP(hipMemcpyAsync(&loss, lp + gl, sizeof(double), hipMemcpyDeviceToHost, m->stream));
-  PPE_HIP(hipStreamSynchronize(m->stream));
-  return loss;
+  const int chunk = grad_chunk(m, n);
+  const int nz = (int)(((int64_t)n + chunk - 1) / chunk);
+  float* parts = m->part.get<float>((size_t)nz * m->n_params);
+  for (int l0 = 0; l0 <= L; l0 += kMaxLayers) {
+    GradArgs a{};
+    int tiles = 0;
+    a.layers = std::min(kMaxLayers, L + 1 - l0);
+    for (int k = 0; k < a.layers; ++k) {
+      const int l = l0 + k;
+      a.l[k] = GradLayer{l == L ? g : pre + l * len, l == 0 ? x : act + (l - 1) * len, m->woff[l],
+                         m->boff[l], m->dims[l + 1], m->dims[l], tiles};
+      tiles += ((m->dims[l + 1] + kTile - 1) / kTile) * ((m->dims[l] + kTileN - 1) / kTileN);
+    }
+    hipLaunchKernelGGL(k_grads, dim3(tiles, nz), dim3(256), 0, m->stream, a, n, chunk,
+                       m->n_params, parts);
+    PPE_LAUNCH_CHECK();
+  }
+  hipLaunchKernelGGL(k_sum_grads, dim3(grid_for(m->n_params) + 1), dim3(kBlock), 0, m->stream,
+                     m->n_params, nz, parts, grad, lp, go, n, m->loss_h);
+  PPE_LAUNCH_CHECK();
 }
 
 void refresh_bf16(ppe_mlp* m) {
@@ -734,6 +892,7 @@ ppe_status ppe_mlp_create(int32_t n_in, int32_t width, int32_t n_hidden, void* s
 void ppe_mlp_destroy(ppe_mlp* m) {
   if (!m) return;
   (void)hipStreamSynchronize(m->stream);
+  if (m->loss_h) (void)hipHostFree(m->loss_h);
   delete m;
 }
 
@@ -800,8 +959,7 @@ ppe_status ppe_mlp_forward(ppe_mlp* m, int32_t n, const float* x, float* y, int 
       }
       PPE_LAUNCH_CHECK();
     } else {
-      float* yy = forward_fp32(m, n, x);
-      PPE_HIP(hipMemcpyAsync(y, yy, sizeof(float) * n, hipMemcpyDeviceToDevice, m->stream));
+      forward_fp32(m, n, x, y);
     }
     PPE_HIP(hipStreamSynchronize(m->stream));
     return PPE_OK;
@@ -812,11 +970,9 @@ ppe_status ppe_mlp_loss_grad(ppe_mlp* m, int32_t n, const float* x, const float*
                              double* loss) {
   if (!m || n < 1 || !x || !t || !grad) return PPE_ERR_ARG;
   return mlp_guard(m, [&]() -> ppe_status {
-    const double l = loss_grad(m, n, x, t);
-    PPE_HIP(hipMemcpyAsync(grad, m->grad.as<float>(), sizeof(float) * m->n_params,
-                           hipMemcpyDeviceToDevice, m->stream));
+    loss_grad(m, n, x, t, grad);
     PPE_HIP(hipStreamSynchronize(m->stream));
-    if (loss) *loss = l;
+    if (loss) *loss = *m->loss_h;
     return PPE_OK;
   });
 }
@@ -825,7 +981,7 @@ ppe_status ppe_mlp_train_step(ppe_mlp* m, int32_t n, const float* x, const float
                               double* loss) {
   if (!m || n < 1 || !x || !t || !(lr > 0)) return PPE_ERR_ARG;
   return mlp_guard(m, [&]() -> ppe_status {
-    const double l = loss_grad(m, n, x, t);
+    loss_grad(m, n, x, t, m->grad.get<float>(m->n_params));
     m->adam_t += 1;
     const float c1 = 1.0f - std::pow(0.9f, (float)m->adam_t);
     const float c2 = 1.0f - std::pow(0.999f, (float)m->adam_t);
@@ -835,7 +991,7 @@ ppe_status ppe_mlp_train_step(ppe_mlp* m, int32_t n, const float* x, const float
     PPE_LAUNCH_CHECK();
     refresh_bf16(m);
     PPE_HIP(hipStreamSynchronize(m->stream));
-    if (loss) *loss = l;
+    if (loss) *loss = *m->loss_h;
     return PPE_OK;
   });
 }

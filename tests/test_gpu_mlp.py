@@ -55,6 +55,34 @@ def test_fp32_loss_and_gradient_match_oracle(n):
     assert np.abs(y - y_ref).max() <= 1e-5 * max(1.0, np.abs(y_ref).max())
 
 
+# edges of the 32 x 32 product tiles, of the 128-column workgroup tiles, of the
+# staged depth (64) and of the gradient's row chunks (128 rows, 64 chunks)
+@pytest.mark.parametrize("n,width,hidden", [(1, 1, 1), (31, 32, 2), (33, 33, 3), (129, 65, 1),
+                                            (127, 128, 2), (8193, 100, 3), (500, 129, 2),
+                                            (64, 300, 2), (40, 5, 18)])
+def test_fp32_gradient_at_tile_edges(n, width, hidden):
+    import torch
+
+    net, shapes, theta = _net(seed=1, width=width, hidden=hidden)
+    rng = np.random.default_rng(n)
+    X = rng.normal(size=(n, 10)).astype(np.float32)
+    T = rng.normal(size=n).astype(np.float32)
+    loss, g = net.loss_grad(to_dev(X, torch.float32), to_dev(T, torch.float32))
+    l_ref, g_ref = omlp.loss_and_grad(theta, shapes, X.astype(np.float64), T.astype(np.float64))
+    assert abs(loss - l_ref) <= BWD_RTOL * l_ref
+    at = 0
+    for a, b in shapes:  # every layer's weights and biases by themselves
+        for size in (a * b, a):
+            ref = g_ref[at:at + size]
+            got = g[at:at + size].cpu().numpy()
+            assert np.linalg.norm(got - ref) <= BWD_RTOL * np.linalg.norm(ref) + 1e-7 * np.linalg.norm(g_ref)
+            at += size
+    assert at == net.n_params
+    y = net.forward(to_dev(X, torch.float32)).cpu().numpy()
+    y_ref, _, _ = omlp.forward(theta, shapes, X.astype(np.float64))
+    assert np.abs(y - y_ref).max() <= 1e-5 * max(1.0, np.abs(y_ref).max())
+
+
 # 100003 cells: more 32-cell tiles than one launch's waves, so waves stride
 # over several tiles, with a ragged last tile
 @pytest.mark.parametrize("n", [1, 32, 1000, 12345, 100003])
