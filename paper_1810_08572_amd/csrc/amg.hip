@@ -1841,6 +1841,7 @@ void build_hierarchy(ppe_solver* s) {
     L.lpr_a = L.lpr_r = L.lpr_p = 0;
     L.fuse0 = true;
     L.ap_ok = false;
+    L.op_ok = false;
     if (lvl > 0 && n > 0) {
       PPE_ROWS(lanes_for(L.A), k_diag, n, n, L.A.rp(), L.A.ci(), L.A.v(), L.diag.get<double>(n),
                err);  // sets SE_DIAG

@@ -66,6 +66,10 @@ double bytes_per_iteration(const ppe_solver* s) {
     const ppe::Level& L = s->levels[l];
     const double n = L.n;
     const double mat = (l == 0) ? off0 * (vm + 4) + vm * n : (double)L.A.nnz * (vm + 4) + 4 * n;
+    if (L.op_ok) {  // the rest of the V-cycle is one dense product
+      total += n * n * v + 2 * n * v;
+      break;
+    }
     if (l == s->nlev - 1) {
       total += L.dense ? n * n * v + 2 * n * v : 2 * deg * (mat + 5 * v * n);
       continue;
@@ -256,6 +260,7 @@ ppe_status assemble_impl(ppe_solver* s, const double* face_coeff, const double* 
       }
       ppe::prepare_solve_levels(s);
       if (s->opt.precision == PPE_MIXED) ppe::make_fp32_hierarchy(s);
+      ppe::coarse_operator(s);
       if (s->opt.autotune) {
         const bool prof = s->prof;  // tuning launches are not measurements
         s->prof = false;

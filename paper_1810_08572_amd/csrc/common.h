@@ -177,6 +177,11 @@ struct Level {
   // coarsest level
   bool dense = false;
   DevBuf Ainv;           // dense inverse, FP64 in both precisions
+  // the V-cycle from this level down as one dense matrix (n rows of op_ld
+  // values), where it pays (coarse_operator)
+  bool op_ok = false;
+  int op_ld = 0;
+  DevBuf op;
   // V-cycle work vectors (FP64 in both precisions)
   DevBuf x, b, r, d, x2, d2, t;
 };
@@ -240,6 +245,7 @@ struct ppe_solver {
   // setup results read back once per hierarchy: the spectral bound of every
   // level (doubles [0, max_levels)), then the deferred setup error bits (int)
   ppe::DevBuf setup_out;
+  ppe::DevBuf cop_ws;  // coarse_operator's blocks of vectors
   ppe::DevBuf rmax;  // max column count of the last transposed operator (device int)
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   hipEvent_t tev0 = nullptr, tev1 = nullptr;  // autotuner timing
@@ -604,6 +610,9 @@ void vcycle(ppe_solver* s, int level, const double* b, double* x);
 // queued work stays short of it.  NULL: always run ahead.
 ppe_status pcg_solve(ppe_solver* s, const double* rhs, double* p, int use_x0, int* pred = nullptr);
 void prepare_solve_levels(ppe_solver* s);
+// Forms the V-cycle of a small coarse level as one dense matrix where that
+// pays (after prepare_solve_levels and, mixed, make_fp32_hierarchy).
+void coarse_operator(ppe_solver* s);
 void make_fp32_hierarchy(ppe_solver* s);
 // Time the candidate launch choices of every level's solve kernels and keep
 // the fastest (cached by level shape).

@@ -451,18 +451,156 @@ __global__ void k_cheb_first(int n, const double* __restrict__ b, const M* __res
   x[i] = v;
 }
 
-// Dense coarsest solve x = Ainv b (FP64 in both modes): one wave per row,
-// lanes over columns.
-__global__ void __launch_bounds__(kBlock) k_dense_gemv(int n, const double* __restrict__ Ainv,
+// Dense product x = G b (n rows of ld values, FP64 in both modes): the
+// coarsest level's inverse, or a coarse level's whole V-cycle.  One wave per
+// row, lanes over columns, eight loads of the row in flight per lane.
+constexpr int kGemvU = 8;
+__global__ void __launch_bounds__(kBlock) k_dense_gemv(int n, int ld, const double* __restrict__ G,
                                                        const double* __restrict__ b,
                                                        double* __restrict__ x) {
   const int i = (blockIdx.x * kBlock + threadIdx.x) / kWave;
   const int lane = threadIdx.x % kWave;
   double s = 0.0;
-  if (i < n)
-    for (int j = lane; j < n; j += kWave) s = s + Ainv[(size_t)i * n + j] * b[j];
+  if (i < n) {
+    const double* g = G + (size_t)i * ld;
+    int j = lane;
+    for (; j + (kGemvU - 1) * kWave < n; j += kGemvU * kWave) {
+      double w[kGemvU], v[kGemvU];
+#pragma unroll
+      for (int u = 0; u < kGemvU; ++u) {
+        w[u] = g[j + u * kWave];
+        v[u] = b[j + u * kWave];
+      }
+#pragma unroll
+      for (int u = 0; u < kGemvU; ++u) s = s + w[u] * v[u];
+    }
+    for (; j < n; j += kWave) s = s + g[j] * b[j];
+  }
   s = wave_sum(s);
   if (i < n && lane == 0) x[i] = s;
+}
+
+// ---- the V-cycle applied to a block of vectors (the columns of the identity
+// on the level where it starts), row-major with ld a multiple of 64: one wave
+// takes one row and 64 columns, so every load of the block is 512 contiguous
+// bytes, and the matrix entry is the same for the whole wave.
+enum BlockOp : int {
+  B_RESID = 0,  // Y = B - A X
+  B_CHEB = 1,   // r = (B - A X)/sd; D = c1 D + c2 r; Y = X + D
+  B_MUL = 2,    // Y = A X
+  B_ADD = 3,    // Y += A X
+};
+
+// B may be NULL: the identity.  The blocks of one column tile meet on one XCD
+// (blockIdx.x mod 8 picks it), whose L2 then holds the tile of X.
+template <int OP, class M>
+__global__ void __launch_bounds__(kBlock) k_block_rows(int n, int ld, const int* __restrict__ rp,
+                                                       const int* __restrict__ ci,
+                                                       const M* __restrict__ v,
+                                                       const double* __restrict__ X,
+                                                       const double* __restrict__ B,
+                                                       const M* __restrict__ sd, double c1,
+                                                       double c2, double* __restrict__ D,
+                                                       double* __restrict__ Y, int rows_per_tile) {
+  constexpr int R = kBlock / kWave;
+  const int k = blockIdx.x >> 3;
+  const int tile = (blockIdx.x & 7) + 8 * (k / rows_per_tile);
+  const int i = __builtin_amdgcn_readfirstlane((k % rows_per_tile) * R + threadIdx.x / kWave);
+  const int c = tile * kWave + threadIdx.x % kWave;
+  if (i >= n || tile * kWave >= ld) return;
+  const size_t at = (size_t)i * ld + c;
+  double s = 0.0;
+  const int k1 = rp[i + 1];
+  int q = rp[i];
+  for (; q + 8 <= k1; q += 8) {
+    double x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = X[(size_t)ci[q + u] * ld + c];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s = s + (double)v[q + u] * x[u];
+  }
+  for (; q < k1; ++q) s = s + (double)v[q] * X[(size_t)ci[q] * ld + c];
+  if (OP == B_MUL) {
+    Y[at] = s;
+  } else if (OP == B_ADD) {
+    Y[at] = Y[at] + s;
+  } else {
+    const double b = B ? B[at] : (c == i ? 1.0 : 0.0);
+    if (OP == B_RESID) {
+      Y[at] = b - s;
+    } else {
+      const double r = (b - s) / (double)sd[i];
+      const double dn = (c1 == 0.0 ? 0.0 : c1 * D[at]) + c2 * r;
+      D[at] = dn;
+      Y[at] = X[at] + dn;
+    }
+  }
+}
+
+// The first smoothing step on a block: D = Y = inv_theta B / sd.
+template <class M>
+__global__ void __launch_bounds__(kBlock) k_block_first(int n, int ld, const double* __restrict__ B,
+                                                        const M* __restrict__ sd, double inv_theta,
+                                                        double* __restrict__ D,
+                                                        double* __restrict__ Y) {
+  const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (e >= (int64_t)n * ld) return;
+  const int i = (int)(e / ld), c = (int)(e % ld);
+  const double w = inv_theta * ((B ? B[e] : (c == i ? 1.0 : 0.0)) / (double)sd[i]);
+  D[e] = w;
+  Y[e] = w;
+}
+
+// The first two smoothing steps from a zero guess on the identity: the first
+// iterate is diagonal, so A X has A's entries only.  One workgroup per row,
+// the row of A X in LDS.
+template <class M>
+__global__ void __launch_bounds__(kBlock) k_block_start(int n, int ld, const int* __restrict__ rp,
+                                                        const int* __restrict__ ci,
+                                                        const M* __restrict__ v,
+                                                        const M* __restrict__ sd, double inv_theta,
+                                                        double c1, double c2,
+                                                        double* __restrict__ D,
+                                                        double* __restrict__ Y) {
+  extern __shared__ double ax[];  // ld
+  const int i = blockIdx.x;
+  for (int c = threadIdx.x; c < ld; c += kBlock) ax[c] = 0.0;
+  __syncthreads();
+  for (int k = rp[i] + threadIdx.x; k < rp[i + 1]; k += kBlock) {
+    const int j = ci[k];
+    ax[j] = (double)v[k] * (inv_theta * (1.0 / (double)sd[j]));
+  }
+  __syncthreads();
+  const double si = (double)sd[i], x1 = inv_theta * (1.0 / si);
+  for (int c = threadIdx.x; c < ld; c += kBlock) {
+    const double xc = c == i ? x1 : 0.0;
+    const double r = ((c == i ? 1.0 : 0.0) - ax[c]) / si;
+    const double dn = c1 * xc + c2 * r;
+    D[(size_t)i * ld + c] = dn;
+    Y[(size_t)i * ld + c] = xc + dn;
+  }
+}
+
+// Y = G X with a dense G (n x n): the coarsest level's inverse.
+__global__ void __launch_bounds__(kBlock) k_block_dense(int n, int ld, const double* __restrict__ G,
+                                                        const double* __restrict__ X,
+                                                        double* __restrict__ Y) {
+  const int i = __builtin_amdgcn_readfirstlane(
+      (int)(blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave));
+  const int c = blockIdx.y * kWave + threadIdx.x % kWave;
+  if (i >= n) return;
+  double s = 0.0;
+  const double* g = G + (size_t)i * n;
+  int j = 0;
+  for (; j + 8 <= n; j += 8) {
+    double x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = X[(size_t)(j + u) * ld + c];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s = s + g[j + u] * x[u];
+  }
+  for (; j < n; ++j) s = s + g[j] * X[(size_t)j * ld + c];
+  Y[(size_t)i * ld + c] = s;
 }
 
 // Row l1 norms sum_j |a_ij| of the finest level (ELL off-diagonal slots,
@@ -1223,6 +1361,13 @@ bool smooth_steps(ppe_solver* s, Level& L, const double* b, const double* cur, i
   return dotted;
 }
 
+// Whether the V-cycle from level l down is one dense product: the coarsest
+// level's inverse, or the level's coarse_operator.
+bool one_product(const ppe_solver* s, int l) {
+  const Level& L = s->levels[l];
+  return L.op_ok || (l == s->nlev - 1 && L.dense);
+}
+
 // Whether the V-cycle's first smoothing on level l (l > 0, from a zero
 // guess) starts with the plain first step (not the fused first two steps),
 // which the restriction into level l then takes; and where that step's
@@ -1230,7 +1375,7 @@ bool smooth_steps(ppe_solver* s, Level& L, const double* b, const double* cur, i
 // level) when the smoother has one step, else its ping-pong buffer x2.
 bool restricted_first(const ppe_solver* s, int l) {
   const Level& C = s->levels[l];
-  if (l == s->nlev - 1 && C.dense) return false;
+  if (one_product(s, l)) return false;
   return !(C.c1.size() >= 1 && C.fuse0);
 }
 template <class M>
@@ -1253,17 +1398,18 @@ bool vcycle_t(ppe_solver* s, int l, const double* b, double* x, const PcgDot* do
   if (n == 0) return false;
   double* xa = L.x2.as<double>();
   double* xb = L.d2.as<double>();
+  if (one_product(s, l)) {
+    const double* G = L.op_ok ? L.op.as<double>() : L.Ainv.as<double>();
+    launch(s,
+           [&]() {
+             return std::make_pair(std::string("k_dense_gemv"),
+                                   8.0 * (double)n * n + 16.0 * n);  // matrix, b, x
+           },
+           k_dense_gemv, dim3(grid_for((int64_t)n * kWave)), dim3(kBlock), n,
+           L.op_ok ? L.op_ld : n, G, b, x);
+    return false;
+  }
   if (l == s->nlev - 1) {
-    if (L.dense) {
-      launch(s,
-             [&]() {
-               return std::make_pair(std::string("k_dense_gemv"),
-                                     8.0 * (double)n * n + 16.0 * n);  // inverse, b, x
-             },
-             k_dense_gemv, dim3(grid_for((int64_t)n * kWave)), dim3(kBlock), n,
-             (const double*)L.Ainv.as<double>(), b, x);
-      return false;
-    }
     double* t = L.r.as<double>();
     smooth<M>(s, L, b, nullptr, t, xa, xb, nullptr, first_done);
     return smooth<M>(s, L, b, t, x, xa, xb, dot);
@@ -1289,6 +1435,9 @@ bool vcycle_t(ppe_solver* s, int l, const double* b, double* x, const PcgDot* do
 }
 
 }  // namespace
+
+constexpr int kCopRows = 2048;                 // 33 MB of matrix at most
+constexpr int64_t kCopOnce = int64_t(32) << 20;
 
 void drop_graph(ppe_solver* s) {
   if (s->gexec) (void)hipGraphExecDestroy(s->gexec);
@@ -1412,6 +1561,94 @@ void prepare_solve_levels(ppe_solver* s) {
       L.c2.push_back(2.0 * rho_j / delta);
       rho_prev = rho_j;
     }
+  }
+}
+
+namespace {
+template <int OP, class M>
+void block_rows(ppe_solver* s, const Csr& A, int ld, const double* X, const double* B,
+                const M* sd, double c1, double c2, double* D, double* Y) {
+  const int per = (A.n + kBlock / kWave - 1) / (kBlock / kWave), tiles = ld / kWave;
+  hipLaunchKernelGGL((k_block_rows<OP, M>), dim3(8 * ((tiles + 7) / 8) * per), dim3(kBlock), 0,
+                     s->stream, A.n, ld, A.rp(), A.ci(), LevelData<M>::val(A), X, B, sd, c1, c2, D,
+                     Y, per);
+  PPE_LAUNCH_CHECK();
+}
+
+// X = M B with M the V-cycle from level l down and B a block of vectors (NULL:
+// the identity); the steps of vcycle_t, vector for vector.  ws: free
+// workspace, four blocks of this level and what the levels below take.
+template <class M>
+void block_vcycle(ppe_solver* s, int l, int ld, const double* B, double* X, double* ws) {
+  Level& L = s->levels[l];
+  const int n = L.n;
+  const size_t len = (size_t)n * ld;
+  if (l == s->nlev - 1) {
+    hipLaunchKernelGGL(k_block_dense, dim3((n + kBlock / kWave - 1) / (kBlock / kWave), ld / kWave),
+                       dim3(kBlock), 0, s->stream, n, ld, L.Ainv.as<double>(), B, X);
+    PPE_LAUNCH_CHECK();
+    return;
+  }
+  const int deg = 1 + (int)L.c1.size();
+  const M* sd = smooth_diag<M>(s, L);
+  double *D = ws, *u = ws + len, *w = ws + 2 * len, *r = ws + 3 * len;
+  int step = 2;
+  if (!B && deg >= 2) {
+    hipLaunchKernelGGL(k_block_start<M>, dim3(n), dim3(kBlock), sizeof(double) * ld, s->stream, n,
+                       ld, L.A.rp(), L.A.ci(), LevelData<M>::val(L.A), sd, L.inv_theta, L.c1[0],
+                       L.c2[0], D, u);
+    step = 3;
+  } else {
+    hipLaunchKernelGGL(k_block_first<M>, dim3(grid_for((int64_t)len)), dim3(kBlock), 0, s->stream,
+                       n, ld, B, sd, L.inv_theta, D, u);
+  }
+  PPE_LAUNCH_CHECK();
+  auto steps = [&](int from) {
+    for (int k = from; k <= deg; ++k) {
+      const double c1 = k == 1 ? 0.0 : L.c1[k - 2], c2 = k == 1 ? L.inv_theta : L.c2[k - 2];
+      block_rows<B_CHEB, M>(s, L.A, ld, u, B, sd, c1, c2, D, w);
+      std::swap(u, w);
+    }
+  };
+  steps(step);
+  block_rows<B_RESID, M>(s, L.A, ld, u, B, sd, 0.0, 0.0, nullptr, r);
+  const size_t clen = (size_t)s->levels[l + 1].n * ld;
+  double *bc = ws + 4 * len, *ec = bc + clen;
+  block_rows<B_MUL, M>(s, L.R, ld, r, nullptr, nullptr, 0.0, 0.0, nullptr, bc);
+  block_vcycle<M>(s, l + 1, ld, bc, ec, ec + clen);
+  block_rows<B_ADD, M>(s, L.P, ld, ec, nullptr, nullptr, 0.0, 0.0, nullptr, u);
+  steps(1);
+  PPE_HIP(hipMemcpyAsync(X, u, sizeof(double) * len, hipMemcpyDeviceToDevice, s->stream));
+}
+}  // namespace
+
+// A coarse level's part of the V-cycle is a chain of dispatches on a few
+// hundred rows, each 3 to 5 us whatever it does (six for a level above the
+// coarsest one): its matrix, formed once, takes one.  Forming it costs about
+// three products of A with an n x n block.  A pressure system is sure of one
+// solve only, some fifteen V-cycles, so only a level past the first coarse one
+// with at most kCopOnce multiply-adds in such a product takes it.  A shifted
+// system is solved several times (three velocity components, the Picard
+// passes of many steps): eight times as many there, and on any coarse level.
+void coarse_operator(ppe_solver* s) {
+  if (s->n_active == 0 || s->nlev < 2 || !s->levels[s->nlev - 1].dense) return;
+  const int64_t most = s->shifted ? 8 * kCopOnce : kCopOnce;
+  for (int l = s->shifted ? 1 : 2; l < s->nlev - 1; ++l) {
+    Level& L = s->levels[l];
+    if (L.op_ok) return;
+    if (L.n == 0 || L.n > kCopRows || L.A.nnz * (int64_t)L.n > most) continue;
+    const int ld = (L.n + kWave - 1) / kWave * kWave;
+    size_t need = 0;
+    for (int k = l; k < s->nlev; ++k) need += (size_t)6 * s->levels[k].n * ld;
+    double* ws = s->cop_ws.get<double>(need);
+    double* op = L.op.get<double>((size_t)L.n * ld);
+    if (s->opt.precision == PPE_MIXED)
+      block_vcycle<float>(s, l, ld, nullptr, op, ws);
+    else
+      block_vcycle<double>(s, l, ld, nullptr, op, ws);
+    L.op_ld = ld;
+    L.op_ok = true;
+    return;
   }
 }
 
@@ -1776,7 +2013,7 @@ template <class M>
 void tune_level(ppe_solver* s, int l) {
   Level& L = s->levels[l];
   const bool coarsest = l == s->nlev - 1;
-  if (L.n == 0 || (coarsest && L.dense)) return;
+  if (L.n == 0 || one_product(s, l)) return;
   double* x = L.x.as<double>();
   double* b = L.b.as<double>();
   double* d = L.d.as<double>();
