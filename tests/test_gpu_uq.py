@@ -128,3 +128,58 @@ def test_smallest_expansions():
     T = np.linspace(-1, 1, 7)[:, None]
     Ye = q.eval(T, W).cpu().numpy()[:, 0]
     assert np.abs(Ye - (1.0 + 2.0 * T[:, 0] - 0.5 * T[:, 0] ** 4)).max() <= 1e-13
+
+
+# the matrix-core product's edges (16-row and 16-column tiles, 64 rows and 64
+# columns of a workgroup, 32 staged columns), the reflections of one column,
+# of more columns than a workgroup's waves take at a time, and of a set whose
+# factorisation does not fit in LDS (M K words and more)
+@pytest.mark.parametrize("kinds,degree,M,n_out", [
+    (["uniform"], 0, 1, 1), (["normal"], 1, 2, 17), (["uniform"] * 2, 3, 10, 64),
+    (["uniform"] * 3, 4, 35, 65), (["normal", "uniform"], 5, 63, 15), (["uniform"] * 3, 5, 65, 130),
+    (["uniform"] * 4, 4, 200, 33), (["uniform"] * 4, 5, 400, 70), (["uniform"] * 6, 3, 260, 5)])
+def test_fit_eval_stats_at_tile_edges(kinds, degree, M, n_out):
+    import torch
+
+    import paper_1810_08572_amd as ppe
+
+    ok = [uq.NORMAL if k == "normal" else uq.UNIFORM for k in kinds]
+    q = ppe.PolynomialChaos(kinds, degree)
+    X, _ = latin_hypercube(kinds, M, seed=M)
+    Y = np.random.default_rng(M).normal(size=(M, n_out))
+    al = uq.total_degree_indices(len(kinds), degree)
+    V = uq.vandermonde(ok, al, X)
+    # a backward-stable least-squares solution differs by eps times the
+    # condition number (1 + its square times the residual): the bar of the
+    # well-conditioned cases, 1e-12, scaled by it
+    cond = np.linalg.cond(V)
+    W = q.fit(X, to_dev(Y, torch.float64)).cpu().numpy()
+    Wo = uq.fit(V, Y)
+    assert np.abs(W - Wo).max() <= 1e-14 * (100 + cond ** 2) * np.abs(Wo).max()
+    Ye = q.eval(X, to_dev(Wo, torch.float64)).cpu().numpy()
+    assert np.abs(Ye - V @ Wo).max() <= 1e-13 * (np.abs(V) @ np.abs(Wo)).max()
+    mean, var, first, total = [t.cpu().numpy() for t in q.stats(to_dev(Wo, torch.float64))]
+    mo, vo, fo, to = uq.statistics(al, Wo)
+    assert np.array_equal(mean, mo) and np.abs(var - vo).max() <= 1e-12 * np.abs(vo).max()
+    assert np.abs(first - fo).max(initial=0) <= 1e-12 and np.abs(total - to).max(initial=0) <= 1e-12
+
+
+def test_rank_deficient_fit_leaves_the_coefficients_alone():
+    import torch
+
+    import paper_1810_08572_amd as ppe
+
+    q = ppe.PolynomialChaos(KINDS, 2)
+    X = np.repeat(np.random.default_rng(0).normal(size=(4, 3)), 3, axis=0)
+    Y = to_dev(np.ones((12, 70)), torch.float64)
+    keep = torch.empty
+    W = to_dev(np.full((q.n_terms, 70), 7.0), torch.float64)
+    torch.empty = lambda *a, **k: W
+    try:
+        with pytest.raises(ppe.PpeError):
+            q.fit(X, Y)
+    finally:
+        torch.empty = keep
+    assert bool((W == 7.0).all())
+    good = q.fit(q.nodes("tensor", 3)[0], to_dev(np.ones((27, 70)), torch.float64))
+    assert abs(float(good[0, 0]) - 1.0) <= 1e-13
