@@ -448,6 +448,126 @@ __global__ void __launch_bounds__(kBlock) k_ap_merge_ell(
   if (COUNT) counts[i] = out;
 }
 
+// ------------------------------------------------------------------ MIS-2, small levels
+// All rounds of a level whose strong graph fits in one workgroup's LDS, and
+// the numbering of its roots: the same synchronous rounds as above on keys
+// (state included) held in LDS, columns in 16 bits.  A round's two passes are
+// 3 to 4 us each as dispatches whatever the level's size, and the host reads
+// the undecided count after a guessed number of them; here a round is two
+// barriers and one compute unit's LDS reads, 0.1 us per 400 entries and pass.
+// So it pays up to about kMisEntries: 16^3 (2,816 rows of six slots, 13
+// rounds) takes 58 us in place of 30 dispatches and two or three round trips
+// (assembly 702 -> 639 us), while a level of 605 rows and 47 k entries took
+// 165 us here and takes 65 in dispatches.  LPR lanes per row; rows as slots
+// (rp NULL: W columns of slot k at k n, the row itself = none) or CSR with the
+// strong flags.
+constexpr int64_t kMisEntries = 20480;
+constexpr int kMisThreads = 1024;
+inline size_t mis_small_lds(int64_t n, int64_t entries, bool csr) {
+  return (size_t)(16 * n + (csr ? 4 * (n + 1) : 0) + 2 * entries);
+}
+
+__global__ void __launch_bounds__(kMisThreads) k_mis_small(
+    int n, int lpr, int W, const int* __restrict__ scol, const int* __restrict__ rp,
+    const int* __restrict__ ci, const unsigned char* __restrict__ strong, uint32_t salt,
+    unsigned char* __restrict__ state, int* __restrict__ root_id, long long* __restrict__ n_roots) {
+  extern __shared__ unsigned long long mis_lds[];
+  __shared__ int wsum[kMisThreads / kWave];
+  unsigned long long* key = mis_lds;
+  unsigned long long* m1 = key + n;
+  int* ptr = reinterpret_cast<int*>(m1 + n);  // CSR only
+  unsigned short* col = reinterpret_cast<unsigned short*>(ptr + (rp ? n + 1 : 0));
+  const int t = threadIdx.x, lane = t % lpr, groups = kMisThreads / lpr;
+  for (int i = t; i < n; i += kMisThreads) key[i] = mis_key(state[i], i, salt);
+  if (rp) {
+    for (int i = t; i <= n; i += kMisThreads) ptr[i] = rp[i];
+    __syncthreads();
+    // a weak entry stores its row, whose key every maximum holds anyway
+    for (int i = t / lpr; i < n; i += groups)
+      for (int k = ptr[i] + lane; k < ptr[i + 1]; k += lpr)
+        col[k] = (unsigned short)(strong[k] ? ci[k] : i);
+  } else {
+    for (int e = t; e < W * n; e += kMisThreads) col[e] = (unsigned short)scol[e];
+  }
+  __syncthreads();
+  // the largest of v over row i and its strong neighbours, in every lane
+  auto row_max = [&](int i, const unsigned long long* v) {
+    unsigned long long m = v[i];
+    int k = rp ? ptr[i] + lane : lane * n + i;
+    const int k1 = rp ? ptr[i + 1] : W * n, step = rp ? lpr : lpr * n;
+    for (; k + 3 * step < k1; k += 4 * step) {
+      unsigned long long x[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) x[u] = v[col[k + u * step]];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) m = x[u] > m ? x[u] : m;
+    }
+    for (; k < k1; k += step) {
+      const unsigned long long x = v[col[k]];
+      m = x > m ? x : m;
+    }
+    for (int o = lpr / 2; o > 0; o >>= 1) {
+      const unsigned long long x = __shfl_xor(m, o, kWave);
+      m = x > m ? x : m;
+    }
+    return m;
+  };
+  // every lane group runs the same trips, so that the shuffles see all lanes
+  const int trips = (n + groups - 1) / groups;
+  for (;;) {
+    for (int q = 0; q < trips; ++q) {
+      const int i = q * groups + t / lpr;
+      const unsigned long long m = row_max(i < n ? i : n - 1, key);
+      if (i < n && lane == 0) m1[i] = m;
+    }
+    __syncthreads();
+    int und = 0;
+    for (int q = 0; q < trips; ++q) {
+      const int i = q * groups + t / lpr;
+      const unsigned long long m = row_max(i < n ? i : n - 1, m1);
+      if (i >= n || lane != 0) continue;
+      const unsigned long long own = key[i];
+      if ((own >> 62) != S_UND) continue;
+      const unsigned long long low = own & ((1ull << 62) - 1ull);
+      if (m == own)
+        key[i] = ((unsigned long long)S_IN << 62) | low;
+      else if ((m >> 62) == S_IN)
+        key[i] = low;  // S_OUT
+      else
+        und = 1;
+    }
+    if (!__syncthreads_or(und)) break;
+  }
+  // states out; roots numbered in row order (each thread a run of rows)
+  const int per = (n + kMisThreads - 1) / kMisThreads, i0 = t * per, i1 = min(n, i0 + per);
+  int cnt = 0;
+  for (int i = i0; i < i1; ++i) {
+    const int st = (int)(key[i] >> 62);
+    state[i] = (unsigned char)st;
+    cnt += st == S_IN ? 1 : 0;
+  }
+  int inc = cnt;
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int u = __shfl_up(inc, o, kWave);
+    if (t % kWave >= o) inc += u;
+  }
+  if (t % kWave == kWave - 1) wsum[t / kWave] = inc;
+  __syncthreads();
+  int at = inc - cnt, total = 0;
+  for (int q = 0; q < kMisThreads / kWave; ++q) {
+    if (q < t / kWave) at += wsum[q];
+    total += wsum[q];
+  }
+  for (int i = i0; i < i1; ++i) {
+    root_id[i] = at;
+    at += (key[i] >> 62) == S_IN ? 1 : 0;
+  }
+  if (t == 0) {
+    root_id[n] = total;
+    *n_roots = total;
+  }
+}
+
 // ------------------------------------------------------------------ aggregation
 __global__ void k_is_root(int n, const unsigned char* __restrict__ state, int* __restrict__ root) {
   int i = blockIdx.x * kBlock + threadIdx.x;
@@ -923,7 +1043,11 @@ __global__ void __launch_bounds__(kBlock) k_spgemm_compact(int n, const int* __r
 // the coarsest level) is transposed without atomics on its few column
 // counters and without sorting: a one-workgroup count, then one workgroup
 // per column that collects the column's entries in storage order.
+// Every column's workgroup walks all entries twice, so the path pays only while
+// columns x entries is small: a 64^3 step's first coarse prolongator (605 x
+// 92 k) took 95 us here and takes about 30 on the general path.
 constexpr int kNarrowCols = 1024;
+constexpr int64_t kNarrowWork = int64_t(8) << 20;
 constexpr int kNarrowU = 8;  // entries per lane whose loads are issued together
 
 // Column counts in LDS, then T's row pointers trp[0..m] (exclusive scan over
@@ -1122,7 +1246,7 @@ __global__ void __launch_bounds__(kWave) k_rank_rows(const int* __restrict__ rp,
 // pivot row is divided by the pivot with a_kk replaced by 1, and every other
 // row i gets a_ij -= f_i a_kj with a_ik replaced by 0 (f the pivot column),
 // which leaves A^-1 in place of A.  Up to kDenseBlk rows one workgroup does
-// it from the n x 2n row-major array G = [A | I] (k_dense_inverse_blk);
+// it from the n x n row-major array G = A (k_dense_inverse_blk);
 // larger levels take the blocked form over many workgroups (k_ginv_*).
 constexpr int kDenseBlk = 128;
 
@@ -1153,7 +1277,7 @@ __global__ void __launch_bounds__(1024) k_dense_inverse_blk(int n, const double*
 #pragma unroll
     for (int c = 0; c < B; ++c) {
       const int i = i0 + r, j = j0 + c;
-      a[r][c] = (i < n && j < n) ? Gm[(size_t)i * 2 * n + j] : (i == j ? 1.0 : 0.0);
+      a[r][c] = (i < n && j < n) ? Gm[(size_t)i * n + j] : (i == j ? 1.0 : 0.0);
     }
   const int nb = (n + B - 1) / B;
   for (int K = 0; K < nb; ++K) {
@@ -1258,102 +1382,166 @@ __global__ void __launch_bounds__(1024) k_dense_inverse_blk(int n, const double*
 //   G'[I][J] = G[I][J] - G[I][K] (D^-1 G[K][J]).
 // Reading only the old matrix, the blocks need no ordering among themselves.
 
-// D^-1 of block K of the N x N row-major G into Dinv (32 x 32): one 1024-thread
-// workgroup, one entry per thread, two barriers per scalar step.
-__global__ void __launch_bounds__(1024) k_ginv_diag(int N, const double* __restrict__ G, int K,
+//
+// One dispatch per block step: the products run on the FP64 matrix cores (one
+// 16 x 16 quadrant per wave), and the workgroup that rewrites the next
+// diagonal block inverts it at once for the next step.  A 279-row level takes
+// 11 dispatches and 120 us; with the diagonal block inverted by a dispatch of
+// its own (two barriers per pivot) and the products added up from LDS it took
+// 21 and 225.
+typedef double double4_t __attribute__((ext_vector_type(4)));
+constexpr int kGinvB = 32, kGinvPitch = kGinvB + 4;
+
+// Inverts the 32 x 32 block held by a workgroup of 256 threads, thread t with
+// rows t / 32 + 8 q of column t mod 32.  Two pivots per step, by the inverse
+// of their 2 x 2 block: what a step costs is its chain (the pivots' rows and
+// columns through LDS and a barrier, a division, two products), not its
+// arithmetic.
+__device__ __forceinline__ void invert_block(double (&d)[4], int* __restrict__ flag) {
+  __shared__ double row[2][2][kGinvB], col[2][2][kGinvB];
+  const int c = threadIdx.x % kGinvB, r0 = threadIdx.x / kGinvB;
+  auto publish = [&](int k) {
+    const int buf = (k >> 1) & 1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = r0 + 8 * q;
+      if ((r & ~1) == k) row[buf][r & 1][c] = d[q];
+      if ((c & ~1) == k) col[buf][c & 1][r] = d[q];
+    }
+    __syncthreads();
+  };
+  publish(0);
+  for (int k = 0; k < kGinvB; k += 2) {
+    const int buf = (k >> 1) & 1;
+    const double p00 = row[buf][0][k], p01 = row[buf][0][k + 1];
+    const double p10 = row[buf][1][k], p11 = row[buf][1][k + 1];
+    const double x0 = row[buf][0][c], x1 = row[buf][1][c];
+    double f0[4], f1[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      f0[q] = col[buf][0][r0 + 8 * q];
+      f1[q] = col[buf][1][r0 + 8 * q];
+    }
+    double det = fma(p00, p11, -(p01 * p10));
+    if (!(p00 > 0.0 && det > 0.0)) {  // both pivots of the elimination are positive
+      if (threadIdx.x == 0) atomicOr(flag, SE_DENSE);
+      det = 1.0;
+    }
+    const double inv = 1.0 / det;
+    // this column of the pivots' rows of [P | I], then of P^-1 times them
+    const double u0 = c == k ? 1.0 : c == k + 1 ? 0.0 : x0;
+    const double u1 = c == k ? 0.0 : c == k + 1 ? 1.0 : x1;
+    const double n0 = (p11 * u0 - p01 * u1) * inv, n1 = (p00 * u1 - p10 * u0) * inv;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = r0 + 8 * q;
+      const double rest = ((c & ~1) == k ? 0.0 : d[q]) - (f0[q] * n0 + f1[q] * n1);
+      d[q] = r == k ? n0 : r == k + 1 ? n1 : rest;
+    }
+    if (k + 2 < kGinvB) publish(k + 2);
+  }
+}
+
+// Dinv = the inverse of G's first diagonal block (N x N row-major G).
+__global__ void __launch_bounds__(256) k_ginv_first(int N, const double* __restrict__ G,
                                                     double* __restrict__ Dinv,
                                                     int* __restrict__ flag) {
-  __shared__ double D[32][33];
-  __shared__ double rowk[32], colk[32];
-  const int r = threadIdx.x / 32, c = threadIdx.x % 32;
-  D[r][c] = G[(size_t)(K * 32 + r) * N + K * 32 + c];
-  __syncthreads();
-  for (int k = 0; k < 32; ++k) {
-    double p = D[k][k];
-    if (!(p > 0.0)) {
-      if (threadIdx.x == 0) atomicOr(flag, SE_DENSE);
-      p = 1.0;
-    }
-    if (r == 0) {
-      rowk[c] = (c == k ? 1.0 : D[k][c]) / p;
-      colk[c] = D[c][k];
-    }
-    __syncthreads();
-    if (r == k)
-      D[r][c] = rowk[c];
-    else
-      D[r][c] = c == k ? -colk[r] / p : D[r][c] - colk[r] * rowk[c];
-    __syncthreads();
-  }
-  Dinv[r * 32 + c] = D[r][c];
+  const int c = threadIdx.x % kGinvB, r0 = threadIdx.x / kGinvB;
+  double d[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) d[q] = G[(size_t)(r0 + 8 * q) * N + c];
+  invert_block(d, flag);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) Dinv[(r0 + 8 * q) * kGinvB + c] = d[q];
 }
 
-// One block step over all blocks: workgroup (J, I) writes block (I, J) of Gn.
-__global__ void __launch_bounds__(1024) k_ginv_update(int N, const double* __restrict__ G,
-                                                      const double* __restrict__ Dinv, int K,
-                                                      double* __restrict__ Gn) {
-  __shared__ double Ds[32][33], Rs[32][33], Cs[32][33], Ts[32][33];
+// The wave's quadrant of X Y (32 x 32 operands in LDS).  Operands and result
+// of v_mfma_f64_16x16x4f64: lane l holds X[l % 16][l / 16], Y[l / 16][l % 16]
+// and, as accumulator r, (X Y)[l / 16 + 4 r][l % 16].
+__device__ __forceinline__ double4_t block_product(const double (&X)[kGinvB][kGinvPitch],
+                                                   const double (&Y)[kGinvB][kGinvPitch], int r0,
+                                                   int c0) {
+  const int i = threadIdx.x % 16, kq = (threadIdx.x % kWave) / 16;
+  double4_t acc{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int k = 0; k < kGinvB; k += 4)
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(X[r0 + i][k + kq], Y[k + kq][c0 + i], acc, 0, 0, 0);
+  return acc;
+}
+
+// Block step K over all blocks: workgroup (J, I) writes block (I, J) of Gn;
+// the one of block (K + 1, K + 1) also leaves that block's inverse in next.
+__global__ void __launch_bounds__(256) k_ginv_step(int N, const double* __restrict__ G,
+                                                   const double* __restrict__ Dinv, int K,
+                                                   double* __restrict__ Gn,
+                                                   double* __restrict__ next,
+                                                   int* __restrict__ flag) {
+  __shared__ double Ds[kGinvB][kGinvPitch], Rs[kGinvB][kGinvPitch], Cs[kGinvB][kGinvPitch],
+      Ts[kGinvB][kGinvPitch];
   const int I = blockIdx.y, J = blockIdx.x;
-  const int r = threadIdx.x / 32, c = threadIdx.x % 32;
-  const size_t row = (size_t)I * 32 + r, col = (size_t)J * 32 + c;
+  const int c = threadIdx.x % kGinvB, r0 = threadIdx.x / kGinvB;
+  const size_t row = (size_t)I * kGinvB, col = (size_t)J * kGinvB, kk = (size_t)K * kGinvB;
   if (I == K && J == K) {
-    Gn[row * N + col] = Dinv[r * 32 + c];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      Gn[(row + r0 + 8 * q) * N + col + c] = Dinv[(r0 + 8 * q) * kGinvB + c];
     return;
   }
-  Ds[r][c] = Dinv[r * 32 + c];
-  if (J != K) Rs[r][c] = G[((size_t)K * 32 + r) * N + col];
-  if (I != K) Cs[r][c] = G[row * N + (size_t)K * 32 + c];
+  double g[4];  // the block itself, requested with the operands
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int r = r0 + 8 * q;
+    Ds[r][c] = Dinv[r * kGinvB + c];
+    if (J != K) Rs[r][c] = G[(kk + r) * N + col + c];
+    if (I != K) Cs[r][c] = G[(row + r) * N + kk + c];
+    g[q] = I != K && J != K ? G[(row + r) * N + col + c] : 0.0;
+  }
   __syncthreads();
-  if (I == K) {
-    double t = 0.0;
-    for (int k = 0; k < 32; ++k) t = t + Ds[r][k] * Rs[k][c];
-    Gn[row * N + col] = t;
+  const int wv = threadIdx.x / kWave, qr = 16 * (wv / 2), qc = 16 * (wv % 2);
+  const int ar = qr + (threadIdx.x % kWave) / 16, ac = qc + threadIdx.x % 16;  // acc 0's place
+  // D^-1 R for the blocks right and left of the diagonal one, -C D^-1 for
+  // those above and below it, C (D^-1 R) elsewhere
+  double4_t acc = J == K ? block_product(Cs, Ds, qr, qc) : block_product(Ds, Rs, qr, qc);
+  if (I == K || J == K) {
+    const double sign = J == K ? -1.0 : 1.0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) Gn[(row + ar + 4 * r) * N + col + ac] = sign * acc[r];
     return;
   }
-  if (J == K) {
-    double t = 0.0;
-    for (int k = 0; k < 32; ++k) t = t + Cs[r][k] * Ds[k][c];
-    Gn[row * N + col] = -t;
-    return;
-  }
-  double t = 0.0;
-  for (int k = 0; k < 32; ++k) t = t + Ds[r][k] * Rs[k][c];
-  Ts[r][c] = t;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) Ts[ar + 4 * r][ac] = acc[r];
   __syncthreads();
-  double u = 0.0;
-  for (int k = 0; k < 32; ++k) u = u + Cs[r][k] * Ts[k][c];
-  Gn[row * N + col] = G[row * N + col] - u;
-}
-
-// G = A padded with the identity to N x N (row-major, zeroed before): one
-// wavefront per row.
-__global__ void k_densify_sq(int n, int N, const int* __restrict__ rp, const int* __restrict__ ci,
-                             const double* __restrict__ v, double* __restrict__ G) {
-  const int i = (blockIdx.x * kBlock + threadIdx.x) / kWave, lane = threadIdx.x % kWave;
-  if (i >= N) return;
-  if (i >= n) {
-    if (lane == 0) G[(size_t)i * N + i] = 1.0;
-    return;
+  acc = block_product(Cs, Ts, qr, qc);
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 4; ++r) Ts[ar + 4 * r][ac] = acc[r];  // back to the loads' layout
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    g[q] = g[q] - Ts[r0 + 8 * q][c];
+    Gn[(row + r0 + 8 * q) * N + col + c] = g[q];
   }
-  for (int k = rp[i] + lane; k < rp[i + 1]; k += kWave) G[(size_t)i * N + ci[k]] = v[k];
+  if (I == K + 1 && J == K + 1) {
+    invert_block(g, flag);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) next[(r0 + 8 * q) * kGinvB + c] = g[q];
+  }
 }
 
-// Ainv (n x n) = the leading block of the N x N G.
-__global__ void k_lead_block(int n, int N, const double* __restrict__ G,
-                             double* __restrict__ Ainv) {
-  const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (p >= (int64_t)n * n) return;
-  const int i = (int)(p / n), j = (int)(p % n);
-  Ainv[p] = G[(size_t)i * N + j];
-}
-
-// G = [A | I] (n x 2n, row-major, zeroed before): one wavefront per row.
-__global__ void k_densify(int n, const int* __restrict__ rp, const int* __restrict__ ci,
-                          const double* __restrict__ v, double* __restrict__ G) {
-  const int i = (blockIdx.x * kBlock + threadIdx.x) / kWave, lane = threadIdx.x % kWave;
-  if (i >= n) return;
-  for (int k = rp[i] + lane; k < rp[i + 1]; k += kWave) G[(size_t)i * 2 * n + ci[k]] = v[k];
-  if (lane == 0) G[(size_t)i * 2 * n + n + i] = 1.0;
+// G = A padded with the identity to N x N, row-major: one workgroup per row,
+// assembled in LDS (N <= kDenseMax).
+__global__ void __launch_bounds__(kBlock) k_densify(int n, int N, const int* __restrict__ rp,
+                                                    const int* __restrict__ ci,
+                                                    const double* __restrict__ v,
+                                                    double* __restrict__ G) {
+  __shared__ double rowv[kDenseMax];
+  const int i = blockIdx.x;
+  for (int j = threadIdx.x; j < N; j += kBlock) rowv[j] = i >= n && j == i ? 1.0 : 0.0;
+  __syncthreads();
+  if (i < n)
+    for (int k = rp[i] + threadIdx.x; k < rp[i + 1]; k += kBlock) rowv[ci[k]] = v[k];
+  __syncthreads();
+  for (int j = threadIdx.x; j < N; j += kBlock) G[(size_t)i * N + j] = rowv[j];
 }
 
 // ------------------------------------------------------------------ host helpers
@@ -1545,7 +1733,7 @@ void transpose(ppe_solver* s, const Csr& A, Csr& T) {
   T.m = A.n;
   T.nnz = A.nnz;
   T.maxrow = 0;
-  if (T.n > 0 && T.n <= kNarrowCols && A.nnz > 0) {
+  if (T.n > 0 && T.n <= kNarrowCols && A.nnz > 0 && A.nnz * T.n <= kNarrowWork) {
     int* trp = T.rowptr.get<int>(T.n + 1);
     hipLaunchKernelGGL(k_narrow_count, dim3(1), dim3(1024), 0, s->stream, A.nnz, T.n, A.ci(), trp,
                        s->rmax.get<int>(1));
@@ -1920,34 +2108,46 @@ void build_hierarchy(ppe_solver* s) {
       int* root = s->tmp_i[2].get<int>(n + 1);
       int* root_id = L.mis_root.get<int>(n + 1);
       long long n_roots = 0;
-      // as many rounds before the first check as this level needed last time
-      for (int batch = std::max(3, L.mis_batch);; batch = 3) {
-        for (int k = 0; k < batch; ++k) {
-          if (k == batch - 1) fill_int(s, und, 0, 1);
-          if (ell) {
+      const int64_t entries = ell ? (int64_t)W * n : L.A.nnz;
+      const size_t lds = mis_small_lds(n, entries, !ell);
+      if (n <= 0xFFFF && entries <= kMisEntries && lds + 256 <= s->lds_max) {
+        int l1 = 1;  // lanes per row: no more than fill the workgroup
+        while (l1 < 16 && 2 * l1 * n <= kMisThreads) l1 *= 2;
+        long long* total = s->tmp_l[0].get<long long>(2);
+        hipLaunchKernelGGL(k_mis_small, dim3(1), dim3(kMisThreads), lds, s->stream, n, l1, W, scol,
+                           ell ? nullptr : L.A.rp(), L.A.ci(), strong, salt, st, root_id, total);
+        PPE_LAUNCH_CHECK();
+        read_back(s, {ReadItem{total, sizeof(long long), &n_roots}});
+      } else {
+        // as many rounds before the first check as this level needed last time
+        for (int batch = std::max(3, L.mis_batch);; batch = 3) {
+          for (int k = 0; k < batch; ++k) {
+            if (k == batch - 1) fill_int(s, und, 0, 1);
+            if (ell) {
 #define PPE_L(WM) PPE_ELL_K(k_mis_max1_ell<WM>, n, W, scol, st, salt, m1)
-            PPE_SLOTS(PPE_L);
+              PPE_SLOTS(PPE_L);
 #undef PPE_L
 #define PPE_L(WM) PPE_ELL_K(k_mis_max2_ell<WM>, n, W, scol, st, salt, m1, st2, und)
-            PPE_SLOTS(PPE_L);
+              PPE_SLOTS(PPE_L);
 #undef PPE_L
-          } else {
-            PPE_ROWS(lpr, k_mis_max1, n, n, L.A.rp(), L.A.ci(), strong, st, salt, m1);
-            PPE_ROWS(lpr, k_mis_max2, n, n, L.A.rp(), L.A.ci(), strong, st, salt, m1, st2, und);
+            } else {
+              PPE_ROWS(lpr, k_mis_max1, n, n, L.A.rp(), L.A.ci(), strong, st, salt, m1);
+              PPE_ROWS(lpr, k_mis_max2, n, n, L.A.rp(), L.A.ci(), strong, st, salt, m1, st2, und);
+            }
+            std::swap(st, st2);
+            ++L.mis_rounds;
           }
-          std::swap(st, st2);
-          ++L.mis_rounds;
+          hipLaunchKernelGGL(k_is_root, dim3(g), dim3(kBlock), 0, s->stream, n, st, root);
+          PPE_LAUNCH_CHECK();
+          const long long* total = exclusive_scan_async(s, root, root_id, n);
+          int left = 0;
+          read_back(s, {ReadItem{und, sizeof(int), &left},
+                        ReadItem{total, sizeof(long long), &n_roots}});
+          if (left == 0) break;
+          require(L.mis_rounds < 10000, PPE_ERR_INTERNAL, "MIS-2 did not terminate");
         }
-        hipLaunchKernelGGL(k_is_root, dim3(g), dim3(kBlock), 0, s->stream, n, st, root);
-        PPE_LAUNCH_CHECK();
-        const long long* total = exclusive_scan_async(s, root, root_id, n);
-        int left = 0;
-        read_back(s, {ReadItem{und, sizeof(int), &left},
-                      ReadItem{total, sizeof(long long), &n_roots}});
-        if (left == 0) break;
-        require(L.mis_rounds < 10000, PPE_ERR_INTERNAL, "MIS-2 did not terminate");
+        L.mis_batch = L.mis_rounds;
       }
-      L.mis_batch = L.mis_rounds;
       const int na = (int)n_roots;
       if (na > 0) {
         int* agg1 = L.agg1.get<int>(n);
@@ -2040,37 +2240,30 @@ void build_hierarchy(ppe_solver* s) {
     join();
     s->nlev = lvl + 1;
     if (n > 0 && n <= kDenseMax) {
-      double* Ainv = L.Ainv.get<double>((size_t)n * n);
-      double* G = nullptr;
-      if (n <= kDenseBlk) {  // [A | I] for the one-workgroup elimination
-        G = s->tmp_d[1].get<double>((size_t)2 * n * n);
-        fill_double(s, G, 0.0, (int64_t)2 * n * n);
-        hipLaunchKernelGGL(k_densify, dim3(grid_for((int64_t)n * kWave)), dim3(kBlock), 0,
-                           s->stream, n, L.A.rp(), L.A.ci(), L.A.v(), G);
-        PPE_LAUNCH_CHECK();
-      }
+      // the blocked form's matrix is padded to whole blocks
+      const int nb = (n + kGinvB - 1) / kGinvB, N = n <= kDenseBlk ? n : kGinvB * nb;
+      double* Ainv = L.Ainv.get<double>((size_t)N * N);
+      L.inv_ld = N;
+      double* G0 = s->tmp_d[1].get<double>((size_t)N * N + 2 * kGinvB * kGinvB);
+      double* Dinv = G0 + (size_t)N * N;
+      double* Dnext = Dinv + kGinvB * kGinvB;
+      double* G1 = Ainv;
+      // the last of the block steps, which alternate between the two, writes Ainv
+      if (n > kDenseBlk && nb % 2 == 0) std::swap(G0, G1);
+      hipLaunchKernelGGL(k_densify, dim3(N), dim3(kBlock), 0, s->stream, n, N, L.A.rp(), L.A.ci(),
+                         L.A.v(), G0);
+      PPE_LAUNCH_CHECK();
       if (n <= kDenseBlk) {
-        hipLaunchKernelGGL(k_dense_inverse_blk, dim3(1), dim3(1024), 0, s->stream, n, G, Ainv, err);
+        hipLaunchKernelGGL(k_dense_inverse_blk, dim3(1), dim3(1024), 0, s->stream, n, G0, Ainv, err);
       } else {
-        // 129 .. 1024 rows: blocked over nb x nb workgroups per block step
-        const int nb = (n + 31) / 32, N = 32 * nb;
-        double* G0 = s->tmp_d[1].get<double>((size_t)2 * N * N + 1024);
-        double* G1 = G0 + (size_t)N * N;
-        double* Dinv = G1 + (size_t)N * N;
-        fill_double(s, G0, 0.0, (int64_t)N * N);
-        hipLaunchKernelGGL(k_densify_sq, dim3(grid_for((int64_t)N * kWave)), dim3(kBlock), 0,
-                           s->stream, n, N, L.A.rp(), L.A.ci(), L.A.v(), G0);
-        PPE_LAUNCH_CHECK();
+        hipLaunchKernelGGL(k_ginv_first, dim3(1), dim3(256), 0, s->stream, N, G0, Dinv, err);
         for (int K = 0; K < nb; ++K) {
-          hipLaunchKernelGGL(k_ginv_diag, dim3(1), dim3(1024), 0, s->stream, N, G0, K, Dinv, err);
           PPE_LAUNCH_CHECK();
-          hipLaunchKernelGGL(k_ginv_update, dim3(nb, nb), dim3(1024), 0, s->stream, N, G0, Dinv,
-                             K, G1);
-          PPE_LAUNCH_CHECK();
+          hipLaunchKernelGGL(k_ginv_step, dim3(nb, nb), dim3(256), 0, s->stream, N, G0, Dinv, K, G1,
+                             Dnext, err);
           std::swap(G0, G1);
+          std::swap(Dinv, Dnext);
         }
-        hipLaunchKernelGGL(k_lead_block, dim3(grid_for((int64_t)n * n)), dim3(kBlock), 0,
-                           s->stream, n, N, G0, Ainv);
       }
       PPE_LAUNCH_CHECK();
       L.dense = true;

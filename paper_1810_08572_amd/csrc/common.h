@@ -176,7 +176,8 @@ struct Level {
   DevBuf scol;           // finest level: ELL strong columns (the row itself elsewhere)
   // coarsest level
   bool dense = false;
-  DevBuf Ainv;           // dense inverse, FP64 in both precisions
+  DevBuf Ainv;           // dense inverse, FP64 in both precisions (n rows of
+  int inv_ld = 0;        // inv_ld values)
   // the V-cycle from this level down as one dense matrix (n rows of op_ld
   // values), where it pays (coarse_operator)
   bool op_ok = false;

@@ -127,10 +127,19 @@ __global__ void __launch_bounds__(kSmallBlock) k_scan_small(const int* __restric
   __shared__ int buf[kSmallScan];
   __shared__ long long wsum[kSmallBlock / kWave];
   int m = INT32_MIN;
-  for (int i = threadIdx.x; i < n; i += kSmallBlock) {
-    const int v = in[i];
-    buf[i] = v;
-    m = max(m, v);
+  int item[kSmallItems];  // all loads requested before the first is stored
+#pragma unroll
+  for (int k = 0; k < kSmallItems; ++k) {
+    const int i = threadIdx.x + k * kSmallBlock;
+    item[k] = n > 0 ? in[i < n ? i : 0] : 0;
+  }
+#pragma unroll
+  for (int k = 0; k < kSmallItems; ++k) {
+    const int i = threadIdx.x + k * kSmallBlock;
+    if (i < n) {
+      buf[i] = item[k];
+      m = max(m, item[k]);
+    }
   }
   if (mx) {  // the largest count, max-ed into *mx as k_max_int does
     m = block_max<kSmallBlock>(m);

@@ -581,8 +581,9 @@ __global__ void __launch_bounds__(kBlock) k_block_start(int n, int ld, const int
   }
 }
 
-// Y = G X with a dense G (n x n): the coarsest level's inverse.
-__global__ void __launch_bounds__(kBlock) k_block_dense(int n, int ld, const double* __restrict__ G,
+// Y = G X with a dense G (n rows of gld values): the coarsest level's inverse.
+__global__ void __launch_bounds__(kBlock) k_block_dense(int n, int ld, int gld,
+                                                        const double* __restrict__ G,
                                                         const double* __restrict__ X,
                                                         double* __restrict__ Y) {
   const int i = __builtin_amdgcn_readfirstlane(
@@ -590,7 +591,7 @@ __global__ void __launch_bounds__(kBlock) k_block_dense(int n, int ld, const dou
   const int c = blockIdx.y * kWave + threadIdx.x % kWave;
   if (i >= n) return;
   double s = 0.0;
-  const double* g = G + (size_t)i * n;
+  const double* g = G + (size_t)i * gld;
   int j = 0;
   for (; j + 8 <= n; j += 8) {
     double x[8];
@@ -1406,7 +1407,7 @@ bool vcycle_t(ppe_solver* s, int l, const double* b, double* x, const PcgDot* do
                                    8.0 * (double)n * n + 16.0 * n);  // matrix, b, x
            },
            k_dense_gemv, dim3(grid_for((int64_t)n * kWave)), dim3(kBlock), n,
-           L.op_ok ? L.op_ld : n, G, b, x);
+           L.op_ok ? L.op_ld : L.inv_ld, G, b, x);
     return false;
   }
   if (l == s->nlev - 1) {
@@ -1585,7 +1586,7 @@ void block_vcycle(ppe_solver* s, int l, int ld, const double* B, double* X, doub
   const size_t len = (size_t)n * ld;
   if (l == s->nlev - 1) {
     hipLaunchKernelGGL(k_block_dense, dim3((n + kBlock / kWave - 1) / (kBlock / kWave), ld / kWave),
-                       dim3(kBlock), 0, s->stream, n, ld, L.Ainv.as<double>(), B, X);
+                       dim3(kBlock), 0, s->stream, n, ld, L.inv_ld, L.Ainv.as<double>(), B, X);
     PPE_LAUNCH_CHECK();
     return;
   }
