@@ -313,6 +313,7 @@ ppe_status ppe_refresh_shift(ppe_solver* s, const double* face_coeff, const doub
     ppe::require(diag_shift && (face_coeff || s->n_faces == 0), PPE_ERR_ARG, "NULL input array");
     PPE_HIP(hipEventRecord(s->ev0, s->stream));
     ppe::drop_graph(s);
+    s->solves_since_assemble = 0;
     try {
       ppe::refresh_fine_shift(s, face_coeff, diag_shift);
     } catch (...) {

@@ -277,11 +277,11 @@ struct ppe_solver {
   // entries): {lpr_a, fuse0, lpr_r, lpr_p, fuse_p}
   std::map<std::array<int, 4>, std::array<int, 5>> tune_cache;
 
-  // HIP graph of two PCG iterations, captured once per hierarchy
+  // HIP graph of two PCG iterations, captured once per system at most
   hipStream_t gstream = nullptr;
   hipGraphExec_t gexec = nullptr;
   bool graph_ok = false;
-  int solves_since_assemble = 0;
+  int solves_since_assemble = 0;  // or since the last refresh of a shift
 
   // geometry of the pressure-correction step: nodes, cell centres, face area
   // vectors, face vertices, vertex -> cells (sorted), local frames

@@ -1889,10 +1889,16 @@ ppe_status pcg_solve(ppe_solver* s, const double* rhs, double* p_out, int use_x0
            (const double*)tpart(T_RR), (const double*)sc, iters, cnt, (const double*)tpart(T_RZ),
            (const double*)rz[sl], rz[1 - sl], (const double*)zb[sl], p, cnt + 1);
   };
-  // Two iterations (both rz slots) captured into a HIP graph on the second
-  // solve with one hierarchy (a single solve per assembly would pay the
-  // capture without reuse), replayed while at least two iterations remain.
-  const bool graph = s->opt.use_graph && !s->prof && s->solves_since_assemble > 0;
+  // Two iterations (both rz slots) captured into a HIP graph once the system
+  // has been solved often enough to expect as many solves again, then replayed
+  // while at least two iterations remain.  A solve of 2.8 k rows saves 95 us by
+  // it (651 -> 557) and the capture costs 150; at 150 k rows it saves 11 of
+  // 1,176 us and costs 320, at 370 k 36 of 1,941 and 475.  So a few solves
+  // where the launches count, many elsewhere: capturing at the second solve
+  // had cost the Picard passes of a time step, each a new diagonal, more than
+  // their replays gave.
+  const int after = na <= 32768 ? 3 : 16;
+  const bool graph = s->opt.use_graph && !s->prof && s->solves_since_assemble >= after;
   if (graph && !s->graph_ok) capture_iterations(s, [&]() { body(0); body(1); });
   int it = 0, slot = 0;
   const int max_iter = s->opt.max_iter, every = s->opt.check_every;

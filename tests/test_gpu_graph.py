@@ -39,3 +39,28 @@ def test_graph_replays_equal_eager(precision):
             assert out[True][1] == out[False][1]
             assert out[True][2] == out[False][2]
             assert out[True][2] <= 1e-10
+
+
+# captured after 3 solves up to 32768 rows, after 16 above
+@pytest.mark.parametrize("shape,solves", [((28, 24, 20), 7), ((36, 34, 30), 20)])
+def test_graph_of_a_long_run_equals_eager(shape, solves):
+    import torch
+
+    import paper_1810_08572_amd as ppe
+
+    torch_dev()
+    m, fl, c, b0 = case(shape=shape, fl="ones")
+    out = {}
+    for g in (True, False):
+        sv = ppe.Solver(use_graph=g)
+        sv.set_mesh(m.n_cells, to_dev(m.owner, torch.int32), to_dev(m.neigh, torch.int32))
+        sv.assemble(to_dev(c, torch.float64), to_dev(fl, torch.float64))
+        out[g] = []
+        for rep in range(solves):
+            b = rhs_uniform(m.n_cells, seed=rep, center_mask=fl > 0)
+            r = sv.solve(to_dev(b, torch.float64))
+            torch.cuda.synchronize()
+            _ = (r.p * 2.0).sum().item()
+            out[g].append((r.p.cpu().numpy(), r.stats["iterations"], r.stats["rel_residual"]))
+    for x, y in zip(out[True], out[False]):
+        assert np.array_equal(x[0], y[0]) and x[1:] == y[1:] and x[2] <= 1e-10
