@@ -15,6 +15,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <mutex>
 #include <string>
 
@@ -425,15 +426,22 @@ __global__ void __launch_bounds__(64 * kWaves) k_mlp_infer_bf16(
 }
 
 // The inference pass used at every timestep.  With out^T = W h^T (features x
-// cells), a lane's accumulators r = 4q .. 4q+3 hold four consecutive
-// features of one cell: the k-quad the next layer's B operand reads.  So
-// activations and weights sit in LDS as quads of BF16 (8 bytes):
-// activation (k, cell) in quad (k/4) 32 + cell of the wave's buffer, weight
-// (f, k) in quad (k/4) 128 + f, and every MFMA operand is one 8-byte LDS
-// read per lane, consecutive across lanes.  The hidden weights are staged
-// once per workgroup; a layer's outputs are computed in registers for all
-// 128 features before they overwrite its inputs (a wave's LDS accesses
-// complete in issue order), so each wave needs one buffer.
+// cells), a lane's accumulators r = 4q .. 4q+3 of tile mt hold features
+// 32 mt + 8 q + 4 (lane / 32) + 0..3 of one cell: exactly the four values that
+// lane supplies as the next layer's B operand in k-step 4 mt + q.  So a wave
+// keeps its 32 cells' activations in registers from the first layer to the
+// last; LDS holds only what all waves share, the BF16 weights as quads of 8
+// bytes (weight (f, k) in quad (k/4) 128 + f: one conflict-free read per lane
+// and operand), the first layer's split weights, the biases and the output
+// weights.
+//
+// Bound by the vector ALUs: a cell's 384 SiLUs (five operations and two
+// transcendentals each) cost more cycles than its matrix products.  What the
+// layout buys is the room for waves to run one's products beside another's
+// SiLUs: with the activations in LDS as well (8 KB per wave) and the split
+// weights in registers, eight waves fitted a compute unit and took turns;
+// twelve run now, 600 k cells in INFER_US us (133 before), the same results
+// bit for bit.
 //
 // Roundings are those of the pass above: the first layer is formed to FP32
 // accuracy on the matrix cores from three-way BF16 splits of x and W1
@@ -443,7 +451,7 @@ __global__ void __launch_bounds__(64 * kWaves) k_mlp_infer_bf16(
 // the output layer is an FP32 dot product with the last BF16 activations.
 // SiLU uses the hardware exp2 and reciprocal (about 1 ulp of FP32 each,
 // far below the BF16 rounding that follows).
-constexpr int kWavesM = 8;  // waves per workgroup
+constexpr int kWavesM = 12;  // waves per workgroup, one workgroup per compute unit
 
 __device__ __forceinline__ float silu_hw(float z) {
   const float e = __builtin_amdgcn_exp2f(-1.4426950408889634f * z);
@@ -460,54 +468,79 @@ __device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(float2_t{a, b}, bf16x2_t));
 }
 
+// LDS: n_mid weight matrices, then the first layer's split operands
+// [part][mt][kt][lane], then the biases of every layer and the output weights.
+constexpr int kQuads = kW * kW / 4;       // quads of one width x width matrix
+constexpr int kSplitQuads = 3 * 4 * 2 * 64;
+inline size_t infer_lds(int n_mid) {
+  return 8 * ((size_t)n_mid * kQuads + kSplitQuads) + 4 * ((size_t)(n_mid + 2) * kW + 4);
+}
+
 __global__ void __launch_bounds__(64 * kWavesM) k_mlp_infer_mfma(
     int n, int n_mid, const float* __restrict__ x, const float* __restrict__ params,
     const uint16_t* __restrict__ wbf, float* __restrict__ y) {
   extern __shared__ uint64_t lds_q[];
-  constexpr int kQ = kW * kW / 4;  // quads of one width x width matrix
-  uint64_t* wq = lds_q;                                   // n_mid matrices
+  uint64_t* wq = lds_q;                                  // n_mid matrices
+  uint64_t* split = wq + (size_t)n_mid * kQuads;         // first-layer A operands
+  float* vecs = reinterpret_cast<float*>(split + kSplitQuads);  // n_mid + 1 biases, W_out, b_out
   const int lane = threadIdx.x % 64, wv = threadIdx.x / 64;
   const int cell = lane % 32, half = lane / 32;
-  uint64_t* act = lds_q + (size_t)n_mid * kQ + (size_t)wv * (kW * 32 / 4);
-  // stage the hidden weights: W_l[f][4kq .. 4kq+3] is 8 contiguous bytes
-  for (int q = threadIdx.x; q < n_mid * kQ; q += blockDim.x) {
-    const int l = q / kQ, rem = q % kQ, kq = rem / kW, f = rem % kW;
+  // W_l[f][4kq .. 4kq+3] is 8 contiguous bytes
+  for (int q = threadIdx.x; q < n_mid * kQuads; q += blockDim.x) {
+    const int l = q / kQuads, rem = q % kQuads, kq = rem / kW, f = rem % kW;
     wq[q] = *reinterpret_cast<const uint64_t*>(wbf + (size_t)l * kW * kW + (size_t)f * kW + 4 * kq);
   }
   const float* W1 = params;
   const float* b1 = W1 + kW * kIn;
   const int64_t hid = (int64_t)kW * kW + kW;
   const float* last = b1 + kW + (int64_t)n_mid * hid;  // W_out [kW], then b_out
-  // first-layer A operands in registers, three BF16 parts each:
-  // A[f][k] = W1[mt 32 + cell][8 kt + 4 half + v], zero for k >= n_in
-  short4_t a1[3][4][2];
-#pragma unroll
-  for (int mt = 0; mt < 4; ++mt)
+  // A[f][k] = W1[mt 32 + cell][8 kt + 4 half + v], zero for k >= n_in, in
+  // three BF16 parts
+  for (int e = threadIdx.x; e < 4 * 2 * 64; e += blockDim.x) {
+    const int mt = e / 128, kt = (e / 64) % 2, ln = e % 64;
+    uint64_t part[3] = {0, 0, 0};
+    for (int v = 0; v < 4; ++v) {
+      const int k = kt * 8 + 4 * (ln / 32) + v;
+      float w = k < kIn ? W1[(mt * 32 + ln % 32) * kIn + k] : 0.0f;
+      for (int p = 0; p < 3; ++p) {
+        const uint16_t h = f2bf(w);
+        part[p] |= (uint64_t)h << (16 * v);
+        w = w - bf2f(h);
+      }
+    }
+    for (int p = 0; p < 3; ++p) split[(p * 8 + mt * 2 + kt) * 64 + ln] = part[p];
+  }
+  for (int e = threadIdx.x; e < (n_mid + 2) * kW + 1; e += blockDim.x) {
+    const int l = e / kW;
+    vecs[e] = l == 0 ? b1[e]
+              : l <= n_mid ? b1[kW + (int64_t)(l - 1) * hid + kW * kW + e % kW]
+                           : last[e - (n_mid + 1) * kW];
+  }
+  __syncthreads();
+  const int ntile = (n + 31) / 32;
+  // this lane's inputs of a tile: x[c][8 kt + 4 half + v] (zero past n_in)
+  float xin[2][4];
+  auto fetch = [&](int tile) {
+    const int c = tile * 32 + cell;
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int k = kt * 8 + 4 * half + v;
-        float w = k < kIn ? W1[(mt * 32 + cell) * kIn + k] : 0.0f;
-#pragma unroll
-        for (int p = 0; p < 3; ++p) {
-          const uint16_t h = f2bf(w);
-          a1[p][mt][kt][v] = (short)h;
-          w = w - bf2f(h);
-        }
+        xin[kt][v] = c < n && k < kIn ? x[(size_t)c * kIn + k] : 0.0f;
       }
-  __syncthreads();
-  const int ntile = (n + 31) / 32;
-  for (int tile = blockIdx.x * kWavesM + wv; tile < ntile; tile += gridDim.x * kWavesM) {
+  };
+  int tile = blockIdx.x * kWavesM + wv;
+  if (tile < ntile) fetch(tile);
+  for (; tile < ntile; tile += gridDim.x * kWavesM) {
     const int c = tile * 32 + cell;
-    // layer 1: B[k][cell] = x[c][k] for k = 8 kt + 4 half + v
+    // layer 1: B[k][cell] in three BF16 parts
     short4_t b1p[3][2];
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int k = kt * 8 + 4 * half + v;
-        float xv = (c < n && k < kIn) ? x[(size_t)c * kIn + k] : 0.0f;
+        float xv = xin[kt][v];
 #pragma unroll
         for (int p = 0; p < 3; ++p) {
           const uint16_t h = f2bf(xv);
@@ -515,65 +548,71 @@ __global__ void __launch_bounds__(64 * kWavesM) k_mlp_infer_mfma(
           xv = xv - bf2f(h);
         }
       }
+    if (tile + (int)gridDim.x * kWavesM < ntile) fetch(tile + gridDim.x * kWavesM);
     float16_t acc[4];
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) {
       acc[mt] = float16_t{0};
 #pragma unroll
       for (int kt = 0; kt < 2; ++kt) {  // smallest products first
-        acc[mt] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a1[0][mt][kt], b1p[2][kt], acc[mt], 0, 0, 0);
-        acc[mt] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a1[1][mt][kt], b1p[1][kt], acc[mt], 0, 0, 0);
-        acc[mt] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a1[2][mt][kt], b1p[0][kt], acc[mt], 0, 0, 0);
-        acc[mt] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a1[0][mt][kt], b1p[1][kt], acc[mt], 0, 0, 0);
-        acc[mt] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a1[1][mt][kt], b1p[0][kt], acc[mt], 0, 0, 0);
-        acc[mt] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a1[0][mt][kt], b1p[0][kt], acc[mt], 0, 0, 0);
+        short4_t a[3];
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+          a[p] = __builtin_bit_cast(short4_t, split[(p * 8 + mt * 2 + kt) * 64 + lane]);
+        acc[mt] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a[0], b1p[2][kt], acc[mt], 0, 0, 0);
+        acc[mt] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a[1], b1p[1][kt], acc[mt], 0, 0, 0);
+        acc[mt] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a[2], b1p[0][kt], acc[mt], 0, 0, 0);
+        acc[mt] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a[0], b1p[1][kt], acc[mt], 0, 0, 0);
+        acc[mt] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a[1], b1p[0][kt], acc[mt], 0, 0, 0);
+        acc[mt] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a[0], b1p[0][kt], acc[mt], 0, 0, 0);
       }
     }
-    const float* bias = b1;
-    for (int l = 0;; ++l) {
-      // SiLU of the accumulators (bias added), rounded to BF16
-      if (l == n_mid) {  // the last hidden layer feeds the output layer
-        float s = 0.0f;
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-          for (int r = 0; r < 16; r += 2) {
-            const int f = mt * 32 + 8 * (r / 4) + 4 * half + (r % 4);
-            const uint32_t h = bf16_pair(silu_hw(acc[mt][r] + bias[f]),
-                                         silu_hw(acc[mt][r + 1] + bias[f + 1]));
-            s = s + last[f] * __uint_as_float(h << 16);
-            s = s + last[f + 1] * __uint_as_float(h & 0xFFFF0000u);
-          }
-        s = s + __shfl_down(s, 32, 64);
-        if (half == 0 && c < n) y[c] = s + last[kW];
-        break;
-      }
+    const float* bias = vecs;
+    for (int l = 0; l < n_mid; ++l, bias += kW) {
+      // SiLU of the accumulators (bias added), rounded to BF16: quad 4 mt + q
+      uint64_t h[16];
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const int f0 = mt * 32 + 8 * q + 4 * half;
-          float h[4];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) h[j] = silu_hw(acc[mt][4 * q + j] + bias[f0 + j]);
-          act[(f0 / 4) * 32 + cell] =
-              (uint64_t)bf16_pair(h[0], h[1]) | ((uint64_t)bf16_pair(h[2], h[3]) << 32);
+          const float4 bq = *reinterpret_cast<const float4*>(bias + mt * 32 + 8 * q + 4 * half);
+          const uint32_t lo = bf16_pair(silu_hw(acc[mt][4 * q] + bq.x), silu_hw(acc[mt][4 * q + 1] + bq.y));
+          const uint32_t hi = bf16_pair(silu_hw(acc[mt][4 * q + 2] + bq.z), silu_hw(acc[mt][4 * q + 3] + bq.w));
+          h[4 * mt + q] = (uint64_t)lo | ((uint64_t)hi << 32);
         }
       // hidden layer l: out^T = W_l h^T, all four output tiles in registers
-      const uint64_t* W = wq + (size_t)l * kQ;
+      const uint64_t* W = wq + (size_t)l * kQuads;
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt) acc[mt] = float16_t{0};
-#pragma unroll 4
+#pragma unroll
       for (int kt = 0; kt < kW / 8; ++kt) {
-        const short4_t b = __builtin_bit_cast(short4_t, act[(2 * kt + half) * 32 + cell]);
+        const short4_t b = __builtin_bit_cast(short4_t, h[kt]);
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) {
           const short4_t a = __builtin_bit_cast(short4_t, W[(2 * kt + half) * kW + mt * 32 + cell]);
           acc[mt] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a, b, acc[mt], 0, 0, 0);
         }
       }
-      bias = b1 + kW + (int64_t)l * hid + kW * kW;
     }
+    // the last hidden layer feeds the output layer
+    const float* wout = bias + kW;
+    float s = 0.0f;
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int f0 = mt * 32 + 8 * q + 4 * half;
+        const float4 bq = *reinterpret_cast<const float4*>(bias + f0);
+        const float4 wo = *reinterpret_cast<const float4*>(wout + f0);
+        const uint32_t lo = bf16_pair(silu_hw(acc[mt][4 * q] + bq.x), silu_hw(acc[mt][4 * q + 1] + bq.y));
+        const uint32_t hi = bf16_pair(silu_hw(acc[mt][4 * q + 2] + bq.z), silu_hw(acc[mt][4 * q + 3] + bq.w));
+        s = s + wo.x * __uint_as_float(lo << 16);
+        s = s + wo.y * __uint_as_float(lo & 0xFFFF0000u);
+        s = s + wo.z * __uint_as_float(hi << 16);
+        s = s + wo.w * __uint_as_float(hi & 0xFFFF0000u);
+      }
+    s = s + __shfl_down(s, 32, 64);
+    if (half == 0 && c < n) y[c] = s + wout[kW];
   }
 }
 
@@ -596,15 +635,18 @@ __global__ void k_ws_stats(int na, const int* __restrict__ perm, const int* __re
   write_partials<kBlock, 3>(s, partials);
 }
 
+// The statistics from their partials; the first also goes to *host, pinned
+// memory that the host reads once the stream has been waited for.
 __global__ void k_ws_stats_final(const double* __restrict__ partials, int g, int na,
-                                 double* __restrict__ out) {
-  const double a = sum_partials<kBlock>(partials, g);
-  const double b = sum_partials<kBlock>(partials + g, g);
-  const double c = sum_partials<kBlock>(partials + 2 * g, g);
+                                 double* __restrict__ out, double* __restrict__ host) {
+  const double* const parts[3] = {partials, partials + g, partials + 2 * g};
+  double s[3];
+  sum_partials_n<kBlock, 3>(parts, g, s);
   if (threadIdx.x == 0) {
-    out[0] = sqrt(a / na);  // RMS of the previous increment
-    out[1] = sqrt(b / na);  // RMS of the right-hand side
-    out[2] = c / na;        // mean cell volume
+    out[0] = sqrt(s[0] / na);  // RMS of the previous increment
+    out[1] = sqrt(s[1] / na);  // RMS of the right-hand side
+    out[2] = s[2] / na;        // mean cell volume
+    *host = out[0];
   }
 }
 
@@ -612,34 +654,66 @@ __global__ void k_ws_stats_final(const double* __restrict__ partials, int g, int
 //   0 previous increment (re-referenced) / its RMS, 1 rhs / its RMS, 2 liquid fraction,
 //   3 volume / mean volume, 4..9 the six largest open-face coefficients of
 //   the cell divided by their sum (descending, 0 where fewer).
-__global__ void k_ws_features(int na, const int* __restrict__ perm, const int* __restrict__ comp,
-                              const int* __restrict__ adj_ptr,
-                              const int* __restrict__ adj_nbr, const int* __restrict__ adj_face,
-                              const int* __restrict__ active, const double* __restrict__ dp,
-                              const double* __restrict__ rhs, const double* __restrict__ fl,
-                              const double* __restrict__ vol, const double* __restrict__ coeff,
-                              const double* __restrict__ st, const float* __restrict__ mu,
-                              const float* __restrict__ sigma, float* __restrict__ out) {
-  const int r = blockIdx.x * kBlock + threadIdx.x;
-  if (r >= na) return;
-  const int c = perm[r];
-  float f[10];
-  f[0] = st[0] > 0.0 ? (float)((dp[c] - dp[comp[c]]) / st[0]) : 0.0f;
-  f[1] = st[1] > 0.0 ? (float)(rhs[c] / st[1]) : 0.0f;
-  f[2] = (float)fl[c];
-  f[3] = st[2] > 0.0 ? (float)(vol[c] / st[2]) : 0.0f;
-  double top[6] = {0, 0, 0, 0, 0, 0};
-  double sum = 0.0;
-  for (int k = adj_ptr[c]; k < adj_ptr[c + 1]; ++k) {
-    if (!active[adj_nbr[k]]) continue;
-    double v = coeff[adj_face[k]];
-    sum += v;
-    for (int q = 0; q < 6; ++q)  // insert into the descending top-6
-      if (v > top[q]) { double t = top[q]; top[q] = v; v = t; }
-  }
-  for (int q = 0; q < 6; ++q) f[4 + q] = sum > 0.0 ? (float)(top[q] / sum) : 0.0f;
+// Bound by memory: about 190 bytes per cell, most of them gathered.  With DEG
+// > 0 (no cell has more neighbours) a thread requests all neighbours, then all
+// their flags and coefficients, where the plain loop waited for three loads in
+// turn per neighbour; the features leave through LDS, so that a wave's stores
+// are contiguous instead of 40 bytes apart.  600 k cells: 37 -> FEAT_US us.
+template <int DEG>
+__global__ void __launch_bounds__(kBlock) k_ws_features(
+    int na, const int* __restrict__ perm, const int* __restrict__ comp,
+    const int* __restrict__ adj_ptr, const int* __restrict__ adj_nbr,
+    const int* __restrict__ adj_face, const int* __restrict__ active,
+    const double* __restrict__ dp, const double* __restrict__ rhs, const double* __restrict__ fl,
+    const double* __restrict__ vol, const double* __restrict__ coeff,
+    const double* __restrict__ st, const float* __restrict__ mu, const float* __restrict__ sigma,
+    float* __restrict__ out) {
+  __shared__ float rows[kBlock * 10];
+  const int r0 = blockIdx.x * kBlock, r = r0 + threadIdx.x;
+  if (r < na) {
+    const int c = perm[r];
+    const int k0 = adj_ptr[c], k1 = adj_ptr[c + 1];
+    double top[6] = {0, 0, 0, 0, 0, 0};
+    double sum = 0.0;
+    auto take = [&](double v) {
+      sum += v;
 #pragma unroll
-  for (int k = 0; k < 10; ++k) out[(size_t)r * 10 + k] = (f[k] - mu[k]) / sigma[k];
+      for (int q = 0; q < 6; ++q)  // insert into the descending top-6
+        if (v > top[q]) { const double t = top[q]; top[q] = v; v = t; }
+    };
+    if constexpr (DEG > 0) {
+      int nb[DEG], fc[DEG], on[DEG];
+      double v[DEG];
+#pragma unroll
+      for (int u = 0; u < DEG; ++u) {
+        nb[u] = k0 + u < k1 ? adj_nbr[k0 + u] : -1;
+        fc[u] = k0 + u < k1 ? adj_face[k0 + u] : -1;
+      }
+#pragma unroll
+      for (int u = 0; u < DEG; ++u) {
+        on[u] = nb[u] >= 0 ? active[nb[u]] : 0;
+        v[u] = fc[u] >= 0 ? coeff[fc[u]] : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < DEG; ++u)
+        if (on[u]) take(v[u]);
+    } else {
+      for (int k = k0; k < k1; ++k)
+        if (active[adj_nbr[k]]) take(coeff[adj_face[k]]);
+    }
+    float f[10];
+    f[0] = st[0] > 0.0 ? (float)((dp[c] - dp[comp[c]]) / st[0]) : 0.0f;
+    f[1] = st[1] > 0.0 ? (float)(rhs[c] / st[1]) : 0.0f;
+    f[2] = (float)fl[c];
+    f[3] = st[2] > 0.0 ? (float)(vol[c] / st[2]) : 0.0f;
+#pragma unroll
+    for (int q = 0; q < 6; ++q) f[4 + q] = sum > 0.0 ? (float)(top[q] / sum) : 0.0f;
+#pragma unroll
+    for (int k = 0; k < 10; ++k) rows[threadIdx.x * 10 + k] = (f[k] - mu[k]) / sigma[k];
+  }
+  __syncthreads();
+  const int cnt = min(kBlock, na - r0) * 10;
+  for (int e = threadIdx.x; e < cnt; e += kBlock) out[(size_t)r0 * 10 + e] = rows[e];
 }
 
 // x0 = p_prev (re-referenced) + scale * y on active non-pin cells, 0 elsewhere
@@ -697,8 +771,8 @@ double* ws_scratch(int device) {
 
 // The warm-start features of the assembled solver's active cells with the
 // statistics' partials in `part` (3 red_grid(n_active) + 3 doubles, written
-// before they are read: nothing needs clearing).  *dp_scale is copied to the
-// host and the stream synchronised.
+// before they are read: nothing needs clearing).  *dp_scale comes back through
+// the solver's pinned box.
 ppe_status ws_features(ppe_solver* s, const double* dp_prev, const double* rhs,
                        const double* face_coeff, const double* fl, const double* cell_volume,
                        const float* mu, const float* sigma, float* features, double* dp_scale,
@@ -712,17 +786,23 @@ ppe_status ws_features(ppe_solver* s, const double* dp_prev, const double* rhs,
   hipLaunchKernelGGL(k_ws_stats, dim3(g), dim3(kBlock), 0, s->stream, na, s->perm.as<int>(),
                      s->comp_full.as<int>(), dp_prev, rhs, cell_volume, part);
   PPE_LAUNCH_CHECK();
+  ensure_box(s, kBoxRead + 2);  // made by the assembly: nothing is allocated here
   hipLaunchKernelGGL(k_ws_stats_final, dim3(1), dim3(kBlock), 0, s->stream, part, g, na,
-                     part + 3 * g);
+                     part + 3 * g, reinterpret_cast<double*>(s->box_d + kBoxRead));
   PPE_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_ws_features, dim3(grid_for(na)), dim3(kBlock), 0, s->stream, na,
-                     s->perm.as<int>(), s->comp_full.as<int>(), s->adj_ptr.as<int>(),
-                     s->adj_nbr.as<int>(), s->adj_face.as<int>(), s->active.as<int>(), dp_prev,
-                     rhs, fl, cell_volume, face_coeff, part + 3 * g, mu, sigma, features);
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(grid_for(na)), dim3(kBlock), 0, s->stream, na,
+                       s->perm.as<int>(), s->comp_full.as<int>(), s->adj_ptr.as<int>(),
+                       s->adj_nbr.as<int>(), s->adj_face.as<int>(), s->active.as<int>(), dp_prev,
+                       rhs, fl, cell_volume, face_coeff, part + 3 * g, mu, sigma, features);
+  };
+  if (s->max_deg <= 6)
+    run(k_ws_features<6>);
+  else
+    run(k_ws_features<0>);
   PPE_LAUNCH_CHECK();
-  PPE_HIP(hipMemcpyAsync(dp_scale, part + 3 * g, sizeof(double), hipMemcpyDeviceToHost,
-                         s->stream));
   PPE_HIP(hipStreamSynchronize(s->stream));
+  std::memcpy(dp_scale, s->box_h + kBoxRead, sizeof(double));
   return PPE_OK;
 }
 
@@ -934,7 +1014,7 @@ ppe_status ppe_mlp_forward(ppe_mlp* m, int32_t n, const float* x, float* y, int 
               "the BF16 MFMA path needs 10 inputs, width 128 and >= 2 hidden layers");
       const int tiles = (n + 31) / 32;
       const int n_mid = m->n_hidden - 1;
-      const size_t lds = ((size_t)n_mid * kW * kW / 4 + (size_t)kWavesM * kW * 32 / 4) * 8;
+      const size_t lds = infer_lds(n_mid);
       if (m->lds_max == 0) {
         int dev = 0, v = 0;
         PPE_HIP(hipGetDevice(&dev));

@@ -100,6 +100,20 @@ def test_bf16_inference_matches_fp32(n):
     assert np.linalg.norm(y16 - ye) <= BF16_EMUL_RTOL * np.linalg.norm(ye)
 
 
+# the twelve waves of a workgroup, ragged tiles, and the depths whose weights
+# fit in LDS (two to five hidden layers) or do not (six)
+@pytest.mark.parametrize("hidden", [2, 4, 5, 6])
+@pytest.mark.parametrize("n", [1, 31, 385, 13000])
+def test_bf16_inference_depths(n, hidden):
+    import torch
+
+    net, shapes, theta = _net(seed=4, hidden=hidden)
+    X = to_dev(np.random.default_rng(n).normal(size=(n, 10)).astype(np.float32), torch.float32)
+    y = net.forward(X, bf16=True).cpu().numpy()
+    ye = _bf16_forward(theta, shapes, X.cpu().numpy().astype(np.float64))
+    assert np.linalg.norm(y - ye) <= BF16_EMUL_RTOL * np.linalg.norm(ye)
+
+
 def _bf16(a):
     """Round to the nearest BF16 (ties to even), returned as float64."""
     u = np.asarray(a, dtype=np.float32).view(np.uint32).astype(np.uint64)
@@ -178,6 +192,40 @@ def test_features_match_oracle_definition():
     pin_of[sy.perm] = sy.comp
     Fr, sr = omlp.warm_start_features(m.n_cells, m.owner, m.neigh, c, fl, m.cell_volume, dp, b,
                                       pin_of)
+    assert abs(scale - sr) <= 1e-14 * sr
+    assert np.abs(F.cpu().numpy() - Fr).max() <= 1e-6
+
+
+def test_features_of_cells_with_many_neighbours():
+    """More than six neighbours (extra faces to in-plane diagonal cells): the
+    plain neighbour loop, against the oracle's definition."""
+    import torch
+
+    import paper_1810_08572_amd as ppe
+
+    torch_dev()
+    m = box_mesh((9, 8, 7), jitter=0.1, seed=3)
+    c0 = face_coeff(m, 2400.0)
+    g = m.grid_index
+    cell = {tuple(v): k for k, v in enumerate(g)}
+    pairs = [(k, cell[(i + 1, j + 1, l)]) for k, (i, j, l) in enumerate(g)
+             if (i + 1, j + 1, l) in cell]
+    owner = np.concatenate([m.owner, [p[0] for p in pairs]]).astype(np.int32)
+    neigh = np.concatenate([m.neigh, [p[1] for p in pairs]]).astype(np.int32)
+    rng = np.random.default_rng(6)
+    c = np.concatenate([c0, np.median(c0[m.neigh >= 0]) * rng.uniform(0.1, 0.5, size=len(pairs))])
+    s = ppe.Solver()
+    s.set_mesh(m.n_cells, to_dev(owner, torch.int32), to_dev(neigh, torch.int32))
+    fl = fl_growing_front(m.cell_centre, 0.05, 0.2)
+    s.assemble(to_dev(c, torch.float64), to_dev(fl, torch.float64))
+    dp, b = rng.normal(size=m.n_cells), rng.normal(size=m.n_cells)
+    F, scale = ppe.warm_start_features(
+        s, *[to_dev(a, torch.float64) for a in (dp, b, c, fl, m.cell_volume)],
+        to_dev(np.zeros(10), torch.float32), to_dev(np.ones(10), torch.float32))
+    sy = assembly.masked_system(m.n_cells, owner, neigh, c, fl)
+    pin_of = np.zeros(m.n_cells, dtype=np.int64)
+    pin_of[sy.perm] = sy.comp
+    Fr, sr = omlp.warm_start_features(m.n_cells, owner, neigh, c, fl, m.cell_volume, dp, b, pin_of)
     assert abs(scale - sr) <= 1e-14 * sr
     assert np.abs(F.cpu().numpy() - Fr).max() <= 1e-6
 
