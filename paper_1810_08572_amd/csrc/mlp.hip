@@ -53,7 +53,7 @@ __device__ __forceinline__ float dsilu_f(float z) {
 // the backward ones, the whole output layer with the loss.  The weight and
 // bias gradients of all layers are one dispatch over (tile, chunk of rows),
 // their chunks added in order by a second: eight dispatches for three hidden
-// layers.  Loss and gradient of 8,192 rows take 102 us; the vector-ALU tiles
+// layers.  Loss and gradient of 8,192 rows take 90 us; the vector-ALU tiles
 // this replaces (64 x 64 outputs per workgroup, eight workgroups for a weight
 // gradient, a separate pass for every bias, activation and column sum) took
 // 3.87 ms.
@@ -70,15 +70,15 @@ __device__ __forceinline__ int acc_row(int r, int lane) {
   return 8 * (r / 4) + 4 * (lane / 32) + r % 4;
 }
 
-// A ROWS x COLS tile of a row-major matrix on its way through 256 threads into
+// A ROWS x COLS tile of a row-major matrix on its way through T threads into
 // LDS: fetch requests it all (zeros past `rows` and `cols`), put stores it.
 // Four columns per load where the matrix allows it (vec: its leading
 // dimension and address are multiples of four floats; one by one, a layer of
-// width 128 takes 14.4 us, with them 11.5).
-template <int ROWS, int COLS>
+// width 128 took 14.4 us, with them 11.5).
+template <int ROWS, int COLS, int T>
 struct Staged {
-  static constexpr int U = ROWS * COLS / 1024, kRow = COLS / 4, kStep = 256 / kRow;
-  static_assert(U * 1024 == ROWS * COLS && kStep * kRow == 256, "whole rounds only");
+  static constexpr int U = ROWS * COLS / (4 * T), kRow = COLS / 4, kStep = T / kRow;
+  static_assert(U * 4 * T == ROWS * COLS && kStep * kRow == T, "whole rounds only");
   float4 v[U];
   __device__ __forceinline__ void fetch(const float* __restrict__ src, int ld, int rows, int cols,
                                         bool vec) {
@@ -124,62 +124,84 @@ __device__ __forceinline__ bool vec4(const float* p, int ld) {
 // One layer over rows of a batch.  Forward (BACK = false): z = X W^T + b with
 // W [N][K]; z (if wanted) and silu(z) are stored.  Backward (BACK = true):
 // Z = (X W) silu'(Z) in place, W [K][N].  A workgroup takes 32 rows and 128
-// columns, one 32 x 32 tile per wave: 256 workgroups for 8,192 rows and a
-// width up to 128.
+// columns: 256 workgroups for 8,192 rows and a width up to 128, one per compute
+// unit, so its eight waves (16 rows and 32 columns each) are all there is to
+// cover the loads' and the epilogue's latency (four waves of 32 x 32: 11.5 us
+// for a width of 128, eight 9.6).
+// Operands of v_mfma_f32_16x16x4f32: lane l holds A[l % 16][l / 16] and
+// B[l / 16][l % 16]; accumulator r of lane l is C[4 (l / 16) + r][l % 16].
+typedef float float4_v __attribute__((ext_vector_type(4)));
+constexpr int kLayerT = 512;
 template <bool BACK>
-__global__ void __launch_bounds__(256) k_layer(int n, int N, int K, const float* __restrict__ X,
-                                               const float* __restrict__ W,
-                                               const float* __restrict__ bias,
-                                               float* __restrict__ Z, float* __restrict__ H) {
+__global__ void __launch_bounds__(kLayerT) k_layer(int n, int N, int K,
+                                                   const float* __restrict__ X,
+                                                   const float* __restrict__ W,
+                                                   const float* __restrict__ bias,
+                                                   float* __restrict__ Z, float* __restrict__ H) {
   // rows of X and (forward) of W are stored one word apart from a multiple of
-  // the bank count: a tile's 32 lanes read 32 rows at one depth
+  // the bank count: a tile's lanes read its rows at one depth
   __shared__ float Xs[kTile][kTileK + 1];
   __shared__ float Ws[kTileN * (kTileK + 1)];
-  const int t = threadIdx.x, lane = t % 64, wv = t / 64, c = lane % 32, half = lane / 32;
+  const int t = threadIdx.x, lane = t % 64, wv = t / 64, c = lane % 16, kq = lane / 16;
   const int64_t i0 = (int64_t)blockIdx.x * kTile;
-  const int j0 = blockIdx.y * kTileN, jw = wv * kTile;
+  const int iw = 16 * (wv / 4);                       // the wave's rows
+  const int j0 = blockIdx.y * kTileN, jw = 32 * (wv % 4);  // and columns
   const bool live = j0 + jw < N;
   const int rows = (int)min((int64_t)kTile, n - i0);
   const bool vx = vec4(X, K), vw = vec4(W, BACK ? N : K);
-  float16_t acc = {0};
-  for (int k0 = 0; k0 < K; k0 += kTileK) {
-    const int kn = min(kTileK, K - k0);  // entries past it are stored as zeros
-    Staged<kTile, kTileK> xs;
-    Staged<BACK ? kTileK : kTileN, BACK ? kTileN : kTileK> ws;
+  Staged<kTile, kTileK, kLayerT> xs;
+  Staged<BACK ? kTileK : kTileN, BACK ? kTileN : kTileK, kLayerT> ws;
+  auto fetch = [&](int k0) {  // entries past the matrix are zeros
+    const int kn = min(kTileK, K - k0);
     xs.fetch(X + i0 * K + k0, K, rows, kn, vx);
     if (BACK)
       ws.fetch(W + (int64_t)k0 * N + j0, N, kn, N - j0, vw);
     else
       ws.fetch(W + (int64_t)j0 * K + k0, K, N - j0, kn, vw);
+  };
+  float4_v acc[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+  fetch(0);
+  for (int k0 = 0; k0 < K; k0 += kTileK) {
+    const int kn = min(kTileK, K - k0);
     __syncthreads();  // the last chunk's readers are done
     xs.put(&Xs[0][0], kTileK + 1);
     ws.put(Ws, BACK ? kTileN : kTileK + 1);
     __syncthreads();
+    if (k0 + kTileK < K) fetch(k0 + kTileK);
     if (live) {
       for (int kk = 0; kk < kn; kk += 16) {
 #pragma unroll
-        for (int u = 0; u < 16; u += 2) {
-          const int k = kk + u + half;
-          const float b = BACK ? Ws[k * kTileN + jw + c] : Ws[(jw + c) * (kTileK + 1) + k];
-          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(Xs[c][k], b, acc, 0, 0, 0);
+        for (int u = 0; u < 16; u += 4) {
+          const int k = kk + u + kq;
+          const float a = Xs[iw + c][k];
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const int j = jw + 16 * h + c;
+            const float b = BACK ? Ws[k * kTileN + j] : Ws[j * (kTileK + 1) + k];
+            acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc[h], 0, 0, 0);
+          }
         }
       }
     }
   }
-  const int j = j0 + jw + c;
-  if (!live || j >= N) return;
-  const float bj = BACK ? 0.0f : bias[j];
+  if (!live) return;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int64_t i = i0 + acc_row(r, lane);
-    if (i >= n) continue;
-    const int64_t e = i * N + j;
-    if (BACK) {
-      Z[e] = acc[r] * dsilu_f(Z[e]);
-    } else {
-      const float z = acc[r] + bj;
-      if (Z) Z[e] = z;
-      H[e] = silu_f(z);
+  for (int h = 0; h < 2; ++h) {
+    const int j = j0 + jw + 16 * h + c;
+    if (j >= N) continue;
+    const float bj = BACK ? 0.0f : bias[j];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t i = i0 + iw + 4 * kq + r;
+      if (i >= n) continue;
+      const int64_t e = i * N + j;
+      if (BACK) {
+        Z[e] = acc[h][r] * dsilu_f(Z[e]);
+      } else {
+        const float z = acc[h][r] + bj;
+        if (Z) Z[e] = z;
+        H[e] = silu_f(z);
+      }
     }
   }
 }
@@ -260,16 +282,20 @@ __global__ void __launch_bounds__(256) k_grads(GradArgs a, int n, int chunk, int
   const bool vg = vec4(L.G, L.M), vh = vec4(L.Hin, L.N);
   float16_t acc = {0};
   float db = 0.0f;
-  for (int64_t k0 = r0; k0 < r1; k0 += kTileK) {
-    Staged<kTileK, kTile> gs;
-    Staged<kTileK, kTileN> hs;
+  Staged<kTileK, kTile, 256> gs;
+  Staged<kTileK, kTileN, 256> hs;
+  auto fetch = [&](int64_t k0) {
     const int rows = (int)min((int64_t)kTileK, r1 - k0);
     gs.fetch(L.G + k0 * L.M + o0, L.M, rows, L.M - o0, vg);
     hs.fetch(L.Hin + k0 * L.N + j0, L.N, rows, L.N - j0, vh);
+  };
+  fetch(r0);
+  for (int64_t k0 = r0; k0 < r1; k0 += kTileK) {
     __syncthreads();  // the last chunk's readers are done
     gs.put(&Gs[0][0], kTile);
     hs.put(&Hs[0][0], kTileN);
     __syncthreads();
+    if (k0 + kTileK < r1) fetch(k0 + kTileK);
     if (j0 == 0)  // eight runs of rows per column, added below
       for (int kk = t / kTile; kk < kTileK; kk += 8) db = db + Gs[kk][t % kTile];
     if (live) {
@@ -440,7 +466,7 @@ __global__ void __launch_bounds__(64 * kWaves) k_mlp_infer_bf16(
 // layout buys is the room for waves to run one's products beside another's
 // SiLUs: with the activations in LDS as well (8 KB per wave) and the split
 // weights in registers, eight waves fitted a compute unit and took turns;
-// twelve run now, 600 k cells in INFER_US us (133 before), the same results
+// twelve run now, 600 k cells in 123 us (148 before), the same results
 // bit for bit.
 //
 // Roundings are those of the pass above: the first layer is formed to FP32
@@ -658,7 +684,7 @@ __global__ void k_ws_stats_final(const double* __restrict__ partials, int g, int
 // > 0 (no cell has more neighbours) a thread requests all neighbours, then all
 // their flags and coefficients, where the plain loop waited for three loads in
 // turn per neighbour; the features leave through LDS, so that a wave's stores
-// are contiguous instead of 40 bytes apart.  600 k cells: 37 -> FEAT_US us.
+// are contiguous instead of 40 bytes apart.  600 k cells: 37 -> 23 us.
 template <int DEG>
 __global__ void __launch_bounds__(kBlock) k_ws_features(
     int na, const int* __restrict__ perm, const int* __restrict__ comp,
@@ -817,7 +843,7 @@ const float* hidden_layers(ppe_mlp* m, int n, const float* x, bool keep_pre) {
   for (int l = 0; l < m->n_hidden; ++l) {
     const dim3 grid((unsigned)((n + (int64_t)kTile - 1) / kTile),
                     (m->width + kTileN - 1) / kTileN);
-    hipLaunchKernelGGL(k_layer<false>, grid, dim3(256), 0, m->stream, n, m->width, m->dims[l], h,
+    hipLaunchKernelGGL(k_layer<false>, grid, dim3(kLayerT), 0, m->stream, n, m->width, m->dims[l], h,
                        P + m->woff[l], P + m->boff[l], pre ? pre + l * len : nullptr,
                        act + l * len);
     PPE_LAUNCH_CHECK();
@@ -869,7 +895,7 @@ void loss_grad(ppe_mlp* m, int n, const float* x, const float* t, float* grad) {
   for (int l = L - 1; l > 0; --l) {
     const dim3 grid((unsigned)((n + (int64_t)kTile - 1) / kTile),
                     (m->width + kTileN - 1) / kTileN);
-    hipLaunchKernelGGL(k_layer<true>, grid, dim3(256), 0, m->stream, n, m->width, m->width,
+    hipLaunchKernelGGL(k_layer<true>, grid, dim3(kLayerT), 0, m->stream, n, m->width, m->width,
                        pre + l * len, P + m->woff[l], (const float*)nullptr, pre + (l - 1) * len,
                        (float*)nullptr);
     PPE_LAUNCH_CHECK();
