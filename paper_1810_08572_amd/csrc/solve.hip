@@ -786,20 +786,6 @@ k_zero_empty_t(Tiles T, int ns, const double* __restrict__ sc, double* __restric
   for (int i = T.r0[t] + threadIdx.x; i < T.r1[t]; i += kTileBlock) x[i] = 0.0;
 }
 
-// p = z on active segments; the first tile of a segment stores its r.z
-__global__ void __launch_bounds__(kTileBlock) k_init_p_t(Tiles T, int ns,
-                                                         const int* __restrict__ done,
-                                                         const double* __restrict__ part_rz,
-                                                         const double* __restrict__ z,
-                                                         double* __restrict__ p,
-                                                         double* __restrict__ rz_out) {
-  const int t = blockIdx.x, q = T.seg[t];
-  if (done[q]) return;
-  const double rz = seg_sum(part_rz, T, q);
-  if (t == T.tp[q] && threadIdx.x == 0) rz_out[q] = rz;
-  for (int i = T.r0[t] + threadIdx.x; i < T.r1[t]; i += kTileBlock) p[i] = z[i];
-}
-
 // alpha_q = rz_q / (p.q)_q; x += alpha p; r -= alpha q; tile partial of r.r
 __global__ void __launch_bounds__(kTileBlock) k_update_xr_t(Tiles T, const int* __restrict__ done,
                                                             const double* __restrict__ rz,
@@ -843,26 +829,68 @@ __global__ void __launch_bounds__(kTileBlock) k_update_xr_t(Tiles T, const int* 
   write_partials<kTileBlock, 1>(sv, part);
 }
 
-// With test set (every PCG iteration): count the iteration of each running
-// segment and test its recurred ||r||^2 against the tolerance; every tile
-// of a segment adds the same partials in the same order, so all of them take
-// the same decision, and a segment that converged (or broke down) keeps its
-// p.  Otherwise (first direction after a restart) restart[q] forces beta 0.
-// Then beta_q = r.z / rz_prev; p = z + beta p; counts the segments still
-// running.
-__global__ void __launch_bounds__(kTileBlock) k_update_p_t(Tiles T, int ns, int test,
-                                                           int* __restrict__ done,
-                                                           int* __restrict__ restart,
-                                                           const double* __restrict__ part_rr,
-                                                           const double* __restrict__ sc,
-                                                           int* __restrict__ iters,
-                                                           int* __restrict__ active,
-                                                           const double* __restrict__ part_rz,
-                                                           const double* __restrict__ rz_prev,
-                                                           double* __restrict__ rz_next,
+// The state of a sample's next direction, the same in every tile of it:
+// with test set (every PCG iteration) the iteration of each running segment is
+// counted and its recurred ||r||^2 tested against the tolerance; every tile of
+// a segment adds the same partials in the same order, so all of them take the
+// same decision, and a segment that converged (or broke down) keeps its p.
+// Otherwise (first direction, or the first after a restart) restart[q] forces
+// beta 0, as first does for every segment.  Then beta_q = r.z / rz_prev; the
+// segments still running are counted.
+struct Direction {
+  int ns, test, first;
+  int* done;
+  int* restart;
+  const double* part_rr;
+  const double* sc;
+  int* iters;
+  int* active;
+  const double* part_rz;
+  const double* rz_prev;
+  double* rz_next;
+  int* err;
+};
+
+// beta of tile t's segment q (not done); *stop: nothing is to be updated.
+__device__ __forceinline__ double direction_beta(const Direction& D, const Tiles& T, int t, int q,
+                                                 bool* stop) {
+  const bool lead = t == T.tp[q] && threadIdx.x == 0;
+  // both sums this block may need, r.r and r.z, in one pass over the
+  // segment's partials
+  const int g0 = T.tp[q], G = T.tp[q + 1] - g0;
+  double sums[2];
+  const double* parts[2] = {D.part_rr + g0, D.part_rz + g0};
+  sum_partials_n<kTileBlock, 2>(parts, G, sums);
+  *stop = false;
+  if (D.test) {
+    const double rr = sums[0];
+    const bool bad = !(rr == rr) || rr > 1.7976931348623157e308;
+    const bool conv = bad || rr <= D.sc[SS_TOL2 * D.ns + q];
+    if (lead) {
+      D.iters[q] += 1;
+      D.restart[q] = 0;
+      if (bad) atomicOr(D.err, 2);
+      if (conv) D.done[q] = 1;
+      else atomicAdd(D.active, 1);
+    }
+    *stop = conv;
+    if (conv) return 0.0;
+  }
+  const double rzn = sums[1];
+  double beta = 0.0;
+  if (!D.first && !(!D.test && D.restart[q])) beta = rzn / D.rz_prev[q];
+  if (lead) {
+    D.rz_next[q] = rzn;
+    if (!D.first && !(rzn > 0.0)) atomicOr(D.err, 4);
+  }
+  return beta;
+}
+
+// p_out = z + beta p (z alone where beta is 0)
+__global__ void __launch_bounds__(kTileBlock) k_update_p_t(Tiles T, Direction D,
                                                            const double* __restrict__ z,
-                                                           double* __restrict__ p,
-                                                           int* __restrict__ err) {
+                                                           const double* __restrict__ p,
+                                                           double* __restrict__ p_out) {
   const int t = blockIdx.x, q = T.seg[t];
   // the thread's first row, requested before the segment's sums
   const int i0 = T.r0[t] + threadIdx.x, i1 = T.r1[t];
@@ -871,38 +899,95 @@ __global__ void __launch_bounds__(kTileBlock) k_update_p_t(Tiles T, int ns, int 
     z0 = z[i0];
     p0 = p[i0];
   }
-  if (done[q]) return;
-  const bool lead = t == T.tp[q] && threadIdx.x == 0;
-  // both sums this block may need, r.r and r.z, in one pass over the
-  // segment's partials
-  const int g0 = T.tp[q], G = T.tp[q + 1] - g0;
-  double sums[2];
-  const double* parts[2] = {part_rr + g0, part_rz + g0};
-  sum_partials_n<kTileBlock, 2>(parts, G, sums);
-  if (test) {
-    const double rr = sums[0];
-    const bool bad = !(rr == rr) || rr > 1.7976931348623157e308;
-    const bool conv = bad || rr <= sc[SS_TOL2 * ns + q];
-    if (lead) {
-      iters[q] += 1;
-      restart[q] = 0;
-      if (bad) atomicOr(err, 2);
-      if (conv) done[q] = 1;
-      else atomicAdd(active, 1);
-    }
-    if (conv) return;
-  }
-  const double rzn = sums[1];
-  double beta = 0.0;
-  if (!(!test && restart[q])) beta = rzn / rz_prev[q];
-  if (lead) {
-    rz_next[q] = rzn;
-    if (!(rzn > 0.0)) atomicOr(err, 4);
-  }
+  if (D.done[q]) return;
+  bool stop;
+  const double beta = direction_beta(D, T, t, q, &stop);
+  if (stop) return;
   for (int i = i0; i < i1; i += kTileBlock) {
     const bool first = i == i0;
-    p[i] = (first ? z0 : z[i]) + beta * (first ? p0 : p[i]);
+    const double zi = first ? z0 : z[i];
+    p_out[i] = beta == 0.0 ? zi : zi + beta * (first ? p0 : p[i]);
   }
+}
+
+// The next direction and its product in one pass: p_out = z + beta p, formed
+// for the row and again for each neighbour, and q = A p_out with the tile
+// partials of p.q: the arithmetic of k_update_p_t and k_ell_dot_t, bit for bit.
+// It drops one of each iteration's dispatches and the write and re-read of p
+// between them (28 of 140 bytes per row), for a second gathered vector: 10.2
+// us in place of 4.9 + 5.6 and a gap at 147 k rows, 12.8 for 7.8 + 6.0 at 369 k,
+// 19.4 for 12.7 + 7.0 at 640 k, but 37.0 for 26.1 + 9.5 at 1.47 M rows, where
+// the gathers no longer stay in cache: two passes above kFuseDirection rows.
+// The first row's operands are requested before the segment's sums.
+constexpr int kFuseDirection = 1 << 20;
+template <int WM>
+__global__ void __launch_bounds__(kTileBlock) k_direction_t(
+    Tiles T, Direction D, int n, int W, const int* __restrict__ ecol,
+    const double* __restrict__ eval, const double* __restrict__ diag,
+    const double* __restrict__ z, const double* __restrict__ p, double* __restrict__ p_out,
+    double* __restrict__ qv, double* __restrict__ part) {
+  constexpr int U = WM > 0 ? WM : 1;
+  const int t = xcd_block(blockIdx.x, gridDim.x);  // the tile (its partial's slot)
+  const int q = T.seg[t];
+  if (D.done[q]) return;
+  const int i0 = T.r0[t] + threadIdx.x, i1 = T.r1[t];
+  // a row's own values and, for WM > 0, its neighbours'
+  double zi = 0.0, pi = 0.0, di = 0.0, gz[U], gp[U], v[U];
+  auto request = [&](int i) {
+    zi = z[i];
+    pi = p[i];
+    di = diag[i];
+    if constexpr (WM > 0) {
+      int col[U];
+      if (W == U) {  // every slot stored: no condition (as in ell_row)
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+          const size_t e = (size_t)k * n + i;
+          col[k] = ecol[e];
+          v[k] = eval[e];
+        }
+      } else {
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+          const size_t e = (size_t)k * n + i;
+          col[k] = k < W ? ecol[e] : i;
+          v[k] = k < W ? eval[e] : 0.0;
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        gz[k] = z[col[k]];
+        gp[k] = p[col[k]];
+      }
+    }
+  };
+  if (i0 < i1) request(i0);
+  bool stop;
+  const double beta = direction_beta(D, T, t, q, &stop);
+  if (stop) return;
+  auto dir = [&](double zj, double pj) { return beta == 0.0 ? zj : zj + beta * pj; };
+  double acc = 0.0;
+  for (int i = i0; i < i1; i += kTileBlock) {
+    if (i != i0) request(i);
+    const double pn = dir(zi, pi);
+    double s = di * pn;
+    if constexpr (WM > 0) {
+#pragma unroll
+      for (int k = 0; k < U; ++k)
+        if (k < W) s = s + v[k] * dir(gz[k], gp[k]);
+    } else {
+      for (int k = 0; k < W; ++k) {
+        const size_t e = (size_t)k * n + i;
+        const int j = ecol[e];
+        s = s + eval[e] * dir(z[j], p[j]);
+      }
+    }
+    p_out[i] = pn;
+    qv[i] = s;
+    acc += pn * s;
+  }
+  double sv[1] = {acc};
+  write_partials<kTileBlock, 1>(sv, part, t);
 }
 
 // After the recurred residuals all met the tolerance: per segment (one
@@ -1764,7 +1849,8 @@ ppe_status pcg_solve(ppe_solver* s, const double* rhs, double* p_out, int use_x0
   double* r = s->vr.get<double>(na);
   // z alternates between two buffers (one captured graph holds both)
   double* zb[2] = {s->vz.get<double>(na), s->vzold.get<double>(na)};
-  double* p = s->vp.get<double>(na);
+  // p alternates too: the fused pass reads the old one at every neighbour
+  double* pb[2] = {s->vp.get<double>(na), s->vp2.get<double>(na)};
   double* q = s->vq.get<double>(na);
   double* b = s->vb.get<double>(na);
   double* tp = s->tpart.get<double>((size_t)T_N * nt);
@@ -1857,37 +1943,53 @@ ppe_status pcg_solve(ppe_solver* s, const double* rhs, double* p_out, int use_x0
   // Samples converged from the start (zero right-hand side, exact guess) are
   // left alone by every iteration, so the first check below finds them.
   auto precondition = [&](int sl) { vcycle_pcg(s, r, zb[sl], PcgDot{T, nt, tpart(T_RZ)}); };
-  precondition(1);
-  hipLaunchKernelGGL(k_init_p_t, dim3(nt), dim3(kTileBlock), 0, s->stream, T, ns, done, tpart(T_RZ),
-                     zb[1], p, rz[0]);
-  PPE_LAUNCH_CHECK();
-  // One PCG iteration of every sample still running: q = A p; x, r update;
-  // the convergence test; z = M r; beta; p.  Samples already converged are
-  // left untouched by every kernel, so extra iterations change nothing.
-  auto body = [&](int sl) {
+  // p = z + beta p from rz slot `from` and p buffer `from` into the other ones,
+  // q = A p: one pass or two (always two while profiling: an operation at a
+  // time).
+  auto direction = [&](int from, const double* z, int test, int first) {
+    const Direction D{ns, test, first, done, restart, tpart(T_RR), sc, iters, cnt, tpart(T_RZ),
+                      rz[from], rz[1 - from], cnt + 1};
+    const double* pin = pb[from];
+    double* pout = pb[1 - from];
+    const int* ecol = L0.ell_col.as<int>();
+    const double* eval = L0.ell_val.as<double>();
+    const double* diag = L0.diag.as<double>();
+    if (s->prof || na > kFuseDirection) {
+      // z, p in; p out
+      launch(s, [&]() { return std::make_pair(std::string("k_update_p_t"), 24.0 * na); },
+             k_update_p_t, dim3(nt), dim3(kTileBlock), T, D, z, pin, pout);
 #define PPE_ELL_DOT(WM_)                                                                      \
   launch(s,                                                                                    \
          [&]() {                                                                               \
            return std::make_pair(kname("k_ell_dot_t", {str(WM_)}),                            \
                                  op_bytes<E_SPMV, double>(s, L0, true, 0.0));                 \
          },                                                                                    \
-         k_ell_dot_t<WM_>, dim3(nt), dim3(kTileBlock), T, na, L0.W,                            \
-         (const int*)L0.ell_col.as<int>(), (const double*)L0.ell_val.as<double>(),              \
-         (const double*)L0.diag.as<double>(), (const int*)done, (const double*)p, q,           \
-         tpart(T_PQ))
-    PPE_ELL_WIDTH(L0.W, PPE_ELL_DOT);
+         k_ell_dot_t<WM_>, dim3(nt), dim3(kTileBlock), T, na, L0.W, ecol, eval, diag,          \
+         (const int*)done, (const double*)pout, q, tpart(T_PQ))
+      PPE_ELL_WIDTH(L0.W, PPE_ELL_DOT);
 #undef PPE_ELL_DOT
+      return;
+    }
+#define PPE_DIRECTION(WM_)                                                                    \
+  hipLaunchKernelGGL(k_direction_t<WM_>, dim3(nt), dim3(kTileBlock), 0, s->stream, T, D, na,  \
+                     L0.W, ecol, eval, diag, z, pin, pout, q, tpart(T_PQ))
+    PPE_ELL_WIDTH(L0.W, PPE_DIRECTION);
+#undef PPE_DIRECTION
+    PPE_LAUNCH_CHECK();
+  };
+  precondition(1);
+  direction(1, zb[1], 0, 1);
+  // One PCG iteration of every sample still running: x, r update; z = M r; the
+  // convergence test, beta and p; q = A p.  Samples already converged are
+  // left untouched by every kernel, so extra iterations change nothing.
+  auto body = [&](int sl) {
     // x, p, r, q in; x, r out
     launch(s, [&]() { return std::make_pair(std::string("k_update_xr_t"), 48.0 * na); },
            k_update_xr_t, dim3(nt), dim3(kTileBlock), T, (const int*)done, (const double*)rz[sl],
-           (const double*)tpart(T_PQ), (const double*)p, (const double*)q, x, r, tpart(T_RR),
+           (const double*)tpart(T_PQ), (const double*)pb[sl], (const double*)q, x, r, tpart(T_RR),
            cnt, cnt + 1);
     precondition(sl);
-    // z, p in; p out
-    launch(s, [&]() { return std::make_pair(std::string("k_update_p_t"), 24.0 * na); },
-           k_update_p_t, dim3(nt), dim3(kTileBlock), T, ns, 1, done, restart,
-           (const double*)tpart(T_RR), (const double*)sc, iters, cnt, (const double*)tpart(T_RZ),
-           (const double*)rz[sl], rz[1 - sl], (const double*)zb[sl], p, cnt + 1);
+    direction(sl, zb[sl], 1, 0);
   };
   // Two iterations (both rz slots) captured into a HIP graph once the system
   // has been solved often enough to expect as many solves again, then replayed
@@ -1957,10 +2059,7 @@ ppe_status pcg_solve(ppe_solver* s, const double* rhs, double* p_out, int use_x0
       if (check_true() == 0) return finish(PPE_OK);
       // restarted samples: z = M r_true, p = z (beta is 0 after a restart)
       precondition(slot);
-      hipLaunchKernelGGL(k_update_p_t, dim3(nt), dim3(kTileBlock), 0, s->stream, T, ns, 0, done,
-                         restart, tpart(T_RR), sc, iters, cnt, tpart(T_RZ), rz[slot],
-                         rz[1 - slot], zb[slot], p, cnt + 1);
-      PPE_LAUNCH_CHECK();
+      direction(slot, zb[slot], 0, 0);
       slot = 1 - slot;
     }
   }
