@@ -827,6 +827,18 @@ __global__ void __launch_bounds__(kBlock) k_spgemm_bound(int n, const int* __res
   if (i < n && lane == 0) prod[i] = s > (1 << 30) ? (1 << 30) : (int)s;
 }
 
+// Between a wavefront's own LDS writes and its other lanes' reads of them: the
+// operations complete in order, so only the compiler has to keep it.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// *p += y in LDS without a result (one operation, no wait)
+__device__ __forceinline__ void lds_add(double* p, double y) {
+  (void)__hip_atomic_fetch_add(p, y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+
 enum SpMode { SP_COUNT = 0, SP_FILL = 1, SP_DENSE = 2, SP_BITS = 3 };
 constexpr int kSpBatch = 4;        // entries of A whose loads are issued together
 constexpr int kSpDenseWidth = 512; // widest C accumulated with one slot per column
@@ -1016,14 +1028,194 @@ __global__ void __launch_bounds__(1024) k_spgemm_rows(
   if (tr == per_row - 1) counts[i] = inc;
 }
 
+// C = A B in one pass, W wavefronts per row (1 or kSpWaves).  A wavefront's
+// products go to value slots found by a hash in LDS (H = 2 cap slots, keys
+// shared by the row's wavefronts): 64 / LPR entries of A's row at a time, LPR
+// lanes across the selected row of B.  Sub-groups that meet in a column would
+// add in an order of their own, so the adds are issued one sub-group after
+// another; they return nothing, so nothing waits for them, and a wavefront's LDS
+// operations complete in issue order: a column is summed from 0 in the entry
+// order of A's row, the wavefronts' sums in theirs, whatever the timing.  The
+// row is written sorted by column to the scratch row at i cap, and counts[i] =
+// its length; a row of more than cap columns sets *over and the host takes the
+// two passes of k_spgemm_rows.
+// It replaces a counting pass with a table of the product bound and a filling
+// one with a value array per sub-group, whose initialisation, merging and
+// probing were most of their LDS traffic.  R (A P) of a 128^3 system's finest
+// level (133 k rows of 390 products) took 258 + 447 us and takes 293 + 36 with
+// the compaction, the next level's A P (210 products) 107 + 403 and takes 221 +
+// 19; the 128^3 set-up went from 5.14 to 4.35 ms.  What is left is LDS (41% of
+// the cycles) and vector instructions (about 60%) of the claims and the adds.
+constexpr int kSpWaves = 4;  // wavefronts per block
+// Scratch columns per row where fewer are not known to do.  Rows of 3D meshes'
+// coarse operators stay below 100 up to some 10^4 rows; 128 rather than 256
+// keeps eight blocks per compute unit in LDS.
+constexpr int kSpCap = 128, kSpCapFew = 256;
+constexpr int kSpFewRows = 16384;
+// Lanes' worth of products above which a row is shared by the block's
+// wavefronts: 11.6 k rows of 84 entries x 32 lanes take 151 us with one and 106
+// with four, 13.8 k rows of 39 entries x 16 lanes 40 with one and 53 with four.
+constexpr int kSpSplit = 1024;
+
+// LDS of one row: W value arrays and the keys of H = 2 cap slots, and the
+// staged entries of A, which the list of columns takes over afterwards.
+inline __host__ __device__ size_t spgemm_wave_lds(int cap, int W) {
+  const size_t list = (size_t)6 * cap, staged = (size_t)W * kWave * 16;
+  return (size_t)2 * cap * (8 * W + 4) + (list > staged ? list : staged);
+}
+
+template <int LPR, int W>
+__global__ void __launch_bounds__(kSpWaves* kWave) k_spgemm_wave(
+    int n, int cap, int hshift, const int* __restrict__ arp, const int* __restrict__ aci,
+    const double* __restrict__ av, const int* __restrict__ brp, const int* __restrict__ bci,
+    const double* __restrict__ bv, int* __restrict__ counts, int* __restrict__ sci,
+    double* __restrict__ sv, int* __restrict__ over) {
+  extern __shared__ char spw[];
+  constexpr int S = kWave / LPR, kRow = W * kWave;  // threads of a row
+  const int H = 2 * cap;
+  const int row = threadIdx.x / kRow, t = threadIdx.x % kRow, w = t / kWave, lane = t % kWave;
+  const int sub = lane / LPR, bl = lane % LPR;
+  char* mine = spw + (size_t)row * spgemm_wave_lds(cap, W);
+  double* vals = reinterpret_cast<double*>(mine);  // [W][H]
+  int* keys = reinterpret_cast<int*>(vals + (size_t)W * H);
+  int4* staged = reinterpret_cast<int4*>(keys + H) + w * kWave;
+  int* ckey = keys + H;
+  unsigned short* slot = reinterpret_cast<unsigned short*>(ckey + cap);
+  const int i = xcd_block(blockIdx.x, gridDim.x) * (kSpWaves / W) + row;
+  if (i >= n) return;  // whole rows: a row of several wavefronts is a block
+  // between LDS writes and other lanes' reads of them
+  auto fence = [] {
+    if (W > 1) __syncthreads();
+    else wave_lds_fence();
+  };
+  for (int q = t; q < H / 4; q += kRow) reinterpret_cast<int4*>(keys)[q] = make_int4(-1, -1, -1, -1);
+  for (int q = t; q < W * H / 2; q += kRow)
+    reinterpret_cast<double2*>(vals)[q] = make_double2(0.0, 0.0);
+  vals += (size_t)w * H;
+  fence();
+
+  bool full = false;
+  auto claim = [&](int key) {  // key's slot (key < 0: none)
+    int q = (int)(((uint32_t)key * 0x9E3779B1u) >> hshift);
+    if (key >= 0) {
+      int prev = atomicCAS(&keys[q], -1, key);
+      for (int probes = 0; prev != -1 && prev != key; ++probes) {
+        if (probes == H) {
+          full = true;
+          break;
+        }
+        q = (q + 1) & (H - 1);
+        prev = atomicCAS(&keys[q], -1, key);
+      }
+    }
+    return q;
+  };
+  auto add = [&](int key, int q, double y) {
+#pragma unroll
+    for (int g = 0; g < S; ++g)
+      if (sub == g && key >= 0) lds_add(&vals[q], y);
+  };
+
+  // wavefront w's run of the row's entries
+  const int r0 = arp[i], r1 = arp[i + 1], run = (r1 - r0 + W - 1) / W;
+  const int a0 = r0 + w * run, a1 = min(r1, a0 + run);
+  for (int c0 = a0; c0 < a1; c0 += kWave) {
+    const int len = min(kWave, a1 - c0);
+    int4 mineA = make_int4(0, 0, 0, 0);  // the selected row's ends, A's value
+    if (lane < len) {
+      const int j = aci[c0 + lane];
+      const double x = av[c0 + lane];
+      mineA = make_int4(brp[j], brp[j + 1], __double2loint(x), __double2hiint(x));
+    }
+    wave_lds_fence();
+    staged[lane] = mineA;
+    wave_lds_fence();
+    for (int e = 0; e < len; e += S * kSpBatch) {
+      int b0[kSpBatch], b1[kSpBatch], kk[kSpBatch], qq[kSpBatch];
+      double xx[kSpBatch], yy[kSpBatch];
+#pragma unroll
+      for (int u = 0; u < kSpBatch; ++u) {
+        const int src = e + u * S + sub;
+        const int4 en = staged[src & (kWave - 1)];
+        b0[u] = en.x + bl;
+        b1[u] = src < len ? en.y : 0;
+        xx[u] = __hiloint2double(en.w, en.z);
+        kk[u] = -1;
+        yy[u] = 0.0;
+        if (b0[u] < b1[u]) {
+          kk[u] = bci[b0[u]];
+          yy[u] = xx[u] * bv[b0[u]];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kSpBatch; ++u) qq[u] = claim(kk[u]);
+#pragma unroll
+      for (int u = 0; u < kSpBatch; ++u) {
+        if (e + u * S >= len) break;
+        add(kk[u], qq[u], yy[u]);
+        for (int b = b0[u] + LPR; __any(b < b1[u]); b += LPR) {
+          int key = -1;
+          double y = 0.0;
+          if (b < b1[u]) {
+            key = bci[b];
+            y = xx[u] * bv[b];
+          }
+          const int q = claim(key);
+          add(key, q, y);
+        }
+      }
+    }
+  }
+  if (__any(full) && lane == 0) atomicOr(over, 1);
+  fence();
+  vals -= (size_t)w * H;
+
+  // every wavefront lists the columns for itself (the last write of equal
+  // values stands) and takes its share of them
+  int u = 0;
+  for (int q = lane; q < H; q += kWave) {
+    const int key = keys[q];
+    const unsigned long long m = __ballot(key != -1);
+    if (key != -1) {
+      const int p = u + __popcll(m & ((1ull << lane) - 1));
+      if (p < cap) {
+        ckey[p] = key;
+        slot[p] = (unsigned short)q;
+      }
+    }
+    u += __popcll(m);
+  }
+  if (t == 0) counts[i] = u;
+  if (u > cap) {
+    if (t == 0) atomicOr(over, 1);
+    return;
+  }
+  if (lane < ((4 - (u & 3)) & 3)) ckey[u + lane] = INT32_MAX;  // cap is a multiple of 4
+  wave_lds_fence();
+  const size_t base = (size_t)i * cap;
+  for (int p = t; p < u; p += kRow) {
+    const int key = ckey[p], q = slot[p];
+    double v = vals[q];
+#pragma unroll
+    for (int k = 1; k < W; ++k) v += vals[(size_t)k * H + q];
+    int rank = 0;
+    for (int o4 = 0; o4 < u; o4 += 4) {
+      const int4 o = *reinterpret_cast<const int4*>(ckey + o4);
+      rank += (o.x < key ? 1 : 0) + (o.y < key ? 1 : 0) + (o.z < key ? 1 : 0) + (o.w < key ? 1 : 0);
+    }
+    sci[base + rank] = key;
+    sv[base + rank] = v;
+  }
+}
+
 __global__ void k_stride_offsets(int n, int stride, int* __restrict__ off) {
   const int i = blockIdx.x * kBlock + threadIdx.x;
   if (i < n) off[i] = i * stride;
 }
 
-// Copy the rows of a product from scratch rows (at off[i]) into C.
+// Copy the rows of a product from scratch rows (at i stride) into C.
 template <int LPR>
-__global__ void __launch_bounds__(kBlock) k_spgemm_compact(int n, const int* __restrict__ off,
+__global__ void __launch_bounds__(kBlock) k_spgemm_compact(int n, int stride,
                                                            const int* __restrict__ crp,
                                                            const int* __restrict__ sci,
                                                            const double* __restrict__ sv,
@@ -1031,7 +1223,7 @@ __global__ void __launch_bounds__(kBlock) k_spgemm_compact(int n, const int* __r
                                                            double* __restrict__ cv) {
   const int i = (blockIdx.x * kBlock + threadIdx.x) / LPR, lane = threadIdx.x % LPR;
   if (i >= n) return;
-  const int src = off[i], dst = crp[i], len = crp[i + 1] - dst;
+  const int src = i * stride, dst = crp[i], len = crp[i + 1] - dst;
   for (int k = lane; k < len; k += LPR) {
     cci[dst + k] = sci[src + k];
     cv[dst + k] = sv[src + k];
@@ -1632,8 +1824,10 @@ static void spgemm_launch(ppe_solver* s, const SpConfig& c, const Csr& A, const 
 
 // C = A B.  Narrow products (C at most kSpDenseWidth columns, rows expected
 // to fill a quarter of them) take one pass with a slot per column into
-// fixed-stride scratch rows and a compaction;
-// wider ones count each row's distinct columns with a hash sized from the
+// fixed-stride scratch rows and a compaction; wider ones one pass of
+// k_spgemm_wave into such rows, unless a row turns out longer than they are.
+// Then, and where the scratch could not be indexed with 32 bits, two
+// passes count each row's distinct columns with a hash sized from the
 // product bound (or a bit per column of C when that is smaller), then fill
 // C with a hash sized from the largest count.  The
 // product bound is maxrow(A) maxrow(B) when both are known on the host, else
@@ -1657,7 +1851,7 @@ void spgemm(ppe_solver* s, const Csr& A, const Csr& B, Csr& C, const int* extra,
   // flag[1] starts at 0 (zeroed below): counts are >= 0, so the max needs
   // no fill of its own unless a bound pass used the slot before
   bool max_slot_used = false;
-  auto fetch_scan = [&](bool with_max) {
+  auto fetch_scan = [&](bool with_max, bool over = false) {
     // a bound pass that used the max slot leaves a larger value there
     if (with_max && max_slot_used) fill_int(s, flag + 1, INT32_MIN, 1);
     const long long* dtotal =
@@ -1668,10 +1862,12 @@ void spgemm(ppe_solver* s, const Csr& A, const Csr& B, Csr& C, const int* extra,
     else
       read_back(s, {ReadItem{dtotal, sizeof(long long), &total},
                     ReadItem{flag, sizeof(int) * 2, fm}});
+    if (over && fm[0] != 0) return false;
     require(fm[0] == 0, PPE_ERR_INTERNAL, "sparse product row overflowed its hash table");
     require(total <= INT32_MAX, PPE_ERR_INTERNAL, "sparse product too large for int32 indices");
     C.nnz = total;
     C.maxrow = fm[1];
+    return true;
   };
   fill_int(s, flag, 0, 2);
 
@@ -1692,14 +1888,50 @@ void spgemm(ppe_solver* s, const Csr& A, const Csr& B, Csr& C, const int* extra,
     fetch_scan(true);
     int* cci = C.col.get<int>(C.nnz);
     double* cv = C.val.get<double>(C.nnz);
-    PPE_ROWS(lanes_for(B), k_spgemm_compact, C.n, C.n, off, crp, sci, sv, cci, cv);
+    PPE_ROWS(lanes_for(B), k_spgemm_compact, C.n, C.n, C.m, crp, sci, sv, cci, cv);
     return;
   }
 
-  int ub;
-  if (A.maxrow > 0 && B.maxrow > 0) {
-    ub = (int)std::min<int64_t>((int64_t)A.maxrow * B.maxrow, C.m);
-  } else {
+  int ub = C.m;  // the product bound, where both longest rows are known
+  if (A.maxrow > 0 && B.maxrow > 0) ub = (int)std::min<int64_t>((int64_t)A.maxrow * B.maxrow, C.m);
+  const bool few = C.n <= kSpFewRows;
+  int wcap = 16;
+  while (wcap < ub && wcap < (few ? kSpCapFew : kSpCap)) wcap *= 2;
+  if ((int64_t)C.n * wcap <= INT32_MAX) {
+    const size_t cap = (size_t)C.n * wcap;
+    int* sci = s->sp_ci.get<int>(cap);
+    double* sv = s->sp_v.get<double>(cap);
+    int hshift = 32;
+    for (int h = 2 * wcap; h > 1; h /= 2) --hshift;
+    const int lpr = lanes_for(B), W = mean_a * lpr > kSpSplit ? kSpWaves : 1, per = kSpWaves / W;
+    const int g = (C.n + per - 1) / per;
+#define PPE_SPW(L_, W_)                                                                          \
+  hipLaunchKernelGGL((k_spgemm_wave<L_, W_>), dim3(g), dim3(kSpWaves * kWave),                   \
+                     per * spgemm_wave_lds(wcap, W), s->stream, C.n, wcap, hshift, A.rp(),       \
+                     A.ci(), A.v(), B.rp(), B.ci(), B.v(), counts, sci, sv, flag)
+#define PPE_SPW_W(L_)             \
+  if (W == 1) PPE_SPW(L_, 1);     \
+  else PPE_SPW(L_, kSpWaves)
+    switch (lpr) {
+      case 4: PPE_SPW_W(4); break;
+      case 8: PPE_SPW_W(8); break;
+      case 16: PPE_SPW_W(16); break;
+      case 32: PPE_SPW_W(32); break;
+      default: PPE_SPW_W(64); break;
+    }
+#undef PPE_SPW_W
+#undef PPE_SPW
+    PPE_LAUNCH_CHECK();
+    if (fetch_scan(true, true)) {
+      int* cci = C.col.get<int>(C.nnz);
+      double* cv = C.val.get<double>(C.nnz);
+      PPE_ROWS(lanes_for(C), k_spgemm_compact, C.n, C.n, wcap, crp, sci, sv, cci, cv);
+      return;
+    }
+    fill_int(s, flag, 0, 2);
+  }
+
+  if (A.maxrow <= 0 || B.maxrow <= 0) {
     int* prod = s->sp_prod.get<int>(C.n + 1);
     PPE_ROWS(lanes_for(A), k_spgemm_bound, C.n, C.n, A.rp(), A.ci(), B.rp(), prod);
     max_int_async(s, prod, C.n, flag + 1, false);

@@ -183,6 +183,47 @@ def test_hierarchy_on_a_graph_of_degree_ten():
     s.close()
 
 
+@pytest.mark.parametrize("links", [9, 120, 1500])
+def test_products_with_one_long_row(links):
+    """A cell weakly joined to cells all over the mesh: its row of A P has one
+    column (9 links: a few) per aggregate it reaches.  With 1,500 links that
+    exceeds the sparse product's scratch rows and the product is formed in
+    two passes.  Tolerance: the row's sums have up to 1,500 terms of one sign,
+    each rounded (1,500 x 2^-53 = 1.7e-13, and as much for the oracle's)."""
+    import torch
+
+    import paper_1810_08572_amd as ppe
+
+    m = box_mesh((24, 20, 10), jitter=0.1, seed=5)
+    rng = np.random.default_rng(links)
+    hub = m.n_cells // 2
+    near = set(m.owner[m.neigh == hub]) | set(m.neigh[m.owner == hub]) | {hub}
+    far = rng.permutation([c for c in range(m.n_cells) if c not in near])[:links]
+    owner = np.concatenate([m.owner, np.full(links, hub)]).astype(np.int32)
+    neigh = np.concatenate([m.neigh, far]).astype(np.int32)
+    c0 = face_coeff(m, 2400.0)
+    c = np.concatenate([c0, np.full(links, 1e-4 * c0[m.neigh >= 0].mean())])
+    f = np.ones(m.n_cells)
+    sy = assembly.masked_system(m.n_cells, owner, neigh, c, f)
+    H = amg.build_hierarchy(sy.A)
+    assert len(H.levels) >= 3
+    s = ppe.Solver()
+    s.set_mesh(m.n_cells, to_dev(owner, torch.int32), to_dev(neigh, torch.int32))
+    s.assemble(to_dev(c, torch.float64), to_dev(f, torch.float64))
+    assert s.n_levels() == len(H.levels)
+    for lvl, lev in enumerate(H.levels):
+        n = lev.A.shape[0]
+        A = csr(*s.level_matrix(lvl), (n, n))
+        assert A.nnz == lev.A.nnz and rel_max(A, lev.A) <= 3.4e-13, lvl
+        if lvl < len(H.levels) - 1:
+            assert np.array_equal(s.aggregates(lvl).cpu().numpy(), lev.agg), lvl
+            P = csr(*s.prolongator(lvl), lev.P.shape)
+            if lvl == 0:
+                assert (np.diff(P.indptr).max() > 256) == (links == 1500)
+            assert rel_max(P, lev.P) <= 3.4e-13, lvl
+    s.close()
+
+
 def test_hierarchy_after_another_mesh_on_the_same_solver():
     """A chain of 200 cells, then a 40^3 cube, on one solver: the second
     setup reuses the first one's level buffers, MIS-2 batch counts and
