@@ -344,9 +344,13 @@ __global__ void __launch_bounds__(kBlock) k_csr_rect(int n, const int* __restric
 // After the coarse correction e the V-cycle forms x = x1 + P e and takes a
 // Chebyshev step from it (c1 = 0: r = (b - A x)/diag, d = c2 r, y = x + d).
 // Row i needs x at its neighbours, so one pass uses the product AP = A P
-// kept from the Galerkin product: (A x)_i = (A x1)_i + (AP e)_i, exact up to
-// the order of the sums.  That saves the separate prolongation pass and its
-// write and re-read of x.
+// kept from the Galerkin product: b - A x = r - AP e with the residual r = b -
+// A x1 that was restricted, exact up to the order of the sums.  That saves the
+// separate prolongation pass, its write and re-read of x, and the reading of A
+// altogether.  Rows of both are short, so the pass is bound by the chain of
+// row pointers, entries and gathers: on level 1 of a 260 k-row system (21 k rows)
+// it took 7.3 us with A's rows read beside them and takes 6.5, on level 1 of a
+// 590 k-row plate 11.9 and 6.9.
 constexpr int kFuseU = 4;  // CSR entries per lane requested before any is used
 
 // Entries k0 + lane + u LPR (u < U) of a CSR row ending at k1: columns (-1
@@ -399,41 +403,36 @@ __device__ __forceinline__ void group_sum2(double& a, double& b) {
   }
 }
 
-// A, P and AP all CSR (A's rows hold the diagonal); LPR lanes per row.
+// P and AP CSR, LPR lanes per row; r = b - A x1 is the residual that was
+// restricted, so A itself is not read: b - A (x1 + P e) = r - AP e.
 template <class M, int LPR>
 __global__ void __launch_bounds__(kBlock) k_csr_prolong_cheb(
-    int n, const int* __restrict__ rp, const int* __restrict__ ci, const M* __restrict__ v,
-    const M* __restrict__ sd, const int* __restrict__ prp, const int* __restrict__ pci,
+    int n, const M* __restrict__ sd, const int* __restrict__ prp, const int* __restrict__ pci,
     const M* __restrict__ pv, const int* __restrict__ arp, const int* __restrict__ aci,
     const M* __restrict__ av, const double* __restrict__ e, const double* __restrict__ x1,
-    const double* __restrict__ b, double* __restrict__ d, double c2, double* __restrict__ y) {
-  const int i = (blockIdx.x * kBlock + threadIdx.x) / LPR;
+    const double* __restrict__ r, double* __restrict__ d, double c2, double* __restrict__ y) {
+  const int i = (xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x) / LPR;
   const int lane = threadIdx.x % LPR;
-  double ax = 0.0, pe = 0.0, bi = 0.0, di = 1.0, xi = 0.0;
+  double ae = 0.0, pe = 0.0, ri = 0.0, di = 1.0, xi = 0.0;
   if (i < n) {
     if (lane == 0) {
-      bi = b[i];
+      ri = r[i];
       di = (double)sd[i];
       xi = x1[i];
     }
-    const int r0 = rp[i], r1 = rp[i + 1], p0 = prp[i], p1 = prp[i + 1], a0 = arp[i],
-              a1 = arp[i + 1];
-    int cc[kFuseU], pc[kFuseU], ac[kFuseU];
-    M cw[kFuseU], pw[kFuseU], aw[kFuseU];
-    chunk_load<LPR, kFuseU, M>(r0, r1, lane, ci, v, cc, cw);
-    chunk_load<LPR, kFuseU, M>(p0, p1, lane, pci, pv, pc, pw);
+    const int p0 = prp[i], p1 = prp[i + 1], a0 = arp[i], a1 = arp[i + 1];
+    int pc[kFuseU], ac[kFuseU];
+    M pw[kFuseU], aw[kFuseU];
     chunk_load<LPR, kFuseU, M>(a0, a1, lane, aci, av, ac, aw);
-    ax = chunk_sum<kFuseU, M>(ax, cc, cw, x1);
-    ax = chunk_sum<kFuseU, M>(ax, ac, aw, e);
+    chunk_load<LPR, kFuseU, M>(p0, p1, lane, pci, pv, pc, pw);
+    ae = chunk_sum<kFuseU, M>(ae, ac, aw, e);
     pe = chunk_sum<kFuseU, M>(pe, pc, pw, e);
-    ax = row_rest<LPR, kFuseU, M>(ax, r0, r1, lane, ci, v, x1);
-    ax = row_rest<LPR, kFuseU, M>(ax, a0, a1, lane, aci, av, e);
+    ae = row_rest<LPR, kFuseU, M>(ae, a0, a1, lane, aci, av, e);
     pe = row_rest<LPR, kFuseU, M>(pe, p0, p1, lane, pci, pv, e);
   }
-  group_sum2<LPR>(ax, pe);
+  group_sum2<LPR>(ae, pe);
   if (i < n && lane == 0) {
-    const double r = (bi - ax) / di;
-    const double dn = c2 * r;
+    const double dn = c2 * ((ri - ae) / di);
     d[i] = dn;
     y[i] = (xi + pe) + dn;
   }
@@ -1292,31 +1291,33 @@ void apply_rect(ppe_solver* s, const Csr& P, const double* x, double* y, int lpr
 }
 
 // Whether level L's prolongation can run fused with its first
-// post-smoothing step: on the coarse levels of the FP64 V-cycle, while AP
-// still equals A P, when the smoother takes at least two steps (and whether
-// it does: the level's launch choice as well).
-//  - The finest level keeps its separate passes: there the fused pass, with
-//    CSR rows of P and AP gathered beside the ELL rows of A, took as long as
-//    the prolongation and the ELL step together, while on the coarse levels
-//    it saves a dispatch each.
-//  - The mixed V-cycle keeps them too: rounded to FP32 separately, the
+// post-smoothing step: in the FP64 V-cycle, while AP still equals A P, when
+// the smoother takes at least two steps (and whether it does: the level's
+// launch choice as well).
+//  - While the dispatches are timed by name, the finest level runs its passes
+//    one by one.
+//  - The mixed V-cycle keeps its separate passes: rounded to FP32 separately, the
 //    stored AP is no longer the product of the stored A and P, and the
 //    V-cycle would stop being symmetric at the level of that rounding.
 bool prolong_can_fuse(const ppe_solver* s, const Level& L) {
-  return s->opt.precision != PPE_MIXED && &L != &s->levels[0] && L.ap_ok && !L.c1.empty();
+  return s->opt.precision != PPE_MIXED && L.ap_ok && !L.c1.empty() &&
+         !(&L == &s->levels[0] && s->prof);
 }
 bool prolong_fusable(const ppe_solver* s, const Level& L) {
   return L.fuse_p && prolong_can_fuse(s, L);
 }
 
 // The fixed rule for fusing: the fused pass reads A P where the separate
-// passes read P and write and re-read x, and saves one dispatch.  Where A P
-// holds more than about 16 MB beyond that (128^3 level 1: 9 M entries), the
-// separate passes move less (182 against about 80 MB there); a level below
-// that is latency-bound and the saved dispatch wins.
-bool fuse_rule(const Level& L) {
-  const double extra = 12.0 * (double)L.AP.nnz - 16.0 * (double)L.n;
-  return extra <= 16.0e6;
+// passes read A and write and re-read x, and saves one dispatch.  Where A P
+// holds more than about 16 MB beyond that (128^3 level 1: 9 M entries against
+// 4 M), the separate passes move less; a level below that is latency-bound and
+// the saved dispatch wins.  The finest level's A is not counted against A P:
+// its ELL slots are streamed, rows of A P are gathered.  Separate and fused
+// there: solves of 16^3 528 and 493 us, of 64^3 (150 k rows) 1,117 and 1,102, of
+// 260 k rows 1,831 and 1,860, of a 590 k-row plate 2,660 and 2,835.
+bool fuse_rule(const Level& L, bool finest) {
+  const double a = finest ? 0.0 : 12.0 * (double)L.A.nnz;
+  return 12.0 * (double)L.AP.nnz - a - 16.0 * (double)L.n <= 16.0e6;
 }
 
 // Lanes per row of the fused pass: the launch choice if set (at least
@@ -1324,31 +1325,30 @@ bool fuse_rule(const Level& L) {
 // lane).
 int prolong_lanes(const Level& L) {
   if (L.lpr_p > 0) return std::max(L.lpr_p, 4);
-  return widen_small(L.A, lanes_near(2.0 * std::sqrt(mean_row(L.A))));
+  return widen_small(L.AP, lanes_near(mean_row(L.AP) / 2.5));
 }
 
-// y = (x1 + P e) + d with d = c2 D^-1 (b - A (x1 + P e)): the prolongation
+// y = (x1 + P e) + d with d = c2 D^-1 (r - A P e), r = b - A x1: the prolongation
 // and the first post-smoothing step in one pass (prolong_fusable must hold).
 template <class M>
-void prolong_cheb(ppe_solver* s, Level& L, const double* e, const double* x1, const double* b,
+void prolong_cheb(ppe_solver* s, Level& L, const double* e, const double* x1, const double* r,
                   double* d, double* y) {
   const int n = L.n;
   const int lpr = prolong_lanes(L);
   const int g = grid_for((int64_t)n * lpr);
   const double c2 = L.inv_theta;
-  // entries and row pointers of A, P and AP, the scaling diagonal, e, and
-  // x1, b in with d, y out
+  // entries and row pointers of P and AP, the scaling diagonal, e, and
+  // x1, r in with d, y out
   auto bytes = [&]() {
-    return (double)(L.A.nnz + L.P.nnz + L.AP.nnz) * (sizeof(M) + 4) + 12.0 * (n + 1) +
+    return (double)(L.P.nnz + L.AP.nnz) * (sizeof(M) + 4) + 8.0 * (n + 1) +
            (double)n * sizeof(M) + 8.0 * L.P.m + 8.0 * 4 * n;
   };
 #define PPE_PC_CSR(LL)                                                                         \
   launch(s, [&]() { return std::make_pair(kname("k_csr_prolong_cheb", {tname<M>(), str(LL)}),   \
                                           bytes()); },                                         \
-         k_csr_prolong_cheb<M, LL>, dim3(g), dim3(kBlock), n, (const int*)L.A.rp(),            \
-         (const int*)L.A.ci(), LevelData<M>::val(L.A), smooth_diag<M>(s, L),                  \
+         k_csr_prolong_cheb<M, LL>, dim3(g), dim3(kBlock), n, smooth_diag<M>(s, L),            \
          (const int*)L.P.rp(), (const int*)L.P.ci(), LevelData<M>::val(L.P),                  \
-         (const int*)L.AP.rp(), (const int*)L.AP.ci(), LevelData<M>::val(L.AP), e, x1, b, d,   \
+         (const int*)L.AP.rp(), (const int*)L.AP.ci(), LevelData<M>::val(L.AP), e, x1, r, d,   \
          c2, y)
   switch (lpr) {
     case 4: PPE_PC_CSR(4); break;
@@ -1513,7 +1513,7 @@ bool vcycle_t(ppe_solver* s, int l, const double* b, double* x, const PcgDot* do
   vcycle_t<M>(s, l + 1, C.b.as<double>(), C.x.as<double>(), nullptr, first);
   if (prolong_fusable(s, L)) {
     // the first post-smoothing step writes xa (it is not the last step)
-    prolong_cheb<M>(s, L, C.x.as<double>(), x1, b, L.d.as<double>(), xa);
+    prolong_cheb<M>(s, L, C.x.as<double>(), x1, r, L.d.as<double>(), xa);
     return smooth_steps<M>(s, L, b, xa, 2, x, xa, xb, dot);
   }
   apply_rect<true, M>(s, L.P, C.x.as<double>(), x1, L.lpr_p);
@@ -1606,7 +1606,7 @@ void prepare_solve_levels(ppe_solver* s) {
     // level of the 128^3 cube and the plate); the finest level has no
     // restriction before it and keeps the fused pair.
     L.fuse0 = l == 0;
-    L.fuse_p = fuse_rule(L);
+    L.fuse_p = fuse_rule(L, l == 0);
     const int n = L.n > 0 ? L.n : 1;
     L.x.get<double>(n);
     L.b.get<double>(n);
@@ -2174,7 +2174,7 @@ void tune_level(ppe_solver* s, int l) {
       s, prolong_lanes(L), 4,
       [&](int c) {
         L.lpr_p = c;
-        prolong_cheb<M>(s, L, C.x.as<double>(), L.t.as<double>(), b, d, y);
+        prolong_cheb<M>(s, L, C.x.as<double>(), L.t.as<double>(), L.r.as<double>(), d, y);
       },
       &t_fused);
   L.fuse_p = t_fused <= t_rect + t_step;
