@@ -186,8 +186,6 @@ void ppe_destroy(ppe_solver* s) {
   if (s->ev1) (void)hipEventDestroy(s->ev1);
   if (s->tev0) (void)hipEventDestroy(s->tev0);
   if (s->tev1) (void)hipEventDestroy(s->tev1);
-  for (auto& e : s->chk_ev)
-    if (e) (void)hipEventDestroy(e);
   if (s->fork_ev) (void)hipEventDestroy(s->fork_ev);
   if (s->join_ev) (void)hipEventDestroy(s->join_ev);
   if (s->side) {

@@ -255,7 +255,6 @@ struct ppe_solver {
   uint32_t* box_d = nullptr;
   size_t box_words = 0;
   uint32_t box_tag = 0;
-  hipEvent_t chk_ev[2] = {nullptr, nullptr};  // PCG convergence checks in flight
   // setup's second stream (default priority): coarse power estimates run on
   // it beside the aggregation of the same level
   hipStream_t side = nullptr;
@@ -536,29 +535,26 @@ void max_int_async(ppe_solver* s, const int* in, int n, int* out, bool init = tr
 // Max of an int array.
 int reduce_max_int(ppe_solver* s, const int* in, int n);
 // ---- read-backs through pinned host memory
-// Box layout in words: [kBoxChecks, kBoxRead) for the PCG's convergence
-// checks (two in flight, three words each with the tag), read_back from
-// kBoxRead on.
-constexpr size_t kBoxChecks = 0, kBoxRead = 8;
+// Box layout in words: the PCG's convergence checks from kBoxChecks (two in
+// flight, three words each with the tag), one double at kBoxScale, read_back
+// from kBoxRead on.  A word that holds a tag never holds anything else.
+constexpr size_t kBoxChecks = 0, kBoxScale = 6, kBoxRead = 8;
 // Makes the solver's pinned box hold at least `words` 4-byte words; a box
 // that must grow is replaced only after the stream has drained.
 void ensure_box(ppe_solver* s, size_t words);
-// Values copied into the box by one publish call: n_words words at `words`,
-// followed by the call's tag.
+// Values copied into the box by one publish call, behind the call's tag.
 struct Published {
-  const uint32_t* words;
-  uint32_t n_words;
+  const uint32_t* box;  // the tag, then the words
   uint32_t tag;
 };
 // One small kernel on the solver stream copies the items (at most 16), in
-// order, into the box from word `at` on, then a fresh tag behind them.  No
-// host copies are made; read the values with published_words once the stream
-// (or an event recorded after the call) has completed.
+// order, into the box from word at + 1 on, then a fresh tag to word `at`.  No
+// host copies are made; read the values with published_words.
 Published publish(ppe_solver* s, const ReadItem* items, int n, size_t at);
-// The published words after checking their tag; throws PPE_ERR_INTERNAL if
-// they are still not visible once the stream has drained.
+// Waits for the published words' tag; throws PPE_ERR_INTERNAL if it is not
+// visible once the stream has drained.
 const uint32_t* published_words(ppe_solver* s, const Published& p);
-// Publishes the items at kBoxRead, waits for the stream and copies each item
+// Publishes the items at kBoxRead, waits for them and copies each item
 // to its host address: one round trip for any number of values.
 void read_back(ppe_solver* s, std::initializer_list<ReadItem> items);
 // One value from device to host on the solver stream (synchronises).

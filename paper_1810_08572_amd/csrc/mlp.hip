@@ -812,9 +812,9 @@ ppe_status ws_features(ppe_solver* s, const double* dp_prev, const double* rhs,
   hipLaunchKernelGGL(k_ws_stats, dim3(g), dim3(kBlock), 0, s->stream, na, s->perm.as<int>(),
                      s->comp_full.as<int>(), dp_prev, rhs, cell_volume, part);
   PPE_LAUNCH_CHECK();
-  ensure_box(s, kBoxRead + 2);  // made by the assembly: nothing is allocated here
+  ensure_box(s, kBoxScale + 2);  // made by the assembly: nothing is allocated here
   hipLaunchKernelGGL(k_ws_stats_final, dim3(1), dim3(kBlock), 0, s->stream, part, g, na,
-                     part + 3 * g, reinterpret_cast<double*>(s->box_d + kBoxRead));
+                     part + 3 * g, reinterpret_cast<double*>(s->box_d + kBoxScale));
   PPE_LAUNCH_CHECK();
   auto run = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(grid_for(na)), dim3(kBlock), 0, s->stream, na,
@@ -828,7 +828,7 @@ ppe_status ws_features(ppe_solver* s, const double* dp_prev, const double* rhs,
     run(k_ws_features<0>);
   PPE_LAUNCH_CHECK();
   PPE_HIP(hipStreamSynchronize(s->stream));
-  std::memcpy(dp_scale, s->box_h + kBoxRead, sizeof(double));
+  std::memcpy(dp_scale, s->box_h + kBoxScale, sizeof(double));
   return PPE_OK;
 }
 

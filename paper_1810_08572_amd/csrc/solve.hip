@@ -2011,15 +2011,12 @@ ppe_status pcg_solve(ppe_solver* s, const double* rhs, double* p_out, int use_x0
   // previous solve's), work is queued ahead only while it stays two
   // iterations short of it, and each chunk after that is checked before the
   // next is queued.
-  for (auto& e : s->chk_ev)
-    if (!e) PPE_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   struct Check {
-    Published h;  // (active segments, error bits) once the event has passed
-    int ev;
+    Published h;  // (active segments, error bits)
     int it;  // iterations launched up to this check
   };
   Check pend[2];
-  int npend = 0, next_ev = 0;
+  int npend = 0, next_box = 0;
   auto launch_chunk = [&]() {
     do {
       if (graph && slot == 0 && it + 2 <= max_iter) {
@@ -2032,10 +2029,9 @@ ppe_status pcg_solve(ppe_solver* s, const double* rhs, double* p_out, int use_x0
       it += 1;
     } while (it % every != 0 && it < max_iter);
     const ReadItem item{cnt, 2 * sizeof(int), nullptr};
-    const Published h = publish(s, &item, 1, kBoxChecks + 3 * next_ev);
-    PPE_HIP(hipEventRecord(s->chk_ev[next_ev], s->stream));
-    pend[npend++] = Check{h, next_ev, it};
-    next_ev = 1 - next_ev;
+    const Published h = publish(s, &item, 1, kBoxChecks + 3 * next_box);
+    pend[npend++] = Check{h, it};
+    next_box = 1 - next_box;
   };
   const int expect = pred ? *pred : 0;
   auto run_ahead = [&]() { return expect <= 0 || it + 2 <= expect - 2; };
@@ -2045,7 +2041,6 @@ ppe_status pcg_solve(ppe_solver* s, const double* rhs, double* p_out, int use_x0
     const Check c = pend[0];
     pend[0] = pend[1];
     --npend;
-    PPE_HIP(hipEventSynchronize(s->chk_ev[c.ev]));
     const uint32_t* w = published_words(s, c.h);
     const int active = (int)w[0], bad = (int)w[1];
     if (bad) {
