@@ -857,7 +857,7 @@ constexpr int kSpDenseWidth = 512; // widest C accumulated with one slot per col
 //   SP_FILL   the same hash; the row is written to C at off[i], sorted by
 //             column (rank among the row's columns);
 //   SP_DENSE  slot = column (H >= width); the row is written in column order
-//             to the scratch row at off[i]; counts[i] = entries written;
+//             to the scratch row at i stride; counts[i] = entries written;
 //   SP_BITS   a bit per column of C in H 32-bit words (no probing); counts[i]
 //             = bits set, the row's distinct columns as with SP_COUNT.
 // The block holds blockDim / (LPR W) rows; LDS is sized by the host.
@@ -865,8 +865,9 @@ template <int LPR, int MODE>
 __global__ void __launch_bounds__(1024) k_spgemm_rows(
     int n, int W, int H, const int* __restrict__ arp, const int* __restrict__ aci,
     const double* __restrict__ av, const int* __restrict__ brp, const int* __restrict__ bci,
-    const double* __restrict__ bv, const int* __restrict__ off, int* __restrict__ counts,
-    int* __restrict__ cci, double* __restrict__ cv, int* __restrict__ flag) {
+    const double* __restrict__ bv, const int* __restrict__ off, int stride,
+    int* __restrict__ counts, int* __restrict__ cci, double* __restrict__ cv,
+    int* __restrict__ flag) {
   extern __shared__ double smem[];
   const int per_row = LPR * W;
   const int rpb = blockDim.x / per_row;
@@ -1015,7 +1016,7 @@ __global__ void __launch_bounds__(1024) k_spgemm_rows(
     inc += before;
   }
   if (i >= n) return;
-  int pos = off[i] + inc - c;
+  int pos = i * stride + inc - c;
   for (int q = s0; q < s1; ++q) {
     if (keys[q] != -1) {
       double v = vals[q];
@@ -1206,11 +1207,6 @@ __global__ void __launch_bounds__(kSpWaves* kWave) k_spgemm_wave(
     sci[base + rank] = key;
     sv[base + rank] = v;
   }
-}
-
-__global__ void k_stride_offsets(int n, int stride, int* __restrict__ off) {
-  const int i = blockIdx.x * kBlock + threadIdx.x;
-  if (i < n) off[i] = i * stride;
 }
 
 // Copy the rows of a product from scratch rows (at i stride) into C.
@@ -1803,14 +1799,16 @@ static SpConfig spgemm_config(ppe_solver* s, const Csr& A, const Csr& B, int mod
 
 template <int MODE>
 static void spgemm_launch(ppe_solver* s, const SpConfig& c, const Csr& A, const Csr& B,
-                          const int* off, int* counts, int* cci, double* cv, int* flag) {
+                          const int* off, int stride, int* counts, int* cci, double* cv,
+                          int* flag) {
   const int g = (A.n + c.rpb - 1) / c.rpb;
   const bool numeric = MODE == SP_FILL || MODE == SP_DENSE;
   const double* av = numeric ? A.v() : nullptr;
   const double* bv = numeric ? B.v() : nullptr;
 #define PPE_SPR(L_)                                                                            \
   hipLaunchKernelGGL((k_spgemm_rows<L_, MODE>), dim3(g), dim3(c.threads), c.lds, s->stream, A.n, \
-                     c.W, c.H, A.rp(), A.ci(), av, B.rp(), B.ci(), bv, off, counts, cci, cv, flag)
+                     c.W, c.H, A.rp(), A.ci(), av, B.rp(), B.ci(), bv, off, stride, counts, cci,   \
+                     cv, flag)
   switch (c.lpr) {
     case 4: PPE_SPR(4); break;
     case 8: PPE_SPR(8); break;
@@ -1833,7 +1831,7 @@ static void spgemm_launch(ppe_solver* s, const SpConfig& c, const Csr& A, const 
 // product bound is maxrow(A) maxrow(B) when both are known on the host, else
 // a bound pass reads it back.  C.maxrow is set to C's longest row.  extra: a
 // device int read back in the same round trip as C's size (extra_host).
-void spgemm(ppe_solver* s, const Csr& A, const Csr& B, Csr& C, const int* extra,
+void spgemm(ppe_solver* s, const Csr& A, const Csr& B, Csr& C, int* flag, const int* extra,
             int* extra_host) {
   require(A.m == B.n, PPE_ERR_INTERNAL, "spgemm shape mismatch");
   C.n = A.n;
@@ -1844,9 +1842,7 @@ void spgemm(ppe_solver* s, const Csr& A, const Csr& B, Csr& C, const int* extra,
     fill_int(s, crp, 0, 1);
     return;
   }
-  int* flag = s->flag.get<int>(4);
   int* counts = s->sp_cnt.get<int>(C.n + 1);
-  long long total = 0;
   int fm[2] = {0, 0};
   // flag[1] starts at 0 (zeroed below): counts are >= 0, so the max needs
   // no fill of its own unless a bound pass used the slot before
@@ -1854,14 +1850,11 @@ void spgemm(ppe_solver* s, const Csr& A, const Csr& B, Csr& C, const int* extra,
   auto fetch_scan = [&](bool with_max, bool over = false) {
     // a bound pass that used the max slot leaves a larger value there
     if (with_max && max_slot_used) fill_int(s, flag + 1, INT32_MIN, 1);
-    const long long* dtotal =
-        exclusive_scan_async(s, counts, crp, C.n, 0, with_max ? flag + 1 : nullptr);
-    if (extra)
-      read_back(s, {ReadItem{dtotal, sizeof(long long), &total},
-                    ReadItem{flag, sizeof(int) * 2, fm}, ReadItem{extra, sizeof(int), extra_host}});
-    else
-      read_back(s, {ReadItem{dtotal, sizeof(long long), &total},
-                    ReadItem{flag, sizeof(int) * 2, fm}});
+    int none = 0;
+    const long long total = exclusive_scan_read(
+        s, counts, crp, C.n, with_max ? flag + 1 : nullptr,
+        {ReadItem{flag, sizeof(int) * 2, fm},
+         extra ? ReadItem{extra, sizeof(int), extra_host} : ReadItem{flag, sizeof(int), &none}});
     if (over && fm[0] != 0) return false;
     require(fm[0] == 0, PPE_ERR_INTERNAL, "sparse product row overflowed its hash table");
     require(total <= INT32_MAX, PPE_ERR_INTERNAL, "sparse product too large for int32 indices");
@@ -1869,7 +1862,6 @@ void spgemm(ppe_solver* s, const Csr& A, const Csr& B, Csr& C, const int* extra,
     C.maxrow = fm[1];
     return true;
   };
-  fill_int(s, flag, 0, 2);
 
   const double mean_a = (double)A.nnz / A.n, mean_b = B.n ? (double)B.nnz / B.n : 0.0;
   if (C.m <= kSpDenseWidth && 4.0 * mean_a * mean_b >= C.m) {
@@ -1878,13 +1870,9 @@ void spgemm(ppe_solver* s, const Csr& A, const Csr& B, Csr& C, const int* extra,
     const SpConfig c = spgemm_config(s, A, B, SP_DENSE, H);
     const size_t cap = (size_t)C.n * C.m;
     require(cap <= INT32_MAX, PPE_ERR_INTERNAL, "sparse product scratch too large");
-    int* off = s->sp_off.get<int>(C.n + 1);
-    hipLaunchKernelGGL(k_stride_offsets, dim3(grid_for(C.n + 1)), dim3(kBlock), 0, s->stream,
-                       C.n + 1, C.m, off);
-    PPE_LAUNCH_CHECK();
     int* sci = s->sp_ci.get<int>(cap);
     double* sv = s->sp_v.get<double>(cap);
-    spgemm_launch<SP_DENSE>(s, c, A, B, off, counts, sci, sv, flag);
+    spgemm_launch<SP_DENSE>(s, c, A, B, nullptr, C.m, counts, sci, sv, flag);
     fetch_scan(true);
     int* cci = C.col.get<int>(C.nnz);
     double* cv = C.val.get<double>(C.nnz);
@@ -1945,10 +1933,10 @@ void spgemm(ppe_solver* s, const Csr& A, const Csr& B, Csr& C, const int* extra,
   const int words = (C.m + 31) / 32;
   if (words < Hc) {
     const SpConfig cb = spgemm_config(s, A, B, SP_BITS, words);
-    spgemm_launch<SP_BITS>(s, cb, A, B, nullptr, counts, nullptr, nullptr, flag);
+    spgemm_launch<SP_BITS>(s, cb, A, B, nullptr, 0, counts, nullptr, nullptr, flag);
   } else {
     const SpConfig cc = spgemm_config(s, A, B, SP_COUNT, Hc);
-    spgemm_launch<SP_COUNT>(s, cc, A, B, nullptr, counts, nullptr, nullptr, flag);
+    spgemm_launch<SP_COUNT>(s, cc, A, B, nullptr, 0, counts, nullptr, nullptr, flag);
   }
   fetch_scan(true);
   int H = 16;  // at least twice the longest row: list and ckey hold H / 2
@@ -1956,11 +1944,12 @@ void spgemm(ppe_solver* s, const Csr& A, const Csr& B, Csr& C, const int* extra,
   const SpConfig cf = spgemm_config(s, A, B, SP_FILL, H);
   int* cci = C.col.get<int>(C.nnz);
   double* cv = C.val.get<double>(C.nnz);
-  spgemm_launch<SP_FILL>(s, cf, A, B, crp, nullptr, cci, cv, flag);
+  spgemm_launch<SP_FILL>(s, cf, A, B, crp, 0, nullptr, cci, cv, flag);
 }
 
-// T = A^T with sorted rows; *s->rmax receives T's longest row (device int).
-void transpose(ppe_solver* s, const Csr& A, Csr& T) {
+// T = A^T with sorted rows; returns where T's longest row is left (a device
+// int, until the next transpose).
+const int* transpose(ppe_solver* s, const Csr& A, Csr& T) {
   T.n = A.m;
   T.m = A.n;
   T.nnz = A.nnz;
@@ -1968,7 +1957,7 @@ void transpose(ppe_solver* s, const Csr& A, Csr& T) {
   if (T.n > 0 && T.n <= kNarrowCols && A.nnz > 0 && A.nnz * T.n <= kNarrowWork) {
     int* trp = T.rowptr.get<int>(T.n + 1);
     hipLaunchKernelGGL(k_narrow_count, dim3(1), dim3(1024), 0, s->stream, A.nnz, T.n, A.ci(), trp,
-                       s->rmax.get<int>(1));
+                       s->cols.get<int>(1));
     PPE_LAUNCH_CHECK();
     int* rowid = s->tmp_i[2].get<int>(A.nnz);
     hipLaunchKernelGGL(k_row_ids, dim3(grid_for(A.n)), dim3(kBlock), 0, s->stream, A.n, A.rp(),
@@ -1977,9 +1966,11 @@ void transpose(ppe_solver* s, const Csr& A, Csr& T) {
     hipLaunchKernelGGL(k_narrow_fill, dim3(T.n), dim3(1024), 0, s->stream, A.nnz, A.ci(), A.v(),
                        rowid, trp, T.col.get<int>(T.nnz), T.val.get<double>(T.nnz));
     PPE_LAUNCH_CHECK();
-    return;
+    return s->cols.as<int>();
   }
-  int* cnt = s->tmp_i[0].get<int>(T.n + 1);
+  // the counts and, behind them, the longest row
+  int* cnt = s->cols.get<int>(T.n + 1);
+  int* rmax = cnt + T.n;
   fill_int(s, cnt, 0, T.n + 1);
   if (A.nnz) {
     hipLaunchKernelGGL(k_col_count, dim3(grid_for(A.nnz)), dim3(kBlock), 0, s->stream, A.nnz, A.ci(),
@@ -1987,11 +1978,8 @@ void transpose(ppe_solver* s, const Csr& A, Csr& T) {
     PPE_LAUNCH_CHECK();
   }
   int* trp = T.rowptr.get<int>(T.n + 1);
-  int* rmax = s->rmax.get<int>(1);
-  fill_int(s, rmax, INT32_MIN, 1);
-  exclusive_scan_async(s, cnt, trp, T.n, 0, rmax);  // the total is A.nnz
   int* cursor = s->tmp_i[1].get<int>(T.n + 1);
-  PPE_HIP(hipMemcpyAsync(cursor, trp, sizeof(int) * (T.n + 1), hipMemcpyDeviceToDevice, s->stream));
+  exclusive_scan_async(s, cnt, trp, T.n, 0, rmax, cursor);  // the total is A.nnz
   int* tci = T.col.get<int>(T.nnz);
   double* tv = T.val.get<double>(T.nnz);
   int* uci = s->tmp_i[2].get<int>(T.nnz);
@@ -2005,6 +1993,7 @@ void transpose(ppe_solver* s, const Csr& A, Csr& T) {
     hipLaunchKernelGGL(k_rank_rows, dim3(T.n), dim3(kWave), 0, s->stream, trp, uci, uv, tci, tv);
     PPE_LAUNCH_CHECK();
   }
+  return rmax;
 }
 
 // The level's spectral bound of D^-1 A into *rho_dev (read back with the
@@ -2172,14 +2161,12 @@ const double* level0_bound_async(ppe_solver* s) {
 // count, scan with the longest row (one round trip), fill.  Q is what the
 // general product gives, entry for entry.
 static void coarsen_cols_ell(ppe_solver* s, const Level& L, const int* agg, const double* pt,
-                             int na, Csr& Q) {
+                             int na, Csr& Q, int* flag) {
   const int n = L.n, W = L.W;
   Q.n = n;
   Q.m = na;
   int* qrp = Q.rowptr.get<int>(n + 1);
   int* counts = s->sp_cnt.get<int>(n + 1);
-  int* flag = s->flag.get<int>(4);
-  fill_int(s, flag, 0, 2);
   const int g = grid_for(n);
   const int* ecol = L.ell_col.as<int>();
   const double* ev = L.ell_val.as<double>();
@@ -2191,10 +2178,9 @@ static void coarsen_cols_ell(ppe_solver* s, const Level& L, const int* agg, cons
   else if (W <= 6) PPE_QC(6, true, counts, nullptr, nullptr, nullptr);
   else PPE_QC(8, true, counts, nullptr, nullptr, nullptr);
   PPE_LAUNCH_CHECK();
-  const long long* dtotal = exclusive_scan_async(s, counts, qrp, n, 0, flag + 1);
-  long long total = 0;
   int fm[2] = {0, 0};
-  read_back(s, {ReadItem{dtotal, sizeof(long long), &total}, ReadItem{flag, sizeof(int) * 2, fm}});
+  const long long total = exclusive_scan_read(s, counts, qrp, n, flag + 1,
+                                              {ReadItem{flag, sizeof(int) * 2, fm}});
   require(total <= INT32_MAX, PPE_ERR_INTERNAL, "sparse product too large for int32 indices");
   Q.nnz = total;
   Q.maxrow = fm[1];
@@ -2210,15 +2196,13 @@ static void coarsen_cols_ell(ppe_solver* s, const Level& L, const int* agg, cons
 // AP = A P on the finest level from its ELL copy (k_ap_merge_ell): count,
 // scan with the longest row and the device value extra (one round trip),
 // fill.  AP is what the general product gives, entry for entry.
-static void ap_merge_ell(ppe_solver* s, const Level& L, const Csr& P, Csr& AP, const int* extra,
-                         int* extra_host) {
+static void ap_merge_ell(ppe_solver* s, const Level& L, const Csr& P, Csr& AP, int* flag,
+                         const int* extra, int* extra_host) {
   const int n = L.n, W = L.W;
   AP.n = n;
   AP.m = P.m;
   int* crp = AP.rowptr.get<int>(n + 1);
   int* counts = s->sp_cnt.get<int>(n + 1);
-  int* flag = s->flag.get<int>(4);
-  fill_int(s, flag, 0, 2);
   const int g = grid_for(n);
   const int* ecol = L.ell_col.as<int>();
   const double* ev = L.ell_val.as<double>();
@@ -2230,11 +2214,10 @@ static void ap_merge_ell(ppe_solver* s, const Level& L, const Csr& P, Csr& AP, c
   else if (W <= 6) PPE_AP(6, true, counts, nullptr, nullptr, nullptr);
   else PPE_AP(8, true, counts, nullptr, nullptr, nullptr);
   PPE_LAUNCH_CHECK();
-  const long long* dtotal = exclusive_scan_async(s, counts, crp, n, 0, flag + 1);
-  long long total = 0;
   int fm[2] = {0, 0};
-  read_back(s, {ReadItem{dtotal, sizeof(long long), &total}, ReadItem{flag, sizeof(int) * 2, fm},
-                ReadItem{extra, sizeof(int), extra_host}});
+  const long long total = exclusive_scan_read(
+      s, counts, crp, n, flag + 1,
+      {ReadItem{flag, sizeof(int) * 2, fm}, ReadItem{extra, sizeof(int), extra_host}});
   require(total <= INT32_MAX, PPE_ERR_INTERNAL, "sparse product too large for int32 indices");
   AP.nnz = total;
   AP.maxrow = fm[1];
@@ -2249,9 +2232,11 @@ static void ap_merge_ell(ppe_solver* s, const Level& L, const Csr& P, Csr& AP, c
 
 void build_hierarchy(ppe_solver* s) {
   const int maxlev = std::max(1, s->opt.max_levels);
-  double* rho_dev = s->setup_out.get<double>((size_t)maxlev + 1);
+  // spectral bounds, the error word, then each level's three products' error
+  // bits and longest rows, all cleared at once
+  double* rho_dev = s->setup_out.get<double>((size_t)maxlev + 1 + 3 * maxlev);
   int* err = reinterpret_cast<int*>(rho_dev + maxlev);
-  fill_int(s, err, 0, 1);
+  fill_int(s, reinterpret_cast<int*>(rho_dev), 0, 2 * ((int64_t)maxlev + 1 + 3 * maxlev));
   for (int lvl = 0;; ++lvl) {
     Level& L = s->levels[lvl];
     const int n = L.n;
@@ -2283,7 +2268,7 @@ void build_hierarchy(ppe_solver* s) {
       }
     };
     if (last && n > 0 && n <= kDenseMax) {
-      fill_double(s, rho_dev + lvl, 0.0, 1);
+      // rho stays 0
     } else if (lvl > 0 && n > 0) {
       ensure_side_stream(s);
       PPE_HIP(hipEventRecord(s->fork_ev, s->stream));
@@ -2371,10 +2356,9 @@ void build_hierarchy(ppe_solver* s) {
           }
           hipLaunchKernelGGL(k_is_root, dim3(g), dim3(kBlock), 0, s->stream, n, st, root);
           PPE_LAUNCH_CHECK();
-          const long long* total = exclusive_scan_async(s, root, root_id, n);
           int left = 0;
-          read_back(s, {ReadItem{und, sizeof(int), &left},
-                        ReadItem{total, sizeof(long long), &n_roots}});
+          n_roots = exclusive_scan_read(s, root, root_id, n, nullptr,
+                                        {ReadItem{und, sizeof(int), &left}});
           if (left == 0) break;
           require(L.mis_rounds < 10000, PPE_ERR_INTERNAL, "MIS-2 did not terminate");
         }
@@ -2408,10 +2392,8 @@ void build_hierarchy(ppe_solver* s) {
         hipLaunchKernelGGL(k_agg_count, dim3(g), dim3(kBlock), 0, s->stream, n, agg, cnt);
         PPE_LAUNCH_CHECK();
         int* aptr = L.agg_ptr.get<int>(na + 1);
-        exclusive_scan_async(s, cnt, aptr, na);
         int* cursor = s->tmp_i[1].get<int>(na + 1);
-        PPE_HIP(hipMemcpyAsync(cursor, aptr, sizeof(int) * (na + 1), hipMemcpyDeviceToDevice,
-                               s->stream));
+        exclusive_scan_async(s, cnt, aptr, na, 0, nullptr, cursor);
         int* mem = L.agg_mem.get<int>(n);
         hipLaunchKernelGGL(k_agg_fill, dim3(g), dim3(kBlock), 0, s->stream, n, agg, cursor, mem);
         PPE_LAUNCH_CHECK();
@@ -2427,21 +2409,23 @@ void build_hierarchy(ppe_solver* s) {
         hipLaunchKernelGGL(k_tent, dim3(g), dim3(kBlock), 0, s->stream, n, agg, L0.B.as<double>(), Bc,
                            pcnt, pt);
         PPE_LAUNCH_CHECK();
-        Csr& Pt = L0.Pt;
-        Pt.n = n;
-        Pt.m = na;
-        Pt.maxrow = 1;
-        int* ptrp = Pt.rowptr.get<int>(n + 1);
-        exclusive_scan_async(s, pcnt, ptrp, n);
-        Pt.nnz = n;  // capacity (an upper bound): only the row pointers are read
-        hipLaunchKernelGGL(k_tent_csr, dim3(g), dim3(kBlock), 0, s->stream, n, ptrp, agg, pt,
-                           Pt.col.get<int>(Pt.nnz), Pt.val.get<double>(Pt.nnz));
-        PPE_LAUNCH_CHECK();
+        int* flag = reinterpret_cast<int*>(rho_dev + maxlev + 1 + 3 * lvl);
+        const bool merge = lvl == 0 && L0.W > 0 && L0.W <= 8;
         // smoothed prolongator
-        if (lvl == 0 && L0.W > 0 && L0.W <= 8) {
-          coarsen_cols_ell(s, L0, agg, pt, na, L0.Q);
+        if (merge) {
+          coarsen_cols_ell(s, L0, agg, pt, na, L0.Q, flag);
         } else {
-          spgemm(s, L0.A, Pt, L0.Q, nullptr, nullptr);
+          Csr& Pt = L0.Pt;
+          Pt.n = n;
+          Pt.m = na;
+          Pt.maxrow = 1;
+          int* ptrp = Pt.rowptr.get<int>(n + 1);
+          exclusive_scan_async(s, pcnt, ptrp, n);
+          Pt.nnz = n;  // capacity (an upper bound): only the row pointers are read
+          hipLaunchKernelGGL(k_tent_csr, dim3(g), dim3(kBlock), 0, s->stream, n, ptrp, agg, pt,
+                             Pt.col.get<int>(Pt.nnz), Pt.val.get<double>(Pt.nnz));
+          PPE_LAUNCH_CHECK();
+          spgemm(s, L0.A, Pt, L0.Q, flag, nullptr, nullptr);
         }
         Csr& P = L0.P;
         P.n = n;
@@ -2456,13 +2440,13 @@ void build_hierarchy(ppe_solver* s) {
         // P has the pattern of A P_tent: take its arrays instead of copying
         std::swap(P.rowptr, L0.Q.rowptr);
         std::swap(P.col, L0.Q.col);
-        transpose(s, P, L0.R);
-        if (lvl == 0 && L0.W > 0 && L0.W <= 8)
-          ap_merge_ell(s, L0, P, L0.AP, s->rmax.as<int>(), &L0.R.maxrow);
+        const int* rmax = transpose(s, P, L0.R);
+        if (merge)
+          ap_merge_ell(s, L0, P, L0.AP, flag + 2, rmax, &L0.R.maxrow);
         else
-          spgemm(s, L0.A, P, L0.AP, s->rmax.as<int>(), &L0.R.maxrow);
+          spgemm(s, L0.A, P, L0.AP, flag + 2, rmax, &L0.R.maxrow);
         L0.ap_ok = true;
-        spgemm(s, L0.R, L0.AP, C.A, nullptr, nullptr);
+        spgemm(s, L0.R, L0.AP, C.A, flag + 4, nullptr, nullptr);
         C.n = na;
         s->nlev = lvl + 2;
         continue;

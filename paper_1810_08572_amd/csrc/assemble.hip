@@ -349,35 +349,23 @@ void build_tiles(ppe_solver* s) {
   const int na = s->seg_row_off[ns];
   int rows = ((na / kRedBlocks + 255) / 256) * 256;
   rows = std::min(std::max(rows, 256), 4096);
-  std::vector<int>& r0 = s->tile_h[0];
-  std::vector<int>& r1 = s->tile_h[1];
-  std::vector<int>& sg = s->tile_h[2];
-  std::vector<int>& tp = s->tile_h[3];
-  r0.clear();
-  r1.clear();
-  sg.clear();
-  tp.assign(ns + 1, 0);
-  for (int q = 0; q < ns; ++q) {
-    tp[q] = (int)r0.size();
-    for (int a = s->seg_row_off[q]; a < s->seg_row_off[q + 1]; a += rows) {
-      r0.push_back(a);
-      r1.push_back(std::min(a + rows, s->seg_row_off[q + 1]));
-      sg.push_back(q);
+  std::vector<int> tp(ns + 1, 0);
+  for (int q = 0; q < ns; ++q)
+    tp[q + 1] = tp[q] + (s->seg_row_off[q + 1] - s->seg_row_off[q] + rows - 1) / rows;
+  const int nt = tp[ns];
+  std::vector<int>& h = s->tile_h;  // r0, r1, seg, seg_tile_ptr: one upload
+  h.resize(3 * (size_t)nt + ns + 1);
+  for (int q = 0; q < ns; ++q)
+    for (int t = tp[q]; t < tp[q + 1]; ++t) {
+      const int a = s->seg_row_off[q] + (t - tp[q]) * rows;
+      h[t] = a;
+      h[nt + t] = std::min(a + rows, s->seg_row_off[q + 1]);
+      h[2 * (size_t)nt + t] = q;
     }
-  }
-  tp[ns] = (int)r0.size();
-  s->n_tiles = (int)r0.size();
-  const size_t nt = r0.size() ? r0.size() : 1;
-  int* a = s->tile_r0.get<int>(nt);
-  int* b = s->tile_r1.get<int>(nt);
-  int* c = s->tile_seg.get<int>(nt);
-  int* d = s->seg_tile_ptr.get<int>(ns + 1);
-  if (!r0.empty()) {
-    PPE_HIP(hipMemcpyAsync(a, r0.data(), sizeof(int) * r0.size(), hipMemcpyHostToDevice, s->stream));
-    PPE_HIP(hipMemcpyAsync(b, r1.data(), sizeof(int) * r1.size(), hipMemcpyHostToDevice, s->stream));
-    PPE_HIP(hipMemcpyAsync(c, sg.data(), sizeof(int) * sg.size(), hipMemcpyHostToDevice, s->stream));
-  }
-  PPE_HIP(hipMemcpyAsync(d, tp.data(), sizeof(int) * (ns + 1), hipMemcpyHostToDevice, s->stream));
+  std::copy(tp.begin(), tp.end(), h.begin() + 3 * (size_t)nt);
+  s->n_tiles = nt;
+  PPE_HIP(hipMemcpyAsync(s->tile_tab.get<int>(h.size()), h.data(), sizeof(int) * h.size(),
+                         hipMemcpyHostToDevice, s->stream));
 }
 
 // flag faces whose two owners lie in different samples
@@ -504,14 +492,20 @@ void assemble_fine(ppe_solver* s, const double* coeff, const double* fl, const d
   hipLaunchKernelGGL(k_active, dim3(grid_for(nc)), dim3(kBlock), 0, s->stream, fl, nc, active, parent);
   PPE_LAUNCH_CHECK();
   exclusive_scan_async(s, active, rowpos, nc);  // rowpos[nc] = number of active cells
-  // compact row offsets of the segments: rowpos at their first cells
-  int* d_off = s->tmp_i[0].get<int>(ns + 1);
-  int* d_row = s->tmp_i[1].get<int>(ns + 1);
-  PPE_HIP(hipMemcpyAsync(d_off, s->seg_cell_off.data(), sizeof(int) * (ns + 1),
-                         hipMemcpyHostToDevice, s->stream));
-  hipLaunchKernelGGL(k_gather_int, dim3(grid_for(ns + 1)), dim3(kBlock), 0, s->stream, ns + 1, d_off,
-                     rowpos, d_row);
-  PPE_LAUNCH_CHECK();
+  // compact row offsets of the segments: rowpos at their first cells (one
+  // segment: 0 and the number of active cells)
+  s->seg_row_off.assign(ns + 1, 0);
+  ReadItem row_off{rowpos + nc, sizeof(int), s->seg_row_off.data() + 1};
+  if (ns > 1) {
+    int* d_off = s->tmp_i[0].get<int>(ns + 1);
+    int* d_row = s->tmp_i[1].get<int>(ns + 1);
+    PPE_HIP(hipMemcpyAsync(d_off, s->seg_cell_off.data(), sizeof(int) * (ns + 1),
+                           hipMemcpyHostToDevice, s->stream));
+    hipLaunchKernelGGL(k_gather_int, dim3(grid_for(ns + 1)), dim3(kBlock), 0, s->stream, ns + 1,
+                       d_off, rowpos, d_row);
+    PPE_LAUNCH_CHECK();
+    row_off = ReadItem{d_row, sizeof(int) * (ns + 1), s->seg_row_off.data()};
+  }
   // Everything up to the row pointers is queued before the host learns the
   // number of active cells (rowpos[nc] on the device): arrays indexed by
   // compact row are sized for all cells.
@@ -557,16 +551,13 @@ void assemble_fine(ppe_solver* s, const double* coeff, const double* fl, const d
                      nc, s->adj_ptr.as<int>(), s->adj_nbr.as<int>(), active, is_pin, counts);
   PPE_LAUNCH_CHECK();
   int* rowptr = L.A.rowptr.get<int>(nc + 1);
-  const long long* d_nnz = exclusive_scan_async(s, counts, rowptr, nc, 0);
   // one read-back: the field checks, the segments' row offsets, the matrix
   // size and the pocket count
   int bad = 0;
   long long tot[2] = {0, 0};
-  s->seg_row_off.assign(ns + 1, 0);
-  read_back(s, {ReadItem{flag, sizeof(int), &bad},
-                ReadItem{d_row, sizeof(int) * (ns + 1), s->seg_row_off.data()},
-                ReadItem{d_nnz, sizeof(long long), &tot[0]},
-                ReadItem{d_ncomp, sizeof(long long), &tot[1]}});
+  tot[0] = exclusive_scan_read(s, counts, rowptr, nc, nullptr,
+                               {ReadItem{flag, sizeof(int), &bad}, row_off,
+                                ReadItem{d_ncomp, sizeof(long long), &tot[1]}});
   require(!(bad & 1), PPE_ERR_ARG, "face coefficient must be finite and > 0 on interior faces");
   require(!(bad & 2), PPE_ERR_ARG, "liquid fraction must be finite and in [0, 1]");
   require(!(bad & 8), PPE_ERR_ARG, "diagonal shift must be finite and > 0 on every active cell");

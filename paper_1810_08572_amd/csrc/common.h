@@ -228,9 +228,9 @@ struct ppe_solver {
   int n_seg = 1;
   std::vector<int> seg_cell_off{0, 0};  // host, n_seg + 1
   std::vector<int> seg_row_off;         // host, compact rows, n_seg + 1
-  std::vector<int> tile_h[4];           // host copies of the tile tables (kept for async uploads)
+  std::vector<int> tile_h;              // host copy of the tile tables (kept for async uploads)
   int n_tiles = 0;
-  ppe::DevBuf tile_r0, tile_r1, tile_seg, seg_tile_ptr;  // reduction tiles
+  ppe::DevBuf tile_tab;  // reduction tiles: r0, r1, seg (n_tiles each), seg_tile_ptr (n_seg + 1)
   ppe::DevBuf seg_sc, seg_done, tpart;                   // per-segment scalars, tile partials
   std::vector<int> seg_iters_h;
   std::vector<double> seg_res_h;
@@ -242,12 +242,12 @@ struct ppe_solver {
   ppe::DevBuf vx, vr, vz, vp, vp2, vq, vzold, vb;
   ppe::DevBuf scal, partial, counter, flag;
   ppe::DevBuf tmp_i[4], tmp_d[2], tmp_l[2];
-  ppe::DevBuf sp_prod, sp_off, sp_cnt, sp_ci, sp_v;  // sparse-product scratch
+  ppe::DevBuf sp_prod, sp_cnt, sp_ci, sp_v;  // sparse-product scratch
   // setup results read back once per hierarchy: the spectral bound of every
   // level (doubles [0, max_levels)), then the deferred setup error bits (int)
   ppe::DevBuf setup_out;
   ppe::DevBuf cop_ws;  // coarse_operator's blocks of vectors
-  ppe::DevBuf rmax;  // max column count of the last transposed operator (device int)
+  ppe::DevBuf cols;  // column counts of the operator being transposed, its longest column
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   hipEvent_t tev0 = nullptr, tev1 = nullptr;  // autotuner timing
   // pinned host memory that k_publish writes read-back values into
@@ -389,7 +389,9 @@ constexpr int kRedBlocks = 1024;
 // each XCD takes one contiguous run of rows: the rows one plane of cells
 // apart, which gather the same values, then meet in one L2 instead of eight
 // (the 128^3 residual pass: 28.6 -> 21.1 us).  The coarse CSR kernels of the
-// solve keep the plain order, which measured faster for them.  A bijection of
+// solve keep the plain order, which measured faster for them, but for the
+// fused prolongation, which runs on the finest level too (64^3 solve 1,107 us
+// in plain order, 1,084 renumbered).  A bijection of
 // [0, G): XCD x's blocks take the run from x q + min(x, r).
 __device__ __forceinline__ int xcd_block(int b, int G) {
   const int x = b & 7, k = b >> 3, q = G >> 3, r = G & 7;
@@ -525,9 +527,14 @@ int64_t exclusive_scan(ppe_solver* s, const int* in, int* out, int n);
 // the total (a long long in tmp_l[slot], slot 0 or 1, valid until the next
 // scan through that slot).  With max_out, the largest count is also max-ed
 // into *max_out, as max_int_async(..., init = false) would do, with no
-// dispatch of its own.
+// dispatch of its own.  With copy, copy[0..n) receives the offsets as well.
 long long* exclusive_scan_async(ppe_solver* s, const int* in, int* out, int n, int slot = 0,
-                                int* max_out = nullptr);
+                                int* max_out = nullptr, int* copy = nullptr);
+// The same through slot 0 with a round trip that the scan's own dispatch
+// publishes: returns the total and reads the further items (device values ready
+// before the scan, or *max_out).
+long long exclusive_scan_read(ppe_solver* s, const int* in, int* out, int n, int* max_out,
+                              std::initializer_list<ReadItem> more);
 int scan_blocks(int n);
 // *out = max of in[0..n) on the device (no host read)
 // init = false: *out already holds a lower bound (e.g. 0 for counts)

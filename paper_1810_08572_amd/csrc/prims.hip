@@ -40,6 +40,40 @@ __device__ __forceinline__ long long block_excl_scan(long long v, long long* tot
   return off + inc - v;
 }
 
+// Read-back staging: item k (kPubMax at most) is off[k+1] - off[k] words at
+// src[k], copied to dst[1 + off[k]..] in the pinned host box (dst null: nothing
+// to publish).
+constexpr int kPubMax = 16;
+struct PubArgs {
+  const uint32_t* src[kPubMax];
+  uint32_t off[kPubMax + 1];
+  int n;
+  uint32_t tag;
+  uint32_t* dst;
+};
+
+// By one whole block.  After the items, dst[0] receives `tag`, stored only once
+// every word is visible at system scope: a host that reads the tag it expects,
+// then the words, reads this call's values.  The word is never used for
+// anything else, so an old value there is an older tag.  Items may have been
+// written by this block before the call.
+__device__ __forceinline__ void publish_items(const PubArgs& a) {
+  __threadfence();
+  __syncthreads();
+  for (int k = 0; k < a.n; ++k) {
+    const uint32_t* src = a.src[k];
+    const uint32_t o = a.off[k], len = a.off[k + 1] - o;
+    for (uint32_t w = threadIdx.x; w < len; w += blockDim.x)
+      a.dst[1 + o + w] = __hip_atomic_load(src + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0)
+    __hip_atomic_store(a.dst, a.tag, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+__global__ void __launch_bounds__(kBlock) k_publish(PubArgs a) { publish_items(a); }
+
 // Block sums of the counts and, with bmax, block maxima (the scan then also
 // delivers the largest count, which the callers need beside the total).
 __global__ void __launch_bounds__(kBlock) k_scan_reduce(const int* __restrict__ in, int n,
@@ -66,11 +100,12 @@ __global__ void __launch_bounds__(kBlock) k_scan_reduce(const int* __restrict__ 
 }
 
 // Scan of the block sums; with mx, the largest block maximum is max-ed into
-// *mx (as k_max_int does).
+// *mx (as k_max_int does).  What pub names is published from here, so the host
+// goes on while the offsets are still being written.
 __global__ void __launch_bounds__(kBlock) k_scan_top(long long* __restrict__ bsum, int nb,
                                                      long long* __restrict__ total,
                                                      const int* __restrict__ bmax,
-                                                     int* __restrict__ mx) {
+                                                     int* __restrict__ mx, PubArgs pub) {
   long long carry = 0;
   for (int base = 0; base < nb; base += kBlock) {
     int i = base + threadIdx.x;
@@ -87,12 +122,14 @@ __global__ void __launch_bounds__(kBlock) k_scan_top(long long* __restrict__ bsu
     m = block_max<kBlock>(m);
     if (threadIdx.x == 0) atomicMax(mx, m);
   }
+  if (pub.dst) publish_items(pub);
 }
 
 __global__ void __launch_bounds__(kBlock) k_scan_down(const int* __restrict__ in, int n,
                                                       const long long* __restrict__ boff,
                                                       const long long* __restrict__ total,
-                                                      int* __restrict__ out) {
+                                                      int* __restrict__ out,
+                                                      int* __restrict__ copy) {
   const long long base = (long long)blockIdx.x * kScanTile + (long long)threadIdx.x * kScanItems;
   int v[kScanItems];
   long long s = 0;
@@ -107,7 +144,10 @@ __global__ void __launch_bounds__(kBlock) k_scan_down(const int* __restrict__ in
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     long long i = base + k;
-    if (i < n) out[i] = (int)run;
+    if (i < n) {
+      out[i] = (int)run;
+      if (copy) copy[i] = (int)run;
+    }
     run += v[k];
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = (int)*total;
@@ -123,8 +163,9 @@ constexpr int kSmallScan = kSmallBlock * kSmallItems;
 
 __global__ void __launch_bounds__(kSmallBlock) k_scan_small(const int* __restrict__ in, int n,
                                                             int* __restrict__ out,
+                                                            int* __restrict__ copy,
                                                             long long* __restrict__ total,
-                                                            int* __restrict__ mx) {
+                                                            int* __restrict__ mx, PubArgs pub) {
   __shared__ int buf[kSmallScan];
   __shared__ long long wsum[kSmallBlock / kWave];
   int m = INT32_MIN;
@@ -174,11 +215,15 @@ __global__ void __launch_bounds__(kSmallBlock) k_scan_small(const int* __restric
     }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < n; i += kSmallBlock) out[i] = buf[i];
+  for (int i = threadIdx.x; i < n; i += kSmallBlock) {
+    out[i] = buf[i];
+    if (copy) copy[i] = buf[i];
+  }
   if (threadIdx.x == 0) {
     out[n] = (int)tot;
     *total = tot;
   }
+  if (pub.dst) publish_items(pub);
 }
 
 __global__ void __launch_bounds__(kBlock) k_max_int(const int* __restrict__ in, int n,
@@ -188,32 +233,6 @@ __global__ void __launch_bounds__(kBlock) k_max_int(const int* __restrict__ in, 
     m = max(m, in[i]);
   m = block_max<kBlock>(m);
   if (threadIdx.x == 0) atomicMax(out, m);
-}
-
-// Read-back staging: item k (kPubMax at most) is off[k+1] - off[k] words at
-// src[k], copied to dst[1 + off[k]..] in the pinned host box.
-constexpr int kPubMax = 16;
-struct PubArgs {
-  const uint32_t* src[kPubMax];
-  uint32_t off[kPubMax + 1];
-  int n;
-};
-
-// After the items, dst[0] receives `tag`, stored only once every word is
-// visible at system scope: a host that reads the tag it expects, then the
-// words, reads this call's values.  The word is never used for anything else,
-// so an old value there is an older tag.
-__global__ void __launch_bounds__(kBlock) k_publish(PubArgs a, uint32_t tag,
-                                                    uint32_t* __restrict__ dst) {
-  for (int k = 0; k < a.n; ++k) {
-    const uint32_t* src = a.src[k];
-    const uint32_t o = a.off[k], len = a.off[k + 1] - o;
-    for (uint32_t w = threadIdx.x; w < len; w += kBlock) dst[1 + o + w] = src[w];
-  }
-  __threadfence_system();
-  __syncthreads();
-  if (threadIdx.x == 0)
-    __hip_atomic_store(dst, tag, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 template <class T>
@@ -230,34 +249,81 @@ int scan_blocks(int n) {
   return nb < 1 ? 1 : nb;
 }
 
-long long* exclusive_scan_async(ppe_solver* s, const int* in, int* out, int n, int slot,
-                                int* max_out) {
+// Where the scan of n counts through a slot leaves its total: after the block
+// sums, before (with max_out) the block maxima as ints.
+static long long* scan_total(ppe_solver* s, int n, int slot, const int* max_out) {
+  const int nb = n <= kSmallScan ? 1 : scan_blocks(n);
+  return s->tmp_l[slot].get<long long>(nb + 1 + (max_out ? (nb + 1) / 2 : 0)) + nb;
+}
+
+static PubArgs pub_args(ppe_solver* s, const ReadItem* items, int n, size_t at) {
+  if (n > kPubMax) throw Error(PPE_ERR_INTERNAL, "too many read-back items in one call");
+  PubArgs a{};
+  a.n = n;
+  uint32_t off = 0;
+  for (int k = 0; k < n; ++k) {
+    if (items[k].bytes % 4 != 0) throw Error(PPE_ERR_INTERNAL, "read-back size not a word multiple");
+    a.src[k] = static_cast<const uint32_t*>(items[k].dev);
+    a.off[k] = off;
+    off += (uint32_t)(items[k].bytes / 4);
+  }
+  a.off[n] = off;
+  ensure_box(s, at + off + 1);
+  a.tag = ++s->box_tag;
+  a.dst = s->box_d + at;
+  return a;
+}
+
+static void read_items(ppe_solver* s, const Published& pub, const std::vector<ReadItem>& items) {
+  const uint32_t* h = published_words(s, pub);
+  for (const auto& it : items) {
+    std::memcpy(it.host, h, it.bytes);
+    h += it.bytes / 4;
+  }
+}
+
+static long long* scan_launch(ppe_solver* s, const int* in, int* out, int n, int slot, int* max_out,
+                              int* copy, const PubArgs& pub) {
   if (n < 0) throw Error(PPE_ERR_INTERNAL, "negative scan length");
+  long long* total = scan_total(s, n, slot, max_out);
   if (n <= kSmallScan) {
-    long long* total = s->tmp_l[slot].get<long long>(2) + 1;
-    hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(kSmallBlock), 0, s->stream, in, n, out, total,
-                       max_out);
+    hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(kSmallBlock), 0, s->stream, in, n, out, copy,
+                       total, max_out, pub);
     PPE_LAUNCH_CHECK();
     return total;
   }
   const int nb = scan_blocks(n);
-  // block sums, the total, then (with max_out) the block maxima as ints
-  long long* bsum = s->tmp_l[slot].get<long long>(nb + 1 + (max_out ? (nb + 1) / 2 : 0));
-  long long* total = bsum + nb;
+  long long* bsum = total - nb;
   int* bmax = max_out ? reinterpret_cast<int*>(total + 1) : nullptr;
   hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(kBlock), 0, s->stream, in, n, bsum, bmax);
   PPE_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kBlock), 0, s->stream, bsum, nb, total,
-                     (const int*)bmax, max_out);
+                     (const int*)bmax, max_out, pub);
   PPE_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_scan_down, dim3(nb), dim3(kBlock), 0, s->stream, in, n, bsum, total, out);
+  hipLaunchKernelGGL(k_scan_down, dim3(nb), dim3(kBlock), 0, s->stream, in, n, bsum, total, out,
+                     copy);
   PPE_LAUNCH_CHECK();
   return total;
 }
 
+long long* exclusive_scan_async(ppe_solver* s, const int* in, int* out, int n, int slot,
+                                int* max_out, int* copy) {
+  return scan_launch(s, in, out, n, slot, max_out, copy, PubArgs{});
+}
+
+long long exclusive_scan_read(ppe_solver* s, const int* in, int* out, int n, int* max_out,
+                              std::initializer_list<ReadItem> more) {
+  long long t = 0;
+  std::vector<ReadItem> all{ReadItem{scan_total(s, n, 0, max_out), sizeof(long long), &t}};
+  all.insert(all.end(), more);
+  const PubArgs pub = pub_args(s, all.data(), (int)all.size(), kBoxRead);
+  scan_launch(s, in, out, n, 0, max_out, nullptr, pub);
+  read_items(s, Published{s->box_h + kBoxRead, pub.tag}, all);
+  return t;
+}
+
 int64_t exclusive_scan(ppe_solver* s, const int* in, int* out, int n) {
-  const long long* total = exclusive_scan_async(s, in, out, n, 0);
-  long long t = read_scalar(s, total);
+  const long long t = exclusive_scan_read(s, in, out, n, nullptr, {});
   if (t > INT32_MAX) throw Error(PPE_ERR_INTERNAL, "scan total exceeds int32 range");
   return t;
 }
@@ -302,22 +368,10 @@ void ensure_box(ppe_solver* s, size_t words) {
 }
 
 Published publish(ppe_solver* s, const ReadItem* items, int n, size_t at) {
-  if (n > kPubMax) throw Error(PPE_ERR_INTERNAL, "too many read-back items in one call");
-  PubArgs a{};
-  a.n = n;
-  uint32_t off = 0;
-  for (int k = 0; k < n; ++k) {
-    if (items[k].bytes % 4 != 0) throw Error(PPE_ERR_INTERNAL, "read-back size not a word multiple");
-    a.src[k] = static_cast<const uint32_t*>(items[k].dev);
-    a.off[k] = off;
-    off += (uint32_t)(items[k].bytes / 4);
-  }
-  a.off[n] = off;
-  ensure_box(s, at + off + 1);
-  const uint32_t tag = ++s->box_tag;
-  hipLaunchKernelGGL(k_publish, dim3(1), dim3(kBlock), 0, s->stream, a, tag, s->box_d + at);
+  const PubArgs a = pub_args(s, items, n, at);
+  hipLaunchKernelGGL(k_publish, dim3(1), dim3(kBlock), 0, s->stream, a);
   PPE_LAUNCH_CHECK();
-  return Published{s->box_h + at, tag};
+  return Published{s->box_h + at, a.tag};
 }
 
 // The tag is watched rather than the stream: the words are there once the tag
@@ -347,12 +401,7 @@ const uint32_t* published_words(ppe_solver* s, const Published& p) {
 
 void read_back(ppe_solver* s, std::initializer_list<ReadItem> items) {
   const std::vector<ReadItem> all(items);
-  const Published pub = publish(s, all.data(), (int)all.size(), kBoxRead);
-  const uint32_t* h = published_words(s, pub);
-  for (const auto& it : all) {
-    std::memcpy(it.host, h, it.bytes);
-    h += it.bytes / 4;
-  }
+  read_items(s, publish(s, all.data(), (int)all.size(), kBoxRead), all);
 }
 
 void fill_int(ppe_solver* s, int* p, int v, int64_t n) {

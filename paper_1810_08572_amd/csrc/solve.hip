@@ -667,22 +667,32 @@ enum TilePart : int { T_BB = 0, T_RR = 1, T_PQ = 2, T_RZ = 3, T_RT = 4, T_N = 5 
 
 __global__ void __launch_bounds__(kTileBlock)
 k_gather_rhs_t(Tiles T, const int* __restrict__ perm, const int* __restrict__ comp,
-               const double* __restrict__ rhs, double* __restrict__ b, double* __restrict__ part) {
+               const double* __restrict__ rhs, double* __restrict__ b, double* __restrict__ part,
+               double* __restrict__ x, double* __restrict__ r, double* __restrict__ part_r,
+               int* __restrict__ cnt) {
   const int t = blockIdx.x;
+  if (t == 0 && threadIdx.x < 2) cnt[threadIdx.x] = 0;
   double acc = 0.0;
   for (int i = T.r0[t] + threadIdx.x; i < T.r1[t]; i += kTileBlock) {
     const int c = perm[i];
     const double v = comp[c] == c ? 0.0 : rhs[c];
     b[i] = v;
+    if (r) {
+      r[i] = v;
+      x[i] = 0.0;
+    }
     acc += v * v;
   }
   double sv[1] = {acc};
   write_partials<kTileBlock, 1>(sv, part);
+  if (r) write_partials<kTileBlock, 1>(sv, part_r);
 }
 
 __global__ void __launch_bounds__(kTileBlock) k_norm2_t(Tiles T, const double* __restrict__ a,
-                                                        double* __restrict__ part) {
+                                                        double* __restrict__ part,
+                                                        int* __restrict__ cnt) {
   const int t = blockIdx.x;
+  if (cnt && t == 0 && threadIdx.x == 0) *cnt = 0;
   double acc = 0.0;
   for (int i = T.r0[t] + threadIdx.x; i < T.r1[t]; i += kTileBlock) acc += a[i] * a[i];
   double sv[1] = {acc};
@@ -1059,11 +1069,6 @@ __global__ void __launch_bounds__(kBlock) k_cast_segments(CastArgs a) {
   for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * kBlock)
     dst[i] = (float)src[i];
-}
-
-__global__ void k_copy(int n, const double* __restrict__ a, double* __restrict__ b) {
-  int i = blockIdx.x * kBlock + threadIdx.x;
-  if (i < n) b[i] = a[i];
 }
 
 double* part(ppe_solver* s, int slot) {
@@ -1859,8 +1864,8 @@ ppe_status pcg_solve(ppe_solver* s, const double* rhs, double* p_out, int use_x0
   int* iters = done + ns;
   int* restart = done + 2 * ns;
   int* cnt = s->flag.get<int>(4);  // [0] active segments, [1] error bits
-  const Tiles T{s->tile_r0.as<int>(), s->tile_r1.as<int>(), s->tile_seg.as<int>(),
-                s->seg_tile_ptr.as<int>()};
+  const int* tab = s->tile_tab.as<int>();
+  const Tiles T{tab, tab + nt, tab + 2 * (size_t)nt, tab + 3 * (size_t)nt};
   auto tpart = [&](int k) { return tp + (size_t)k * nt; };
   const int* perm = s->perm.as<int>();
   const int* comp = s->comp_full.as<int>();
@@ -1869,21 +1874,18 @@ ppe_status pcg_solve(ppe_solver* s, const double* rhs, double* p_out, int use_x0
   // the box holds the final statistics (read_back) beside the two check slots
   ensure_box(s, kBoxRead + 1 + 5 * (size_t)ns);
   std::vector<double> bbh(ns), rth(ns);
+  // without an initial guess x = 0, r = b and its norm come from the same pass
   hipLaunchKernelGGL(k_gather_rhs_t, dim3(nt), dim3(kTileBlock), 0, s->stream, T, perm, comp, rhs,
-                     b, tpart(T_BB));
+                     b, tpart(T_BB), x, use_x0 ? nullptr : r, tpart(T_RR), cnt);
   PPE_LAUNCH_CHECK();
   if (use_x0) {
     hipLaunchKernelGGL(k_gather_x0, dim3(ge), dim3(kBlock), 0, s->stream, na, perm, comp, p_out, x);
     PPE_LAUNCH_CHECK();
     apply_op<E_RESID, double>(s, L0, x, b, nullptr, 0.0, 0.0, r, nullptr);
-  } else {
-    fill_double(s, x, 0.0, na);
-    hipLaunchKernelGGL(k_copy, dim3(ge), dim3(kBlock), 0, s->stream, na, b, r);
+    hipLaunchKernelGGL(k_norm2_t, dim3(nt), dim3(kTileBlock), 0, s->stream, T, r, tpart(T_RR),
+                       nullptr);
     PPE_LAUNCH_CHECK();
   }
-  hipLaunchKernelGGL(k_norm2_t, dim3(nt), dim3(kTileBlock), 0, s->stream, T, r, tpart(T_RR));
-  PPE_LAUNCH_CHECK();
-  fill_int(s, cnt, 0, 2);
   hipLaunchKernelGGL(k_seg_init, dim3(ns), dim3(kTileBlock), 0, s->stream, ns, T, tpart(T_BB),
                      tpart(T_RR), s->opt.rtol * s->opt.rtol, sc, done, iters, restart, cnt);
   PPE_LAUNCH_CHECK();
@@ -1897,9 +1899,9 @@ ppe_status pcg_solve(ppe_solver* s, const double* rhs, double* p_out, int use_x0
   bool fetched = false;
   auto check_true = [&]() {
     apply_op<E_RESID, double>(s, L0, x, b, nullptr, 0.0, 0.0, q, nullptr);
-    hipLaunchKernelGGL(k_norm2_t, dim3(nt), dim3(kTileBlock), 0, s->stream, T, q, tpart(T_RT));
+    hipLaunchKernelGGL(k_norm2_t, dim3(nt), dim3(kTileBlock), 0, s->stream, T, q, tpart(T_RT),
+                       cnt);
     PPE_LAUNCH_CHECK();
-    fill_int(s, cnt, 0, 1);
     hipLaunchKernelGGL(k_seg_check, dim3(ns), dim3(kTileBlock), 0, s->stream, ns, T, tpart(T_RT),
                        sc, done, restart, cnt);
     PPE_LAUNCH_CHECK();
@@ -2060,9 +2062,8 @@ ppe_status pcg_solve(ppe_solver* s, const double* rhs, double* p_out, int use_x0
   }
   // out of iterations: record the true residuals
   apply_op<E_RESID, double>(s, L0, x, b, nullptr, 0.0, 0.0, q, nullptr);
-  hipLaunchKernelGGL(k_norm2_t, dim3(nt), dim3(kTileBlock), 0, s->stream, T, q, tpart(T_RT));
+  hipLaunchKernelGGL(k_norm2_t, dim3(nt), dim3(kTileBlock), 0, s->stream, T, q, tpart(T_RT), cnt);
   PPE_LAUNCH_CHECK();
-  fill_int(s, cnt, 0, 1);
   hipLaunchKernelGGL(k_seg_check, dim3(ns), dim3(kTileBlock), 0, s->stream, ns, T, tpart(T_RT), sc,
                      done, restart, cnt);
   PPE_LAUNCH_CHECK();
