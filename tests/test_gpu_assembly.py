@@ -50,6 +50,28 @@ def test_random_pockets_bitwise(seed):
     assert len(sy.pins) > 3
 
 
+@pytest.mark.parametrize("shape", [(64, 32, 32), (65, 32, 32), (48, 45, 40)])
+@pytest.mark.parametrize("floor", ["flat", "hollows"])
+def test_component_search_by_trees_bitwise(shape, floor):
+    """Up to 65,536 cells the trees of the component search are linked face by
+    face, above in one round of whole trees first where the floor of the
+    liquid has hollows (more than 64 trees); pockets stay apart either way."""
+    m = box_mesh(shape, jitter=0.0, seed=0)
+    g = m.grid_index
+    low = np.zeros(shape[:2], int) + 3
+    if floor == "hollows":
+        x, y = np.meshgrid(np.arange(shape[0]), np.arange(shape[1]), indexing="ij")
+        low = (6 + 3 * np.sin(1.7 * x) * np.cos(1.3 * y)).astype(int)
+    f = (g[:, 2] >= low[g[:, 0], g[:, 1]]).astype(float)
+    rng = np.random.default_rng(7)
+    walls = rng.integers(0, shape[0], 3)
+    f[np.isin(g[:, 0], walls) & (g[:, 1] != 5)] = 0.0   # slabs joined through one row of cells
+    f[g[:, 1] == shape[1] // 2] = 0.0                    # two halves
+    s, sy = _check_bitwise(m, f, face_coeff(m, 2400.0))
+    assert len(sy.pins) > 1
+    s.close()
+
+
 @pytest.mark.parametrize("cse", json.load(open(GOLDEN))["cases"], ids=lambda c: c["name"])
 def test_golden_chains_on_gpu(cse):
     import torch
