@@ -391,47 +391,67 @@ __global__ void __launch_bounds__(kBlock) k_coarsen_cols_ell(
 // order the general product adds them in (one sub-group walks A's row in
 // order): bitwise its result.  COUNT: entries per row into counts; else the
 // row, sorted, at rp[i].
+// The next entries of each list wait in registers, loaded kApU at a time: the
+// pass is bound by the accesses of 64 lanes to as many lines (one a cycle and
+// compute unit), and a row of P is three to four entries.  P's arrays
+// therefore extend kApU entries past its last.  Loaded one by one, each when the
+// one before it was taken, 1.47 M rows took 411 us and take 231 (0.15 M rows: 27
+// us either way).
+constexpr int kApU = 4;
+template <int U> struct __attribute__((packed, aligned(4))) ApCols { int c[U]; };
+template <int U> struct __attribute__((packed, aligned(8))) ApVals { double v[U]; };
+struct __attribute__((packed, aligned(4))) ApEnds { int first, end; };
+
 template <int WM, bool COUNT>
 __global__ void __launch_bounds__(kBlock) k_ap_merge_ell(
     int n, int W, const int* __restrict__ ecol, const double* __restrict__ ev,
     const double* __restrict__ diag, const int* __restrict__ prp, const int* __restrict__ pci,
     const double* __restrict__ pv, int* __restrict__ counts, const int* __restrict__ rp,
     int* __restrict__ ci, double* __restrict__ v) {
+  constexpr int U = COUNT ? 1 : kApU;  // the count reads columns only
   const int i = xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
   if (i >= n) return;
   int c[WM];
   slot_cols<WM>(i, n, W, ecol, c);
   // list k < WM: row c[k] of P (empty for padding); list WM: row i (the
   // diagonal), which comes before list dpos in CSR order
-  int pos[WM + 1], end[WM + 1], col[WM + 1];
-  double a[WM + 1], pval[WM + 1];
+  int pos[WM + 1], end[WM + 1];
+  ApCols<U> col[WM + 1];
+  ApVals<U> val[WM + 1];
+  double a[WM + 1];
   int dpos = WM;
 #pragma unroll
   for (int k = WM; k >= 0; --k) {
     const int j = k < WM ? c[k] : i;
     const bool real = k == WM || j != i;
     if (k < WM && real && j > i) dpos = k;
-    pos[k] = real ? prp[j] : 0;
-    end[k] = real ? prp[j + 1] : 0;
+    const ApEnds e = *reinterpret_cast<const ApEnds*>(prp + j);
+    pos[k] = real ? e.first : 0;
+    end[k] = real ? e.end : 0;
     if (!COUNT) a[k] = k < WM ? (real ? ev[(size_t)k * n + i] : 0.0) : diag[i];
   }
+  auto load = [&](int k) {  // entries pos .. pos + U of list k, past its end none
+    col[k] = *reinterpret_cast<const ApCols<U>*>(pci + pos[k]);
+    if (!COUNT) val[k] = *reinterpret_cast<const ApVals<U>*>(pv + pos[k]);
 #pragma unroll
-  for (int k = 0; k <= WM; ++k) {
-    col[k] = pos[k] < end[k] ? pci[pos[k]] : INT32_MAX;
-    if (!COUNT) pval[k] = pos[k] < end[k] ? pv[pos[k]] : 0.0;
-  }
+    for (int u = 0; u < U; ++u)
+      if (pos[k] + u >= end[k]) col[k].c[u] = INT32_MAX;
+    pos[k] += U;
+  };
+#pragma unroll
+  for (int k = 0; k <= WM; ++k) load(k);
   int out = COUNT ? 0 : rp[i];
   for (;;) {
-    int cur = col[0];
+    int cur = col[0].c[0];
 #pragma unroll
-    for (int k = 1; k <= WM; ++k) cur = col[k] < cur ? col[k] : cur;
+    for (int k = 1; k <= WM; ++k) cur = min(cur, col[k].c[0]);
     if (cur == INT32_MAX) break;
     if (!COUNT) {
       double sum = 0.0;
 #pragma unroll
       for (int k = 0; k <= WM; ++k) {
-        if (k == dpos && col[WM] == cur) sum = sum + a[WM] * pval[WM];
-        if (k < WM && col[k] == cur) sum = sum + a[k] * pval[k];
+        if (k == dpos && col[WM].c[0] == cur) sum = sum + a[WM] * val[WM].v[0];
+        if (k < WM && col[k].c[0] == cur) sum = sum + a[k] * val[k].v[0];
       }
       ci[out] = cur;
       v[out] = sum;
@@ -439,10 +459,14 @@ __global__ void __launch_bounds__(kBlock) k_ap_merge_ell(
     ++out;
 #pragma unroll
     for (int k = 0; k <= WM; ++k)
-      if (col[k] == cur) {
-        ++pos[k];
-        col[k] = pos[k] < end[k] ? pci[pos[k]] : INT32_MAX;
-        if (!COUNT) pval[k] = pos[k] < end[k] ? pv[pos[k]] : 0.0;
+      if (col[k].c[0] == cur) {
+#pragma unroll
+        for (int u = 0; u + 1 < U; ++u) {
+          col[k].c[u] = col[k].c[u + 1];
+          if (!COUNT) val[k].v[u] = val[k].v[u + 1];
+        }
+        col[k].c[U - 1] = INT32_MAX;
+        if (col[k].c[0] == INT32_MAX && pos[k] < end[k]) load(k);
       }
   }
   if (COUNT) counts[i] = out;
@@ -2184,7 +2208,7 @@ static void coarsen_cols_ell(ppe_solver* s, const Level& L, const int* agg, cons
   require(total <= INT32_MAX, PPE_ERR_INTERNAL, "sparse product too large for int32 indices");
   Q.nnz = total;
   Q.maxrow = fm[1];
-  int* qci = Q.col.get<int>(Q.nnz);
+  int* qci = Q.col.get<int>(Q.nnz + kApU);  // P takes this array
   double* qv = Q.val.get<double>(Q.nnz);
   if (W <= 4) PPE_QC(4, false, nullptr, qrp, qci, qv);
   else if (W <= 6) PPE_QC(6, false, nullptr, qrp, qci, qv);
@@ -2435,7 +2459,7 @@ void build_hierarchy(ppe_solver* s) {
         join();  // the smoothing uses this level's spectral bound
         hipLaunchKernelGGL(k_smooth_p, dim3(g), dim3(kBlock), 0, s->stream, n, L0.Q.rp(), L0.Q.ci(),
                            L0.Q.v(), L0.diag.as<double>(), agg, pt, rho_dev + lvl,
-                           P.val.get<double>(P.nnz));
+                           P.val.get<double>(P.nnz + kApU));
         PPE_LAUNCH_CHECK();
         // P has the pattern of A P_tent: take its arrays instead of copying
         std::swap(P.rowptr, L0.Q.rowptr);
