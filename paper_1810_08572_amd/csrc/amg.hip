@@ -327,7 +327,9 @@ __global__ void __launch_bounds__(kBlock) k_agg_second_ell(int n, int W, const i
   agg[i] = a;
 }
 
-// Finest level: Q = A P_tent from the ELL copy, one thread per row.  P_tent
+// Finest level: the smoothed prolongator P = P_tent - omega D^-1 Q, Q = A
+// P_tent, from the ELL copy, one thread per row (omega as in k_smooth_p; a pass
+// of its own took 54 us for 1.47 M rows, reading Q back).  P_tent
 // has one entry per aggregated node (pt_j in column agg_j), so row i of Q
 // holds, for every aggregate J reached from row i, the sum of a_ij pt_j
 // over that row's entries j in J.  The row's entries are taken in CSR order
@@ -339,8 +341,8 @@ template <int WM, bool COUNT>
 __global__ void __launch_bounds__(kBlock) k_coarsen_cols_ell(
     int n, int W, const int* __restrict__ ecol, const double* __restrict__ ev,
     const double* __restrict__ diag, const int* __restrict__ agg, const double* __restrict__ pt,
-    int* __restrict__ counts, const int* __restrict__ rp, int* __restrict__ ci,
-    double* __restrict__ v) {
+    const double* __restrict__ rho, int* __restrict__ counts, const int* __restrict__ rp,
+    int* __restrict__ ci, double* __restrict__ v) {
   const int i = xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
   if (i >= n) return;
   // fixed register slots: ELL slot k (aggregate Jk[k], -1 for none), and the
@@ -359,7 +361,9 @@ __global__ void __launch_bounds__(kBlock) k_coarsen_cols_ell(
     if (!COUNT) yk[k] = Jk[k] >= 0 ? ev[(size_t)k * n + i] * pt[j] : 0.0;
   }
   const int Jd = agg[i];
-  const double yd = (!COUNT && Jd >= 0) ? diag[i] * pt[i] : 0.0;
+  const double di = COUNT ? 1.0 : diag[i], pti = !COUNT && Jd >= 0 ? pt[i] : 0.0;
+  const double yd = Jd >= 0 ? di * pti : 0.0;
+  const double omega = COUNT ? 0.0 : 4.0 / (3.0 * *rho), dinv = 1.0 / di;
   int out = COUNT ? 0 : rp[i];
   int last = -1;
   for (int step = 0; step <= WM; ++step) {
@@ -376,7 +380,7 @@ __global__ void __launch_bounds__(kBlock) k_coarsen_cols_ell(
         if (k < WM && Jk[k] == cur) sum = sum + yk[k];
       }
       ci[out] = cur;
-      v[out] = sum;
+      v[out] = (cur == Jd ? pti : 0.0) - omega * (sum * dinv);
     }
     ++out;
     last = cur;
@@ -2187,15 +2191,15 @@ const double* level0_bound_async(ppe_solver* s) {
   return out;
 }
 
-// Q = A P_tent on the finest level from its ELL copy (k_coarsen_cols_ell):
-// count, scan with the longest row (one round trip), fill.  Q is what the
-// general product gives, entry for entry.
+// P on the finest level from its ELL copy (k_coarsen_cols_ell): count, scan
+// with the longest row (one round trip), fill.  P is what the general product
+// and k_smooth_p give, entry for entry.
 static void coarsen_cols_ell(ppe_solver* s, const Level& L, const int* agg, const double* pt,
-                             int na, Csr& Q, int* flag) {
+                             int na, const double* rho, Csr& P, int* flag) {
   const int n = L.n, W = L.W;
-  Q.n = n;
-  Q.m = na;
-  int* qrp = Q.rowptr.get<int>(n + 1);
+  P.n = n;
+  P.m = na;
+  int* prp = P.rowptr.get<int>(n + 1);
   int* counts = s->sp_cnt.get<int>(n + 1);
   const int g = grid_for(n);
   const int* ecol = L.ell_col.as<int>();
@@ -2203,22 +2207,22 @@ static void coarsen_cols_ell(ppe_solver* s, const Level& L, const int* agg, cons
   const double* dg = L.diag.as<double>();
 #define PPE_QC(WM, COUNT, ...)                                                                 \
   hipLaunchKernelGGL((k_coarsen_cols_ell<WM, COUNT>), dim3(g), dim3(kBlock), 0, s->stream, n, W, \
-                     ecol, ev, dg, agg, pt, __VA_ARGS__)
+                     ecol, ev, dg, agg, pt, rho, __VA_ARGS__)
   if (W <= 4) PPE_QC(4, true, counts, nullptr, nullptr, nullptr);
   else if (W <= 6) PPE_QC(6, true, counts, nullptr, nullptr, nullptr);
   else PPE_QC(8, true, counts, nullptr, nullptr, nullptr);
   PPE_LAUNCH_CHECK();
   int fm[2] = {0, 0};
-  const long long total = exclusive_scan_read(s, counts, qrp, n, flag + 1,
+  const long long total = exclusive_scan_read(s, counts, prp, n, flag + 1,
                                               {ReadItem{flag, sizeof(int) * 2, fm}});
   require(total <= INT32_MAX, PPE_ERR_INTERNAL, "sparse product too large for int32 indices");
-  Q.nnz = total;
-  Q.maxrow = fm[1];
-  int* qci = Q.col.get<int>(Q.nnz + kApU);  // P takes this array
-  double* qv = Q.val.get<double>(Q.nnz);
-  if (W <= 4) PPE_QC(4, false, nullptr, qrp, qci, qv);
-  else if (W <= 6) PPE_QC(6, false, nullptr, qrp, qci, qv);
-  else PPE_QC(8, false, nullptr, qrp, qci, qv);
+  P.nnz = total;
+  P.maxrow = fm[1];
+  int* pci = P.col.get<int>(P.nnz + kApU);
+  double* pv = P.val.get<double>(P.nnz + kApU);
+  if (W <= 4) PPE_QC(4, false, nullptr, prp, pci, pv);
+  else if (W <= 6) PPE_QC(6, false, nullptr, prp, pci, pv);
+  else PPE_QC(8, false, nullptr, prp, pci, pv);
 #undef PPE_QC
   PPE_LAUNCH_CHECK();
 }
@@ -2441,9 +2445,13 @@ void build_hierarchy(ppe_solver* s) {
         PPE_LAUNCH_CHECK();
         int* flag = reinterpret_cast<int*>(rho_dev + maxlev + 1 + 3 * lvl);
         const bool merge = lvl == 0 && L0.W > 0 && L0.W <= 8;
-        // smoothed prolongator
+        // smoothed prolongator (with this level's spectral bound)
+        Csr& P = L0.P;
+        P.n = n;
+        P.m = na;
         if (merge) {
-          coarsen_cols_ell(s, L0, agg, pt, na, L0.Q, flag);
+          join();
+          coarsen_cols_ell(s, L0, agg, pt, na, rho_dev + lvl, P, flag);
         } else {
           Csr& Pt = L0.Pt;
           Pt.n = n;
@@ -2456,20 +2464,17 @@ void build_hierarchy(ppe_solver* s) {
                              Pt.col.get<int>(Pt.nnz), Pt.val.get<double>(Pt.nnz));
           PPE_LAUNCH_CHECK();
           spgemm(s, L0.A, Pt, L0.Q, flag, nullptr, nullptr);
+          P.nnz = L0.Q.nnz;
+          P.maxrow = L0.Q.maxrow;
+          join();
+          hipLaunchKernelGGL(k_smooth_p, dim3(g), dim3(kBlock), 0, s->stream, n, L0.Q.rp(),
+                             L0.Q.ci(), L0.Q.v(), L0.diag.as<double>(), agg, pt, rho_dev + lvl,
+                             P.val.get<double>(P.nnz));
+          PPE_LAUNCH_CHECK();
+          // P has the pattern of A P_tent: take its arrays instead of copying
+          std::swap(P.rowptr, L0.Q.rowptr);
+          std::swap(P.col, L0.Q.col);
         }
-        Csr& P = L0.P;
-        P.n = n;
-        P.m = na;
-        P.nnz = L0.Q.nnz;
-        P.maxrow = L0.Q.maxrow;
-        join();  // the smoothing uses this level's spectral bound
-        hipLaunchKernelGGL(k_smooth_p, dim3(g), dim3(kBlock), 0, s->stream, n, L0.Q.rp(), L0.Q.ci(),
-                           L0.Q.v(), L0.diag.as<double>(), agg, pt, rho_dev + lvl,
-                           P.val.get<double>(P.nnz + kApU));
-        PPE_LAUNCH_CHECK();
-        // P has the pattern of A P_tent: take its arrays instead of copying
-        std::swap(P.rowptr, L0.Q.rowptr);
-        std::swap(P.col, L0.Q.col);
         const int* rmax = transpose(s, P, L0.R);
         if (merge)
           ap_merge_ell(s, L0, P, L0.AP, flag + 2, rmax, &L0.R.maxrow);
