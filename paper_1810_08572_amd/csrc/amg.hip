@@ -721,15 +721,10 @@ __global__ void __launch_bounds__(kBlock) k_agg_second(int n, const int* __restr
   }
 }
 
-__global__ void k_agg_count(int n, const int* __restrict__ agg, int* __restrict__ cnt) {
+__global__ void k_agg_fill(int n, const int* __restrict__ agg, const int* __restrict__ ptr,
+                           const int* __restrict__ pos, int* __restrict__ mem) {
   int i = blockIdx.x * kBlock + threadIdx.x;
-  if (i < n && agg[i] >= 0) atomicAdd(&cnt[agg[i]], 1);
-}
-
-__global__ void k_agg_fill(int n, const int* __restrict__ agg, int* __restrict__ cursor,
-                           int* __restrict__ mem) {
-  int i = blockIdx.x * kBlock + threadIdx.x;
-  if (i < n && agg[i] >= 0) mem[atomicAdd(&cursor[agg[i]], 1)] = i;
+  if (i < n && agg[i] >= 0) mem[ptr[agg[i]] + pos[i]] = i;
 }
 
 // Sort each aggregate's members, then norm_J = sqrt(sum B_i^2) in ascending
@@ -1423,7 +1418,9 @@ __global__ void __launch_bounds__(1024) k_narrow_fill(int64_t nnz, const int* __
   }
 }
 
-// Column counts of a CSR, and for every entry its place among its column's.
+// Column counts of a CSR, and for every entry its place among its column's
+// (with the aggregate of each node for column: member counts and places; a
+// negative column is none).
 // Consecutive entries belong to neighbouring rows and share columns, and
 // device-scope atomics, not the loads, bound a pass with one per entry: a block
 // counts its kSlotChunk entries in an LDS hash of their columns and then takes
@@ -2482,13 +2479,14 @@ void build_hierarchy(ppe_solver* s) {
         // row pointers are exact)
         int* cnt = s->tmp_i[0].get<int>(na + 1);
         fill_int(s, cnt, 0, na + 1);
-        hipLaunchKernelGGL(k_agg_count, dim3(g), dim3(kBlock), 0, s->stream, n, agg, cnt);
+        int* pos = s->tmp_i[1].get<int>(n);
+        hipLaunchKernelGGL(k_col_slots, dim3(grid_for(n, kSlotChunk)), dim3(kBlock), 0, s->stream,
+                           (int64_t)n, agg, cnt, pos);
         PPE_LAUNCH_CHECK();
         int* aptr = L.agg_ptr.get<int>(na + 1);
-        int* cursor = s->tmp_i[1].get<int>(na + 1);
-        exclusive_scan_async(s, cnt, aptr, na, 0, nullptr, cursor);
+        exclusive_scan_async(s, cnt, aptr, na);
         int* mem = L.agg_mem.get<int>(n);
-        hipLaunchKernelGGL(k_agg_fill, dim3(g), dim3(kBlock), 0, s->stream, n, agg, cursor, mem);
+        hipLaunchKernelGGL(k_agg_fill, dim3(g), dim3(kBlock), 0, s->stream, n, agg, aptr, pos, mem);
         PPE_LAUNCH_CHECK();
         if ((int)s->levels.size() < lvl + 2) s->levels.resize(lvl + 2);
         Level& L0 = s->levels[lvl];  // re-fetch: resize may move levels

@@ -526,9 +526,9 @@ int64_t exclusive_scan(ppe_solver* s, const int* in, int* out, int n);
 // the total (a long long in tmp_l[slot], slot 0 or 1, valid until the next
 // scan through that slot).  With max_out, the largest count is also max-ed
 // into *max_out, as max_int_async(..., init = false) would do, with no
-// dispatch of its own.  With copy, copy[0..n) receives the offsets as well.
+// dispatch of its own.
 long long* exclusive_scan_async(ppe_solver* s, const int* in, int* out, int n, int slot = 0,
-                                int* max_out = nullptr, int* copy = nullptr);
+                                int* max_out = nullptr);
 // The same through slot 0 with a round trip that the scan's own dispatch
 // publishes: returns the total and reads the further items (device values ready
 // before the scan, or *max_out).

@@ -128,8 +128,7 @@ __global__ void __launch_bounds__(kBlock) k_scan_top(long long* __restrict__ bsu
 __global__ void __launch_bounds__(kBlock) k_scan_down(const int* __restrict__ in, int n,
                                                       const long long* __restrict__ boff,
                                                       const long long* __restrict__ total,
-                                                      int* __restrict__ out,
-                                                      int* __restrict__ copy) {
+                                                      int* __restrict__ out) {
   const long long base = (long long)blockIdx.x * kScanTile + (long long)threadIdx.x * kScanItems;
   int v[kScanItems];
   long long s = 0;
@@ -144,10 +143,7 @@ __global__ void __launch_bounds__(kBlock) k_scan_down(const int* __restrict__ in
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     long long i = base + k;
-    if (i < n) {
-      out[i] = (int)run;
-      if (copy) copy[i] = (int)run;
-    }
+    if (i < n) out[i] = (int)run;
     run += v[k];
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = (int)*total;
@@ -178,7 +174,6 @@ constexpr int kSmallScan = kSmallBlock * kSmallItems;
 
 __global__ void __launch_bounds__(kSmallBlock) k_scan_small(const int* __restrict__ in, int n,
                                                             int* __restrict__ out,
-                                                            int* __restrict__ copy,
                                                             long long* __restrict__ total,
                                                             int* __restrict__ mx, PubArgs pub) {
   constexpr int kWaves = kSmallBlock / kWave;
@@ -227,10 +222,7 @@ __global__ void __launch_bounds__(kSmallBlock) k_scan_small(const int* __restric
   for (int k = 0; k < kSmallItems; ++k) {
     const int i = threadIdx.x + k * kSmallBlock;
     const int off = wsum[k * kWaves + w] + inc[k] - item[k];
-    if (i < n) {
-      out[i] = off;
-      if (copy) copy[i] = off;
-    }
+    if (i < n) out[i] = off;
   }
   if (threadIdx.x == 0) {
     out[n] = (int)sum;
@@ -296,12 +288,12 @@ static void read_items(ppe_solver* s, const Published& pub, const std::vector<Re
 }
 
 static long long* scan_launch(ppe_solver* s, const int* in, int* out, int n, int slot, int* max_out,
-                              int* copy, const PubArgs& pub) {
+                              const PubArgs& pub) {
   if (n < 0) throw Error(PPE_ERR_INTERNAL, "negative scan length");
   long long* total = scan_total(s, n, slot, max_out);
   if (n <= kSmallScan) {
-    hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(kSmallBlock), 0, s->stream, in, n, out, copy,
-                       total, max_out, pub);
+    hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(kSmallBlock), 0, s->stream, in, n, out, total,
+                       max_out, pub);
     PPE_LAUNCH_CHECK();
     return total;
   }
@@ -313,15 +305,14 @@ static long long* scan_launch(ppe_solver* s, const int* in, int* out, int n, int
   hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kBlock), 0, s->stream, bsum, nb, total,
                      (const int*)bmax, max_out, pub);
   PPE_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_scan_down, dim3(nb), dim3(kBlock), 0, s->stream, in, n, bsum, total, out,
-                     copy);
+  hipLaunchKernelGGL(k_scan_down, dim3(nb), dim3(kBlock), 0, s->stream, in, n, bsum, total, out);
   PPE_LAUNCH_CHECK();
   return total;
 }
 
 long long* exclusive_scan_async(ppe_solver* s, const int* in, int* out, int n, int slot,
-                                int* max_out, int* copy) {
-  return scan_launch(s, in, out, n, slot, max_out, copy, PubArgs{});
+                                int* max_out) {
+  return scan_launch(s, in, out, n, slot, max_out, PubArgs{});
 }
 
 long long exclusive_scan_read(ppe_solver* s, const int* in, int* out, int n, int* max_out,
@@ -330,7 +321,7 @@ long long exclusive_scan_read(ppe_solver* s, const int* in, int* out, int n, int
   std::vector<ReadItem> all{ReadItem{scan_total(s, n, 0, max_out), sizeof(long long), &t}};
   all.insert(all.end(), more);
   const PubArgs pub = pub_args(s, all.data(), (int)all.size(), kBoxRead);
-  scan_launch(s, in, out, n, 0, max_out, nullptr, pub);
+  scan_launch(s, in, out, n, 0, max_out, pub);
   read_items(s, Published{s->box_h + kBoxRead, pub.tag}, all);
   return t;
 }
