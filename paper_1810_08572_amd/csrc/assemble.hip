@@ -135,6 +135,17 @@ __device__ __forceinline__ int find_root(int* parent, int x) {
   return x;
 }
 
+// Entries e .. e + kAdjU of cell i's neighbours (past e1: i itself), requested
+// together; the passes over a cell's faces then request what those name before
+// they use the first.  One by one, each entry waited for its own loads (1.7 M rows:
+// filling them 200 us, now 130; counting them 36 and 21).
+constexpr int kAdjU = 6;
+__device__ __forceinline__ void adj_chunk(int e, int e1, int i, const int* __restrict__ adj,
+                                          int (&out)[kAdjU]) {
+#pragma unroll
+  for (int u = 0; u < kAdjU; ++u) out[u] = e + u < e1 ? adj[e + u] : i;
+}
+
 // Connected components start from a forest built without atomics: every
 // active cell hooks to its smallest active neighbour (or itself), which
 // already joins most of a component; the forest is then flattened (each cell
@@ -146,11 +157,18 @@ __global__ void k_cc_init(int n, const int* __restrict__ adj_ptr, const int* __r
   const int i = blockIdx.x * kBlock + threadIdx.x;
   if (i >= n) return;
   int m = i;
-  if (active[i])
-    for (int k = adj_ptr[i]; k < adj_ptr[i + 1]; ++k) {
-      const int j = adj_nbr[k];
-      if (j < m && active[j]) m = j;
+  if (active[i]) {
+    const int e1 = adj_ptr[i + 1];
+    for (int e = adj_ptr[i]; e < e1; e += kAdjU) {
+      int nb[kAdjU], on[kAdjU];
+      adj_chunk(e, e1, i, adj_nbr, nb);
+#pragma unroll
+      for (int u = 0; u < kAdjU; ++u) on[u] = active[nb[u]];
+#pragma unroll
+      for (int u = 0; u < kAdjU; ++u)
+        if (on[u]) m = min(m, nb[u]);
     }
+  }
   forest[i] = m;
 }
 
@@ -273,9 +291,18 @@ __global__ void k_row_counts(const int* __restrict__ perm, const int* __restrict
   int c = perm[r];
   int cnt = 1;
   if (!is_pin[c]) {
-    for (int k = adj_ptr[c]; k < adj_ptr[c + 1]; ++k) {
-      int j = adj_nbr[k];
-      if (active[j] && !is_pin[j]) ++cnt;
+    const int e1 = adj_ptr[c + 1];
+    for (int e = adj_ptr[c]; e < e1; e += kAdjU) {
+      int nb[kAdjU], on[kAdjU], pin[kAdjU];
+      adj_chunk(e, e1, c, adj_nbr, nb);
+#pragma unroll
+      for (int u = 0; u < kAdjU; ++u) {
+        on[u] = active[nb[u]];
+        pin[u] = is_pin[nb[u]];
+      }
+#pragma unroll
+      for (int u = 0; u < kAdjU; ++u)
+        if (nb[u] != c && on[u] && !pin[u]) ++cnt;
     }
   }
   counts[r] = cnt;
@@ -307,10 +334,28 @@ __global__ void k_fill_rows(const int* __restrict__ perm, int n_active,
   if (r < n_active) {
     int c = perm[r];
     const bool pin = is_pin[c] != 0;
+    const int e0 = adj_ptr[c], e1 = adj_ptr[c + 1];
+    // kAdjU faces at a time: neighbour, face coefficient, whether open, whether
+    // the neighbour is a pin, its row
+    int nb[kAdjU], f[kAdjU], on[kAdjU], pj[kAdjU], cj[kAdjU];
+    double w[kAdjU];
+    auto load = [&](int e) {
+      adj_chunk(e, e1, c, adj_nbr, nb);
+      adj_chunk(e, e1, 0, adj_face, f);
+#pragma unroll
+      for (int u = 0; u < kAdjU; ++u) {
+        on[u] = nb[u] != c && active[nb[u]];
+        pj[u] = is_pin[nb[u]];
+        cj[u] = cid[nb[u]];
+        w[u] = nb[u] != c ? coeff[f[u]] : 0.0;
+      }
+    };
     double d = shift ? shift[c] : 0.0;
-    for (int k = adj_ptr[c]; k < adj_ptr[c + 1]; ++k) {
-      int j = adj_nbr[k];
-      if (active[j]) d = d + coeff[adj_face[k]];
+    for (int e = e0; e < e1; e += kAdjU) {
+      load(e);
+#pragma unroll
+      for (int u = 0; u < kAdjU; ++u)
+        if (on[u]) d = d + w[u];
     }
     if (pin && d == 0.0) d = 1.0;
     diag[r] = d;
@@ -319,23 +364,24 @@ __global__ void k_fill_rows(const int* __restrict__ perm, int n_active,
     int slot = 0;
     bool diag_done = false;
     if (!pin) {
-      for (int k = adj_ptr[c]; k < adj_ptr[c + 1]; ++k) {
-        int j = adj_nbr[k];
-        if (!active[j] || is_pin[j]) continue;
-        int cj = cid[j];
-        double v = -coeff[adj_face[k]];
-        if (!diag_done && cj > r) {
-          cdst[p] = r;
-          vdst[p] = d;
+      for (int e = e0; e < e1; e += kAdjU) {
+        if (e1 - e0 > kAdjU) load(e);
+#pragma unroll
+        for (int u = 0; u < kAdjU; ++u) {
+          if (!on[u] || pj[u]) continue;
+          if (!diag_done && cj[u] > r) {
+            cdst[p] = r;
+            vdst[p] = d;
+            ++p;
+            diag_done = true;
+          }
+          cdst[p] = cj[u];
+          vdst[p] = -w[u];
           ++p;
-          diag_done = true;
+          ell_col[(size_t)slot * n_active + r] = cj[u];
+          ell_val[(size_t)slot * n_active + r] = -w[u];
+          ++slot;
         }
-        cdst[p] = cj;
-        vdst[p] = v;
-        ++p;
-        ell_col[(size_t)slot * n_active + r] = cj;
-        ell_val[(size_t)slot * n_active + r] = v;
-        ++slot;
       }
     }
     if (!diag_done) {
