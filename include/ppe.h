@@ -91,7 +91,9 @@ typedef struct {
                          convergence leave a converged system untouched, so
                          the result and iteration count do not depend on it */
   void* stream;       /* hipStream_t used for every launch; NULL = default stream */
-  int use_graph;      /* replay PCG iterations from a captured HIP graph, default 1 */
+  int use_graph;      /* replay PCG iterations from a captured HIP graph, default 1
+                         (captured once the system has been solved often enough
+                         since its assembly for the capture to pay) */
   int autotune;       /* 1: at assembly, time the candidate launch choices of each
                          level's solve kernels (lanes per row of the smoother,
                          restriction and prolongation; fused or split first
@@ -511,8 +513,10 @@ ppe_status ppe_pce_stats(ppe_pce* q, int64_t n_out, const double* W, double* mea
  * the kernel time and the algorithmic bytes each launch moves: every stored
  * matrix entry read once (value + 4-byte column index; 4-byte row pointers
  * for CSR), each diagonal read once, and 8 bytes per row for every vector
- * the kernel reads or writes.  Graph replay is off meanwhile.  Enabling
- * resets the table.  PPE_ERR_ARG on NULL. */
+ * the kernel reads or writes.  Graph replay is off meanwhile, and passes
+ * that a solve otherwise takes together on the finest level (the next
+ * direction and its product, the prolongation and the first post-smoothing
+ * step) run one by one.  Enabling resets the table.  PPE_ERR_ARG on NULL. */
 ppe_status ppe_profile_enable(ppe_solver* s, int enable);
 /* *n_kernels = the number of kernel instantiations recorded so far. */
 ppe_status ppe_profile_count(const ppe_solver* s, int32_t* n_kernels);

@@ -208,7 +208,7 @@ constexpr int kHookCells = 1 << 16, kFewTrees = 64;
 // and linking those face by face grows chains that every later find walks at
 // a memory round trip a step.  Linking them took 1,262 us on average over the
 // assemblies of a 64^3 melting pool, up to 2,478; with a test for cells of one
-// tree before it and this round 92, up to 289, after 24 for the round itself (a
+// tree before it and this pass 92, up to 289, after 24 for the pass itself (a
 // second round: no gain).  The pool's three time steps went from 56.3 to 53.9 ms.
 __global__ void k_cc_hook(int n, const int* __restrict__ adj_ptr, const int* __restrict__ adj_nbr,
                           const int* __restrict__ active, const int* __restrict__ parent,
