@@ -514,9 +514,9 @@ ppe_status ppe_pce_stats(ppe_pce* q, int64_t n_out, const double* W, double* mea
  * matrix entry read once (value + 4-byte column index; 4-byte row pointers
  * for CSR), each diagonal read once, and 8 bytes per row for every vector
  * the kernel reads or writes.  Graph replay is off meanwhile, and passes
- * that a solve otherwise takes together on the finest level (the next
- * direction and its product, the prolongation and the first post-smoothing
- * step) run one by one.  Enabling resets the table.  PPE_ERR_ARG on NULL. */
+ * that a solve otherwise takes together on the finest level (the residual's
+ * update and the first smoothing steps, the next direction and its product,
+ * the prolongation and the first post-smoothing step) run one by one.  Enabling resets the table.  PPE_ERR_ARG on NULL. */
 ppe_status ppe_profile_enable(ppe_solver* s, int enable);
 /* *n_kernels = the number of kernel instantiations recorded so far. */
 ppe_status ppe_profile_count(const ppe_solver* s, int32_t* n_kernels);

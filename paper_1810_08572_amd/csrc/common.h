@@ -238,7 +238,7 @@ struct ppe_solver {
   int nlev = 0;                    // levels in use
 
   // solve workspace
-  ppe::DevBuf vx, vr, vz, vp, vp2, vq, vzold, vb;
+  ppe::DevBuf vx, vr, vz, vp, vp2, vr2, vq, vzold, vb;
   ppe::DevBuf scal, partial, counter, flag;
   ppe::DevBuf tmp_i[4], tmp_d[2], tmp_l[2];
   ppe::DevBuf sp_prod, sp_cnt, sp_ci, sp_v;  // sparse-product scratch

@@ -999,6 +999,108 @@ __global__ void __launch_bounds__(kTileBlock) k_direction_t(
   write_partials<kTileBlock, 1>(sv, part, t);
 }
 
+// The x, r update and the V-cycle's first two smoothing steps in one pass.
+// Rows read the old r of their neighbours, so r alternates between two buffers.
+// b_j = r_j - alpha q_j and everything made of it are the expressions of
+// k_update_xr_t and of E_CHEB0, so the results are the two passes' bit for bit.
+// Rows of samples that have converged are copied.  It saves a dispatch and pays
+// with a gather and a division's operands more per entry: 2.8 k rows' solve 466 ->
+// 432 us, 150 k rows' 1,069 -> 1,089, 260 k rows' 1,766 -> 1,846; the two sides
+// meet near 10^5 rows.
+constexpr int kFuseAdvance = 1 << 16;
+
+template <class M, int WM>
+__global__ void __launch_bounds__(kTileBlock) k_advance_t(
+    Tiles T, const int* __restrict__ done, const double* __restrict__ rz,
+    const double* __restrict__ part_pq, const double* __restrict__ p,
+    const double* __restrict__ qv, double* __restrict__ x, const double* __restrict__ r,
+    double* __restrict__ r_out, double* __restrict__ part, int* __restrict__ active,
+    int* __restrict__ err, int n, int W, const int* __restrict__ ecol,
+    const M* __restrict__ eval, const M* __restrict__ diag, const M* __restrict__ sd, double c0,
+    double c1, double c2, double* __restrict__ d, double* __restrict__ y) {
+  constexpr int U = WM > 0 ? WM : 1;
+  const int t = xcd_block(blockIdx.x, gridDim.x);  // the tile (its partial's slot)
+  const int q = T.seg[t];
+  if (t == 0 && threadIdx.x == 0) *active = 0;  // counted again with the direction
+  const int i0 = T.r0[t] + threadIdx.x, i1 = T.r1[t];
+  double xi = 0.0, pi = 0.0, ri = 0.0, qi = 0.0, di = 1.0, si = 1.0, gr[U], gq[U], gs[U];
+  M v[U];
+  auto request = [&](int i) {
+    xi = x[i];
+    pi = p[i];
+    ri = r[i];
+    qi = qv[i];
+    di = (double)diag[i];
+    si = (double)sd[i];
+    if constexpr (WM > 0) {
+      int col[U];
+      if (W == U) {  // every slot stored: no condition (as in ell_row)
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+          const size_t e = (size_t)k * n + i;
+          col[k] = ecol[e];
+          v[k] = eval[e];
+        }
+      } else {
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+          const size_t e = (size_t)k * n + i;
+          col[k] = k < W ? ecol[e] : i;
+          v[k] = k < W ? eval[e] : M(0);
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        gr[k] = r[col[k]];
+        gq[k] = qv[col[k]];
+        gs[k] = (double)sd[col[k]];
+      }
+    }
+  };
+  if (i0 < i1) request(i0);
+  bool move = false;
+  double alpha = 0.0;
+  if (!done[q]) {
+    const double pq = seg_sum(part_pq, T, q);
+    const double num = rz[q];
+    if (!(pq > 0.0) || !(num > 0.0)) {
+      if (threadIdx.x == 0) atomicOr(err, 1);
+    } else {
+      move = true;
+      alpha = num / pq;
+    }
+  }
+  auto res = [&](double rj, double qj) { return move ? rj - alpha * qj : rj; };
+  double acc = 0.0;
+  for (int i = i0; i < i1; i += kTileBlock) {
+    if (i != i0) request(i);
+    const double b = res(ri, qi);
+    const double x1 = c0 * (b / si);
+    double s = di * x1;
+    if constexpr (WM > 0) {
+#pragma unroll
+      for (int k = 0; k < U; ++k)
+        if (k < W) s = s + (double)v[k] * (c0 * (res(gr[k], gq[k]) / gs[k]));
+    } else {
+      for (int k = 0; k < W; ++k) {
+        const size_t e = (size_t)k * n + i;
+        const int j = ecol[e];
+        s = s + (double)eval[e] * (c0 * (res(r[j], qv[j]) / (double)sd[j]));
+      }
+    }
+    r_out[i] = b;
+    if (move) {
+      x[i] = xi + alpha * pi;
+      acc += b * b;
+    }
+    const double dn = c1 * x1 + c2 * ((b - s) / si);
+    d[i] = dn;
+    y[i] = x1 + dn;
+  }
+  double sv[1] = {acc};
+  write_partials<kTileBlock, 1>(sv, part, t);
+}
+
 // After the recurred residuals all met the tolerance: per segment (one
 // block each), the true residual; a segment that misses it restarts.
 __global__ void __launch_bounds__(kTileBlock) k_seg_check(int ns, Tiles T,
@@ -1022,10 +1124,11 @@ __global__ void __launch_bounds__(kTileBlock) k_seg_check(int ns, Tiles T,
 // r = r_true on segments that restart
 __global__ void __launch_bounds__(kTileBlock)
 k_copy_restart_t(Tiles T, const int* __restrict__ restart, const double* __restrict__ rt,
-                 double* __restrict__ r) {
+                 const double* r, double* r_out) {
   const int t = blockIdx.x;
-  if (!restart[T.seg[t]]) return;
-  for (int i = T.r0[t] + threadIdx.x; i < T.r1[t]; i += kTileBlock) r[i] = rt[i];
+  const bool again = restart[T.seg[t]] != 0;
+  if (!again && r == r_out) return;
+  for (int i = T.r0[t] + threadIdx.x; i < T.r1[t]; i += kTileBlock) r_out[i] = again ? rt[i] : r[i];
 }
 
 __global__ void k_gather_x0(int na, const int* __restrict__ perm, const int* __restrict__ comp,
@@ -1383,7 +1486,7 @@ bool smooth_steps(ppe_solver* s, Level& L, const double* b, const double* cur, i
 
 template <class M>
 bool smooth(ppe_solver* s, Level& L, const double* b, const double* x_in, double* x_out,
-            double* xa, double* xb, const PcgDot* dot = nullptr, bool first_done = false) {
+            double* xa, double* xb, const PcgDot* dot = nullptr, int taken = 0) {
   const int n = L.n;
   const int deg = 1 + (int)L.c1.size();
   double* d = L.d.as<double>();
@@ -1391,9 +1494,9 @@ bool smooth(ppe_solver* s, Level& L, const double* b, const double* x_in, double
   const double* cur = x_in;
   int step = 1;
   if (cur == nullptr) {
-    if (first_done) {  // the restriction took the first step (restricted_first)
-      cur = dst_of(1);
-      step = 2;
+    if (taken > 0) {  // one by the restriction (restricted_first), two by k_advance_t
+      cur = dst_of(taken);
+      step = taken + 1;
     } else if (deg >= 2 && L.fuse0) {
       double* dst = dst_of(2);
       apply_op<E_CHEB0, M>(s, L, nullptr, b, d, L.c1[0], L.c2[0], dst, nullptr, nullptr, 0,
@@ -1479,11 +1582,12 @@ FirstStep<M> first_step(ppe_solver* s, int l) {
 
 // One V-cycle with zero initial guess, x = M b on level l, matrix values in
 // type M (vectors FP64).  dot: see smooth (consumed by the last level-0
-// smoothing step, if any).  first_done: the restriction into level l has
-// taken its first smoothing step (restricted_first).
+// smoothing step, if any).  taken: the smoothing steps already taken on
+// level l, one by the restriction into it (restricted_first) or the finest level's
+// first two (k_advance_t).
 template <class M>
 bool vcycle_t(ppe_solver* s, int l, const double* b, double* x, const PcgDot* dot = nullptr,
-              bool first_done = false) {
+              int taken = 0) {
   Level& L = s->levels[l];
   const int n = L.n;
   if (n == 0) return false;
@@ -1502,20 +1606,20 @@ bool vcycle_t(ppe_solver* s, int l, const double* b, double* x, const PcgDot* do
   }
   if (l == s->nlev - 1) {
     double* t = L.r.as<double>();
-    smooth<M>(s, L, b, nullptr, t, xa, xb, nullptr, first_done);
+    smooth<M>(s, L, b, nullptr, t, xa, xb, nullptr, taken);
     return smooth<M>(s, L, b, t, x, xa, xb, dot);
   }
   Level& C = s->levels[l + 1];
   double* x1 = L.t.as<double>();  // pre-smoothed iterate, corrected in place
   double* r = L.r.as<double>();
-  smooth<M>(s, L, b, nullptr, x1, xa, xb, nullptr, first_done);
+  smooth<M>(s, L, b, nullptr, x1, xa, xb, nullptr, taken);
   apply_op<E_RESID, M>(s, L, x1, b, nullptr, 0.0, 0.0, r, nullptr);
   const bool first = C.n > 0 && restricted_first(s, l + 1);
   if (first)
     apply_rect<false, M, true>(s, L.R, r, C.b.as<double>(), L.lpr_r, first_step<M>(s, l + 1));
   else
     apply_rect<false, M>(s, L.R, r, C.b.as<double>(), L.lpr_r);
-  vcycle_t<M>(s, l + 1, C.b.as<double>(), C.x.as<double>(), nullptr, first);
+  vcycle_t<M>(s, l + 1, C.b.as<double>(), C.x.as<double>(), nullptr, first ? 1 : 0);
   if (prolong_fusable(s, L)) {
     // the first post-smoothing step writes xa (it is not the last step)
     prolong_cheb<M>(s, L, C.x.as<double>(), x1, r, L.d.as<double>(), xa);
@@ -1755,9 +1859,9 @@ void vcycle(ppe_solver* s, int l, const double* b, double* x) {
 
 // z = M r for PCG, with the dot r.z left as tile partials: fused into the
 // last level-0 smoothing step, else a separate pass.
-static void vcycle_pcg(ppe_solver* s, const double* r, double* z, const PcgDot& dot) {
-  const bool dotted = s->opt.precision == PPE_MIXED ? vcycle_t<float>(s, 0, r, z, &dot)
-                                                    : vcycle_t<double>(s, 0, r, z, &dot);
+static void vcycle_pcg(ppe_solver* s, const double* r, double* z, const PcgDot& dot, int taken) {
+  const bool dotted = s->opt.precision == PPE_MIXED ? vcycle_t<float>(s, 0, r, z, &dot, taken)
+                                                    : vcycle_t<double>(s, 0, r, z, &dot, taken);
   if (!dotted)
     launch(s, [&]() { return std::make_pair(std::string("k_dot_t"), 16.0 * s->n_active); },
            k_dot_t, dim3(dot.nt), dim3(kTileBlock), dot.T, r, (const double*)z, dot.part);
@@ -1851,11 +1955,15 @@ ppe_status pcg_solve(ppe_solver* s, const double* rhs, double* p_out, int use_x0
   }
   Level& L0 = s->levels[0];
   double* x = s->vx.get<double>(na);
-  double* r = s->vr.get<double>(na);
+  double* r = s->vr.get<double>(na);  // later in rb[slot]
   // z alternates between two buffers (one captured graph holds both)
   double* zb[2] = {s->vz.get<double>(na), s->vzold.get<double>(na)};
   // p alternates too: the fused pass reads the old one at every neighbour
   double* pb[2] = {s->vp.get<double>(na), s->vp2.get<double>(na)};
+  // and r, where the update and the first two smoothing steps run as one pass
+  const bool advance = !s->prof && na <= kFuseAdvance && s->nlev >= 2 && !one_product(s, 0) &&
+                       L0.fuse0 && !L0.c1.empty();
+  double* rb[2] = {r, advance ? s->vr2.get<double>(na) : r};
   double* q = s->vq.get<double>(na);
   double* b = s->vb.get<double>(na);
   double* tp = s->tpart.get<double>((size_t)T_N * nt);
@@ -1897,7 +2005,7 @@ ppe_status pcg_solve(ppe_solver* s, const double* rhs, double* p_out, int use_x0
   // tolerance.  The scatter and the statistics ride along in the same round
   // trip: when nothing restarts they are the final ones.
   bool fetched = false;
-  auto check_true = [&]() {
+  auto check_true = [&](int sl) {  // r in rb[sl] goes to rb[1 - sl]
     apply_op<E_RESID, double>(s, L0, x, b, nullptr, 0.0, 0.0, q, nullptr);
     hipLaunchKernelGGL(k_norm2_t, dim3(nt), dim3(kTileBlock), 0, s->stream, T, q, tpart(T_RT),
                        cnt);
@@ -1906,7 +2014,7 @@ ppe_status pcg_solve(ppe_solver* s, const double* rhs, double* p_out, int use_x0
                        sc, done, restart, cnt);
     PPE_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_copy_restart_t, dim3(nt), dim3(kTileBlock), 0, s->stream, T, restart, q,
-                       r);
+                       rb[sl], rb[1 - sl]);
     PPE_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_scatter, dim3(grid_for(nc)), dim3(kBlock), 0, s->stream, nc,
                        s->cid.as<int>(), comp, x, p_out);
@@ -1944,7 +2052,9 @@ ppe_status pcg_solve(ppe_solver* s, const double* rhs, double* p_out, int use_x0
 
   // Samples converged from the start (zero right-hand side, exact guess) are
   // left alone by every iteration, so the first check below finds them.
-  auto precondition = [&](int sl) { vcycle_pcg(s, r, zb[sl], PcgDot{T, nt, tpart(T_RZ)}); };
+  auto precondition = [&](int sl, const double* res, int taken) {
+    vcycle_pcg(s, res, zb[sl], PcgDot{T, nt, tpart(T_RZ)}, taken);
+  };
   // p = z + beta p from rz slot `from` and p buffer `from` into the other ones,
   // q = A p: one pass or two (always two while profiling: an operation at a
   // time).
@@ -1979,18 +2089,39 @@ ppe_status pcg_solve(ppe_solver* s, const double* rhs, double* p_out, int use_x0
 #undef PPE_DIRECTION
     PPE_LAUNCH_CHECK();
   };
-  precondition(1);
+  precondition(1, rb[0], 0);
   direction(1, zb[1], 0, 1);
   // One PCG iteration of every sample still running: x, r update; z = M r; the
   // convergence test, beta and p; q = A p.  Samples already converged are
   // left untouched by every kernel, so extra iterations change nothing.
   auto body = [&](int sl) {
-    // x, p, r, q in; x, r out
-    launch(s, [&]() { return std::make_pair(std::string("k_update_xr_t"), 48.0 * na); },
-           k_update_xr_t, dim3(nt), dim3(kTileBlock), T, (const int*)done, (const double*)rz[sl],
-           (const double*)tpart(T_PQ), (const double*)pb[sl], (const double*)q, x, r, tpart(T_RR),
-           cnt, cnt + 1);
-    precondition(sl);
+    if (advance) {
+      const double c0 = L0.inv_theta, c1 = L0.c1[0], c2 = L0.c2[0];
+      // the second step's iterate goes where smooth leaves it
+      double* y = L0.c1.size() == 1 ? L0.t.as<double>() : L0.d2.as<double>();
+      auto run = [&](auto value) {
+        using M = decltype(value);
+#define PPE_ADVANCE(WM_)                                                                        \
+  hipLaunchKernelGGL((k_advance_t<M, WM_>), dim3(nt), dim3(kTileBlock), 0, s->stream, T, done, \
+                     rz[sl], tpart(T_PQ), pb[sl], q, x, rb[sl], rb[1 - sl], tpart(T_RR), cnt,   \
+                     cnt + 1, na, L0.W, L0.ell_col.as<int>(), LevelData<M>::ell(L0),            \
+                     LevelData<M>::diag(L0), smooth_diag<M>(s, L0), c0, c1, c2,                 \
+                     L0.d.as<double>(), y)
+        PPE_ELL_WIDTH(L0.W, PPE_ADVANCE);
+#undef PPE_ADVANCE
+      };
+      if (s->opt.precision == PPE_MIXED) run(float{});
+      else run(double{});
+      PPE_LAUNCH_CHECK();
+      precondition(sl, rb[1 - sl], 2);
+    } else {
+      // x, p, r, q in; x, r out
+      launch(s, [&]() { return std::make_pair(std::string("k_update_xr_t"), 48.0 * na); },
+             k_update_xr_t, dim3(nt), dim3(kTileBlock), T, (const int*)done,
+             (const double*)rz[sl], (const double*)tpart(T_PQ), (const double*)pb[sl],
+             (const double*)q, x, r, tpart(T_RR), cnt, cnt + 1);
+      precondition(sl, r, 0);
+    }
     direction(sl, zb[sl], 1, 0);
   };
   // Two iterations (both rz slots) captured into a HIP graph once the system
@@ -2053,9 +2184,9 @@ ppe_status pcg_solve(ppe_solver* s, const double* rhs, double* p_out, int use_x0
       // everything converged at this check: the chunk behind it was a no-op
       npend = 0;
       it = c.it;
-      if (check_true() == 0) return finish(PPE_OK);
+      if (check_true(slot) == 0) return finish(PPE_OK);
       // restarted samples: z = M r_true, p = z (beta is 0 after a restart)
-      precondition(slot);
+      precondition(slot, rb[1 - slot], 0);
       direction(slot, zb[slot], 0, 0);
       slot = 1 - slot;
     }

@@ -227,6 +227,12 @@ def test_products_with_one_long_row(shape, links):
             if lvl == 0:
                 assert (np.diff(P.indptr).max() > 256) == (links == 1500)
             assert rel_max(P, lev.P) <= 3.4e-13, lvl
+    # and the solve on rows of these widths: the residual the oracle recomputes
+    b = rng.normal(size=m.n_cells)
+    b -= b.mean()
+    res = s.solve(to_dev(b, torch.float64))
+    assert res.status == 0
+    assert assembly.relative_residual(sy, b, res.p.cpu().numpy()) <= 1e-10
     s.close()
 
 
