@@ -540,13 +540,15 @@ __global__ void __launch_bounds__(kBlock) k_ap_merge_ell(
 // the undecided count after a guessed number of them; here a round is two
 // barriers and one compute unit's LDS reads, 0.1 us per 400 entries and pass.
 // So it pays up to about kMisEntries: 16^3 (2,816 rows of six slots, 13
-// rounds) takes 58 us in place of 30 dispatches and two or three round trips
-// (assembly 702 -> 639 us), while a level of 605 rows and 47 k entries took
+// rounds) took 58 us in place of 30 dispatches and two or three round trips
+// (assembly 702 -> 639 us), and takes 43 with the last nine rounds on the few
+// undecided nodes, while a level of 605 rows and 47 k entries took
 // 165 us here and takes 65 in dispatches.  LPR lanes per row; rows as slots
 // (rp NULL: W columns of slot k at k n, the row itself = none) or CSR with the
 // strong flags.
 constexpr int64_t kMisEntries = 20480;
 constexpr int kMisThreads = 1024;
+constexpr int kMisSmallRounds = 4;  // rounds over all rows before the few left go alone
 inline size_t mis_small_lds(int64_t n, int64_t entries, bool csr) {
   return (size_t)(16 * n + (csr ? 4 * (n + 1) : 0) + 2 * entries);
 }
@@ -598,7 +600,13 @@ __global__ void __launch_bounds__(kMisThreads) k_mis_small(
   };
   // every lane group runs the same trips, so that the shuffles see all lanes
   const int trips = (n + groups - 1) / groups;
-  for (;;) {
+  const bool slots = !rp && lpr == 1;
+  bool finish = false;
+  for (int round = 0;; ++round) {
+    if (slots && round == kMisSmallRounds) {
+      finish = true;
+      break;
+    }
     for (int q = 0; q < trips; ++q) {
       const int i = q * groups + t / lpr;
       const unsigned long long m = row_max(i < n ? i : n - 1, key);
@@ -621,6 +629,49 @@ __global__ void __launch_bounds__(kMisThreads) k_mis_small(
         und = 1;
     }
     if (!__syncthreads_or(und)) break;
+  }
+  if (finish) {
+    // the nodes left, eight lanes each, in place (as k_mis_finish_ell: a key is
+    // one 8-byte access, old or new); the one of the highest key among them
+    // decides in every pass
+    __shared__ int num;
+    unsigned short* list = reinterpret_cast<unsigned short*>(m1);
+    if (t == 0) num = 0;
+    __syncthreads();
+    for (int i = t; i < n; i += kMisThreads)
+      if ((key[i] >> 62) == S_UND) list[atomicAdd(&num, 1)] = (unsigned short)i;
+    __syncthreads();
+    for (;;) {
+      int und = 0;
+      for (int e0 = 0; e0 < num; e0 += kMisThreads / 8) {
+        const int e = e0 + t / 8, l = t % 8, i = e < num ? list[e] : 0;
+        const unsigned long long own = key[i];
+        const bool on = e < num && (own >> 62) == S_UND;
+        unsigned long long m = own;
+        if (on)
+          for (int k = l; k < W; k += 8) {
+            const int j = col[k * n + i];
+            m = key[j] > m ? key[j] : m;
+            for (int q = 0; q < W; ++q) {
+              const unsigned long long x = key[col[q * n + j]];
+              m = x > m ? x : m;
+            }
+          }
+        for (int o = 4; o > 0; o >>= 1) {
+          const unsigned long long x = __shfl_xor(m, o, kWave);
+          m = x > m ? x : m;
+        }
+        if (!on || l != 0) continue;
+        const unsigned long long low = own & ((1ull << 62) - 1ull);
+        if (m == own)
+          key[i] = ((unsigned long long)S_IN << 62) | low;
+        else if ((m >> 62) == S_IN)
+          key[i] = low;  // S_OUT
+        else
+          und = 1;
+      }
+      if (!__syncthreads_or(und)) break;
+    }
   }
   // states out; roots numbered in row order (each thread a run of rows)
   const int per = (n + kMisThreads - 1) / kMisThreads, i0 = t * per, i1 = min(n, i0 + per);
