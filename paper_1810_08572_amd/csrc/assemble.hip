@@ -488,7 +488,7 @@ void check_segments(ppe_solver* s, const std::vector<int>& off) {
   int* d_off = s->tmp_i[0].get<int>(ns + 1);
   PPE_HIP(hipMemcpyAsync(d_off, off.data(), sizeof(int) * (ns + 1), hipMemcpyHostToDevice,
                          s->stream));
-  int* flag = s->flag.get<int>(4);
+  int* flag = s->flag.get<int>(kFlagWords);
   fill_int(s, flag, 0, 1);
   if (s->n_faces) {
     hipLaunchKernelGGL(k_check_segments, dim3(grid_for(s->n_faces)), dim3(kBlock), 0, s->stream,
@@ -506,7 +506,7 @@ void build_topology(ppe_solver* s, const int32_t* owner, const int32_t* neigh) {
     PPE_HIP(hipMemcpyAsync(o, owner, sizeof(int) * nf, hipMemcpyDeviceToDevice, s->stream));
     PPE_HIP(hipMemcpyAsync(nb, neigh, sizeof(int) * nf, hipMemcpyDeviceToDevice, s->stream));
   }
-  int* flag = s->flag.get<int>(1);
+  int* flag = s->flag.get<int>(kFlagWords);
   fill_int(s, flag, 0, 1);
   if (nf) {
     hipLaunchKernelGGL(k_check_faces, dim3(grid_for(nf)), dim3(kBlock), 0, s->stream, o, nb, nf, nc,
@@ -555,7 +555,7 @@ __global__ void k_same_system(const double* __restrict__ coeff, const double* __
 
 bool same_system(ppe_solver* s, const double* coeff, const double* fl) {
   const int nc = s->n_cells, nf = s->n_faces;
-  int* flag = s->flag.get<int>(1);
+  int* flag = s->flag.get<int>(kFlagWords);
   fill_int(s, flag, 0, 1);
   const int g = grid_for(nf > nc ? nf : nc);
   hipLaunchKernelGGL(k_check_fields, dim3(g), dim3(kBlock), 0, s->stream, coeff, s->neigh.as<int>(),
@@ -574,7 +574,7 @@ bool same_system(ppe_solver* s, const double* coeff, const double* fl) {
 void assemble_fine(ppe_solver* s, const double* coeff, const double* fl, const double* shift) {
   const int nc = s->n_cells, nf = s->n_faces, ns = s->n_seg;
   s->shifted = shift != nullptr;
-  int* flag = s->flag.get<int>(1);
+  int* flag = s->flag.get<int>(kFlagWords);
   fill_int(s, flag, 0, 2);  // the checks' bits, the trees of the component search
   int g = grid_for(nf > nc ? nf : nc);
   hipLaunchKernelGGL(k_check_fields, dim3(g), dim3(kBlock), 0, s->stream, coeff, s->neigh.as<int>(),
@@ -704,7 +704,7 @@ void refresh_fine_shift(ppe_solver* s, const double* coeff, const double* shift)
   L.ap_ok = false;  // the kept A P no longer matches the new diagonal
   const int na = s->n_active;
   if (na == 0) return;
-  int* flag = s->flag.get<int>(1);
+  int* flag = s->flag.get<int>(kFlagWords);
   fill_int(s, flag, 0, 1);
   hipLaunchKernelGGL(k_refresh_diag, dim3(grid_for(na)), dim3(kBlock), 0, s->stream,
                      s->perm.as<int>(), na, s->adj_ptr.as<int>(), s->adj_nbr.as<int>(),

@@ -381,6 +381,9 @@ __device__ __forceinline__ T block_max(T v) {
 // and value; a consumer kernel sums those partials in a fixed order at the
 // start of every block, so all blocks see the same bitwise result.
 constexpr int kRedBlocks = 1024;
+// words of a solver's or a time-step driver's flag block: every pass that takes
+// it uses some of them
+constexpr int kFlagWords = 4;
 
 // Workgroups are dispatched round-robin over the eight XCDs (block b runs on
 // XCD b mod 8), and each XCD has its own L2.  The finest level's ELL kernels,

@@ -795,7 +795,7 @@ void set_geometry(ppe_solver* s, int n_nodes, const double* nodes, const int32_t
   }
   PPE_HIP(hipMemcpyAsync(cnodes, cell_nodes, sizeof(int) * 8 * nc, hipMemcpyDeviceToDevice,
                          s->stream));
-  int* flag = s->flag.get<int>(4);
+  int* flag = s->flag.get<int>(kFlagWords);
   fill_int(s, flag, 0, 1);
   // vertex -> cells
   int* vcnt = s->tmp_i[0].get<int>(n_nodes + 1);

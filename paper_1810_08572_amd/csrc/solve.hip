@@ -1971,7 +1971,7 @@ ppe_status pcg_solve(ppe_solver* s, const double* rhs, double* p_out, int use_x0
   int* done = s->seg_done.get<int>(3 * (size_t)ns);
   int* iters = done + ns;
   int* restart = done + 2 * ns;
-  int* cnt = s->flag.get<int>(4);  // [0] active segments, [1] error bits
+  int* cnt = s->flag.get<int>(kFlagWords);  // [0] active segments, [1] error bits
   const int* tab = s->tile_tab.as<int>();
   const Tiles T{tab, tab + nt, tab + 2 * (size_t)nt, tab + 3 * (size_t)nt};
   auto tpart = [&](int k) { return tp + (size_t)k * nt; };

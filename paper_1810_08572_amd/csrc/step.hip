@@ -540,7 +540,7 @@ ppe_status ppe_flow_set_mesh(ppe_flow* f, int32_t n_cells, int32_t n_faces, cons
     if (nf)
       PPE_HIP(hipMemcpyAsync(Xf, face_centre, sizeof(double) * 3 * nf, hipMemcpyDeviceToDevice,
                              f->stream));
-    int* flag = f->flag.get<int>(4);
+    int* flag = f->flag.get<int>(kFlagWords);
     fill_int(s, flag, 0, 1);
     double* cgeo = f->cgeo.get<double>(nf > 0 ? nf : 1);
     double* wgeo = f->wgeo.get<double>(nf > 0 ? nf : 1);
@@ -628,7 +628,7 @@ ppe_status ppe_flow_step(ppe_flow* f, const ppe_alloy* al, const ppe_step_params
     PPE_HIP(hipMemcpyAsync(u_n, u, sizeof(double) * 3 * nc, hipMemcpyDeviceToDevice, f->stream));
     PPE_HIP(hipMemcpyAsync(T_n, T, sizeof(double) * nc, hipMemcpyDeviceToDevice, f->stream));
     PPE_HIP(hipMemcpyAsync(fs_n, fs, sizeof(double) * nc, hipMemcpyDeviceToDevice, f->stream));
-    int* counts = f->flag.get<int>(4);
+    int* counts = f->flag.get<int>(kFlagWords);
     fill_int(s, counts, 0, 2);
     hipLaunchKernelGGL(k_count_fluid, dim3(gc), dim3(kBlock), 0, f->stream, nc, fs_n, counts);
     PPE_LAUNCH_CHECK();

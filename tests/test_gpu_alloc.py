@@ -1,0 +1,116 @@
+"""Device memory from a caller's allocator that promises no more than it was
+asked for: blocks cut to the byte from one arena, filled gaps between them.
+Whatever the library runs, no gap is written."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import paper_1810_08572_amd as ppe
+from synth import al_alloy, box_mesh, face_coeff, fl_linear_x, rhs_uniform, t_wall_layer
+from tests.gpu_util import to_dev, torch_dev
+
+pytestmark = pytest.mark.gpu
+
+FILL, GAP, ALIGN = 0xA5, 256, 256
+
+
+class Arena:
+    """Blocks of exactly the bytes asked for, never handed out twice."""
+
+    def __init__(self, size):
+        import torch
+
+        self.mem = torch.full((size,), FILL, dtype=torch.uint8, device=torch_dev())
+        self.base, self.size, self.at = self.mem.data_ptr(), size, 0
+        self.blocks = []  # (offset, bytes)
+
+        def _alloc(nbytes, stream, ctx):
+            if self.at + nbytes + GAP > self.size:
+                return None
+            at = self.at
+            self.blocks.append((at, int(nbytes)))
+            self.at = (at + nbytes + GAP + ALIGN - 1) // ALIGN * ALIGN
+            return self.base + at
+
+        self._alloc = ppe.ALLOC_FN(_alloc)
+        self._free = ppe.FREE_FN(lambda ptr, ctx: None)
+
+    def install(self, o):
+        o.alloc = ctypes.cast(self._alloc, ctypes.c_void_p)
+        o.free = ctypes.cast(self._free, ctypes.c_void_p)
+        o.alloc_ctx = None
+
+    def check(self):
+        """Every byte outside the blocks still holds the fill value."""
+        import torch
+
+        torch.cuda.synchronize()
+        h = self.mem[:self.at + GAP].cpu().numpy()
+        free = np.ones(h.size, dtype=bool)
+        for at, n in self.blocks:
+            free[at:at + n] = False
+        bad = np.nonzero(free & (h != FILL))[0]
+        if bad.size:
+            before = [b for b in self.blocks if b[0] <= bad[0]][-1]
+            raise AssertionError(f"{bad.size} bytes written outside their blocks, the first "
+                                 f"{bad[0] - before[0]} bytes into a block of {before[1]}")
+        assert len(self.blocks) > 20
+
+
+def _f64(*arrays):
+    import torch
+
+    return [to_dev(a, torch.float64) for a in arrays]
+
+
+# 44^3 cells: past the limits below which the component search and the scans
+# take their short forms
+@pytest.mark.parametrize("shape,opts", [
+    ((10, 9, 8), {}), ((16, 14, 12), {"coarse_max": 8, "autotune": True}),
+    ((20, 16, 18), {"precision": "mixed"}), ((24, 20, 22), {"smoother": "l1jacobi"}),
+    ((24, 20, 22), {"coarse_reuse": 2}), ((44, 44, 44), {})])
+def test_solver_writes_stay_in_their_blocks(shape, opts):
+    import torch
+
+    arena = Arena(1 << 29)
+    m = box_mesh(shape, jitter=0.1, seed=1, mode="node")
+    c = face_coeff(m, 2400.0)
+    s = ppe.Solver(allocator=arena, **opts)
+    s.set_mesh(m.n_cells, to_dev(m.owner, torch.int32), to_dev(m.neigh, torch.int32))
+    cd, = _f64(c)
+    for x0 in (0.3, 0.35):
+        fl = fl_linear_x(m.cell_centre, x0=x0)
+        b, f = _f64(rhs_uniform(m.n_cells, seed=1, center_mask=fl > 0), fl)
+        s.assemble(cd, f)
+        for _ in range(5):  # with captured iterations
+            p = s.solve(b).p
+        s.solve(b, x0=p)
+    arena.check()
+    s.set_geometry(to_dev(m.nodes, torch.float64), to_dev(m.extra["face_nodes"], torch.int32),
+                   to_dev(m.extra["cell_nodes"], torch.int32), *_f64(m.cell_centre, m.face_area))
+    u = np.random.default_rng(2).normal(size=(m.n_cells, 3))
+    s.project(cd, *_f64(u), 2400.0, 1e-3)
+    shift, = _f64(np.full(m.n_cells, float(np.median(c))))
+    s.assemble_shifted(cd, shift)
+    s.solve(b)
+    s.refresh_shift(cd, shift)
+    s.solve(b)
+    arena.check()
+
+
+@pytest.mark.parametrize("shape", [(8, 7, 6), (20, 16, 18)])
+def test_time_step_writes_stay_in_their_blocks(shape):
+    import torch
+
+    arena = Arena(1 << 29)
+    m = box_mesh(shape, jitter=0.0, seed=1, lengths=tuple(0.01 * k / max(shape) for k in shape))
+    fw = ppe.Flow(allocator=arena)
+    fw.set_mesh(to_dev(m.owner, torch.int32), to_dev(m.neigh, torch.int32), *_f64(m.nodes),
+                to_dev(m.extra["face_nodes"], torch.int32),
+                to_dev(m.extra["cell_nodes"], torch.int32),
+                *_f64(m.cell_centre, m.face_area, m.face_centre, m.cell_volume))
+    props = al_alloy(T_wall=600.0, T_ref=950.0)
+    T, = _f64(t_wall_layer(m, 600.0, 950.0, 0.0008))
+    fw.run(props, fw.new_state(T, props=props), 1e-3, 2)
+    arena.check()
