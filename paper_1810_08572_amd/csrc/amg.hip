@@ -549,6 +549,9 @@ __global__ void __launch_bounds__(kBlock) k_ap_merge_ell(
 constexpr int64_t kMisEntries = 20480;
 constexpr int kMisThreads = 1024;
 constexpr int kMisSmallRounds = 4;  // rounds over all rows before the few left go alone
+// What the kernel takes of a workgroup's LDS beside mis_small_lds: the
+// wavefronts' sums and what the voting barriers use (328 bytes as built).
+constexpr size_t kMisStatic = 1024;
 inline size_t mis_small_lds(int64_t n, int64_t entries, bool csr) {
   return (size_t)(16 * n + (csr ? 4 * (n + 1) : 0) + 2 * entries);
 }
@@ -2531,7 +2534,7 @@ void build_hierarchy(ppe_solver* s) {
       long long n_roots = 0;
       const int64_t entries = ell ? (int64_t)W * n : L.A.nnz;
       const size_t lds = mis_small_lds(n, entries, !ell);
-      if (n <= 0xFFFF && entries <= kMisEntries && lds + 256 <= s->lds_max) {
+      if (n <= 0xFFFF && entries <= kMisEntries && lds + kMisStatic <= s->lds_max) {
         int l1 = 1;  // lanes per row: no more than fill the workgroup
         while (l1 < 16 && 2 * l1 * n <= kMisThreads) l1 *= 2;
         long long* total = s->tmp_l[0].get<long long>(2);

@@ -263,3 +263,25 @@ def test_hierarchy_after_another_mesh_on_the_same_solver():
         z = s.apply_vcycle(to_dev(r, torch.float64)).cpu().numpy()
         assert np.linalg.norm(z - amg.vcycle(H, r)) <= 1e-12 * np.linalg.norm(z)
     s.close()
+
+
+@pytest.mark.parametrize("cells", [8124, 8140, 8177, 8179, 8192])
+def test_hierarchy_of_a_chain_that_fills_lds(cells):
+    """MIS-2 of a small level in one workgroup takes 20 bytes of LDS per cell
+    of a chain beside the kernel's own: the longest chain that does, and the
+    lengths around the limit of 160 KB without and with the latter."""
+    import torch
+
+    import paper_1810_08572_amd as ppe
+
+    m = box_mesh((cells, 1, 1), jitter=0.1, seed=2)
+    f, c = np.ones(m.n_cells), face_coeff(m, 2400.0)
+    sy = assembly.masked_system(m.n_cells, m.owner, m.neigh, c, f)
+    H = amg.build_hierarchy(sy.A)
+    s = ppe.Solver()
+    s.set_mesh(m.n_cells, to_dev(m.owner, torch.int32), to_dev(m.neigh, torch.int32))
+    s.assemble(to_dev(c, torch.float64), to_dev(f, torch.float64))
+    assert s.n_levels() == len(H.levels)
+    for lvl, lev in enumerate(H.levels[:-1]):
+        assert np.array_equal(s.aggregates(lvl).cpu().numpy(), lev.agg), lvl
+    s.close()
