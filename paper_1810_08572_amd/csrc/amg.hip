@@ -635,10 +635,16 @@ __global__ void __launch_bounds__(kMisThreads) k_mis_small(
   }
   if (finish) {
     // the nodes left, eight lanes each, in place (as k_mis_finish_ell: a key is
-    // one 8-byte access, old or new); the one of the highest key among them
-    // decides in every pass
+    // read by one relaxed access, old or new); the one of the highest key among
+    // them decides in every pass
     __shared__ int num;
     unsigned short* list = reinterpret_cast<unsigned short*>(m1);
+    auto key_of = [&](int j) {
+      return __hip_atomic_load(key + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    auto decide_key = [&](int i, unsigned long long k) {
+      __hip_atomic_store(key + i, k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
     if (t == 0) num = 0;
     __syncthreads();
     for (int i = t; i < n; i += kMisThreads)
@@ -648,15 +654,16 @@ __global__ void __launch_bounds__(kMisThreads) k_mis_small(
       int und = 0;
       for (int e0 = 0; e0 < num; e0 += kMisThreads / 8) {
         const int e = e0 + t / 8, l = t % 8, i = e < num ? list[e] : 0;
-        const unsigned long long own = key[i];
+        const unsigned long long own = key_of(i);
         const bool on = e < num && (own >> 62) == S_UND;
         unsigned long long m = own;
         if (on)
           for (int k = l; k < W; k += 8) {
             const int j = col[k * n + i];
-            m = key[j] > m ? key[j] : m;
+            const unsigned long long kj = key_of(j);
+            m = kj > m ? kj : m;
             for (int q = 0; q < W; ++q) {
-              const unsigned long long x = key[col[q * n + j]];
+              const unsigned long long x = key_of(col[q * n + j]);
               m = x > m ? x : m;
             }
           }
@@ -667,9 +674,9 @@ __global__ void __launch_bounds__(kMisThreads) k_mis_small(
         if (!on || l != 0) continue;
         const unsigned long long low = own & ((1ull << 62) - 1ull);
         if (m == own)
-          key[i] = ((unsigned long long)S_IN << 62) | low;
+          decide_key(i, ((unsigned long long)S_IN << 62) | low);
         else if ((m >> 62) == S_IN)
-          key[i] = low;  // S_OUT
+          decide_key(i, low);  // S_OUT
         else
           und = 1;
       }
