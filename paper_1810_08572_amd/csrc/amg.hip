@@ -1252,6 +1252,10 @@ constexpr int kSpWaves = 4;  // wavefronts per block
 // keeps eight blocks per compute unit in LDS.
 constexpr int kSpCap = 128, kSpCapFew = 256;
 constexpr int kSpFewRows = 16384;
+// Entries of scratch (12 bytes each) beyond which the two passes, which need
+// none, are taken: 3 GB, about one percent of the device's memory, reached with
+// two million coarse rows.  They are also taken where less is not to be had.
+constexpr int64_t kSpScratch = int64_t(1) << 28;
 // Lanes' worth of products above which a row is shared by the block's
 // wavefronts: 11.6 k rows of 84 entries x 32 lanes take 151 us with one and 106
 // with four, 13.8 k rows of 39 entries x 16 lanes 40 with one and 53 with four.
@@ -2033,8 +2037,8 @@ static void spgemm_launch(ppe_solver* s, const SpConfig& c, const Csr& A, const 
 // to fill a quarter of them) take one pass with a slot per column into
 // fixed-stride scratch rows and a compaction; wider ones one pass of
 // k_spgemm_wave into such rows, unless a row turns out longer than they are.
-// Then, and where the scratch could not be indexed with 32 bits, two
-// passes count each row's distinct columns with a hash sized from the
+// Then, and where the scratch would be large or cannot be had, two passes
+// count each row's distinct columns with a hash sized from the
 // product bound (or a bit per column of C when that is smaller), then fill
 // C with a hash sized from the largest count.  The
 // product bound is maxrow(A) maxrow(B) when both are known on the host, else
@@ -2094,10 +2098,11 @@ void spgemm(ppe_solver* s, const Csr& A, const Csr& B, Csr& C, int* flag, const 
   const bool few = C.n <= kSpFewRows;
   int wcap = 16;
   while (wcap < ub && wcap < (few ? kSpCapFew : kSpCap)) wcap *= 2;
-  if ((int64_t)C.n * wcap <= INT32_MAX) {
-    const size_t cap = (size_t)C.n * wcap;
-    int* sci = s->sp_ci.get<int>(cap);
-    double* sv = s->sp_v.get<double>(cap);
+  const int64_t cap = (int64_t)C.n * wcap;
+  int* sci = cap <= kSpScratch ? s->sp_ci.try_get<int>(cap) : nullptr;
+  double* sv = sci ? s->sp_v.try_get<double>(cap) : nullptr;
+  if (sci && !sv) s->sp_ci.release();
+  if (sv) {
     int hshift = 32;
     for (int h = 2 * wcap; h > 1; h /= 2) --hshift;
     const int lpr = lanes_for(B), W = mean_a * lpr > kSpSplit ? kSpWaves : 1, per = kSpWaves / W;

@@ -127,6 +127,18 @@ struct DevBuf {
     }
     return static_cast<T*>(p);
   }
+  // The same, or NULL (and no block held) where the memory is not to be had:
+  // for a workspace that the caller can do without.
+  template <class T>
+  T* try_get(size_t n) {
+    try {
+      return get<T>(n);
+    } catch (const Error& e) {
+      if (e.status != PPE_ERR_OOM) throw;
+      (void)hipGetLastError();
+      return nullptr;
+    }
+  }
   template <class T>
   T* as() const { return static_cast<T*>(p); }
 };
