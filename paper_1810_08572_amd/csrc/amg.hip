@@ -1238,7 +1238,10 @@ __global__ void __launch_bounds__(1024) k_spgemm_rows(
 // order of A's row, the wavefronts' sums in theirs, whatever the timing.  The
 // row is written sorted by column to the scratch row at i cap, and counts[i] =
 // its length; a row of more than cap columns sets *over and the host takes the
-// two passes of k_spgemm_rows.
+// two passes of k_spgemm_rows (a wavefront stops after its first column without
+// a slot: for every later product it would probe all of a full table, which made
+// the set-up of 100^3 cells with a shift, 22.5 k rows of 279 columns in 256
+// slots, 14.7 ms; 8.5 so, and 7.2 where the host foresees it).
 // It replaces a counting pass with a table of the product bound and a filling
 // one with a value array per sub-group, whose initialisation, merging and
 // probing were most of their LDS traffic.  R (A P) of a 128^3 system's finest
@@ -1256,6 +1259,13 @@ constexpr int kSpFewRows = 16384;
 // none, are taken: 3 GB, about one percent of the device's memory, reached with
 // two million coarse rows.  They are also taken where less is not to be had.
 constexpr int64_t kSpScratch = int64_t(1) << 28;
+// A row of C is a union of rows of B that overlap: in hierarchies of boxes,
+// plates and beams its longest row held 1.6 to 4.6 times as many columns as B's
+// longest one (R A P of shifted systems' second level 3.6 to 4.6, with rows up to
+// 514).  Where kSpUnion times B's longest row passes the scratch row, the pass
+// would in all likelihood only be found too short, so the two passes are taken
+// at once.
+constexpr int kSpUnion = 4;
 // Lanes' worth of products above which a row is shared by the block's
 // wavefronts: 11.6 k rows of 84 entries x 32 lanes take 151 us with one and 106
 // with four, 13.8 k rows of 39 entries x 16 lanes 40 with one and 53 with four.
@@ -1304,7 +1314,7 @@ __global__ void __launch_bounds__(kSpWaves* kWave) k_spgemm_wave(
     if (key >= 0) {
       int prev = atomicCAS(&keys[q], -1, key);
       for (int probes = 0; prev != -1 && prev != key; ++probes) {
-        if (probes == H) {
+        if (probes == cap) {
           full = true;
           break;
         }
@@ -1335,6 +1345,7 @@ __global__ void __launch_bounds__(kSpWaves* kWave) k_spgemm_wave(
     staged[lane] = mineA;
     wave_lds_fence();
     for (int e = 0; e < len; e += S * kSpBatch) {
+      if (__any(full)) break;
       int b0[kSpBatch], b1[kSpBatch], kk[kSpBatch], qq[kSpBatch];
       double xx[kSpBatch], yy[kSpBatch];
 #pragma unroll
@@ -2037,8 +2048,8 @@ static void spgemm_launch(ppe_solver* s, const SpConfig& c, const Csr& A, const 
 // to fill a quarter of them) take one pass with a slot per column into
 // fixed-stride scratch rows and a compaction; wider ones one pass of
 // k_spgemm_wave into such rows, unless a row turns out longer than they are.
-// Then, and where the scratch would be large or cannot be had, two passes
-// count each row's distinct columns with a hash sized from the
+// Then, and where that is likely, or the scratch would be large or cannot be
+// had, two passes count each row's distinct columns with a hash sized from the
 // product bound (or a bit per column of C when that is smaller), then fill
 // C with a hash sized from the largest count.  The
 // product bound is maxrow(A) maxrow(B) when both are known on the host, else
@@ -2099,7 +2110,8 @@ void spgemm(ppe_solver* s, const Csr& A, const Csr& B, Csr& C, int* flag, const 
   int wcap = 16;
   while (wcap < ub && wcap < (few ? kSpCapFew : kSpCap)) wcap *= 2;
   const int64_t cap = (int64_t)C.n * wcap;
-  int* sci = cap <= kSpScratch ? s->sp_ci.try_get<int>(cap) : nullptr;
+  const bool fits = (int64_t)std::min<int64_t>(ub, (int64_t)kSpUnion * B.maxrow) <= wcap;
+  int* sci = fits && cap <= kSpScratch ? s->sp_ci.try_get<int>(cap) : nullptr;
   double* sv = sci ? s->sp_v.try_get<double>(cap) : nullptr;
   if (sci && !sv) s->sp_ci.release();
   if (sv) {

@@ -285,3 +285,29 @@ def test_hierarchy_of_a_chain_that_fills_lds(cells):
     for lvl, lev in enumerate(H.levels[:-1]):
         assert np.array_equal(s.aggregates(lvl).cpu().numpy(), lev.agg), lvl
     s.close()
+
+
+def test_products_whose_rows_outgrow_the_scratch():
+    """A beam's second level has rows of 300 to 500 columns throughout: its
+    R A P is formed in two passes at once, which the longest row of A P (four
+    times as many columns pass the 256 of a scratch row) gives away."""
+    import torch
+
+    import paper_1810_08572_amd as ppe
+
+    m = box_mesh((200, 20, 10), jitter=0.1, seed=1)
+    f, c = np.ones(m.n_cells), face_coeff(m, 2400.0)
+    sy = assembly.masked_system(m.n_cells, m.owner, m.neigh, c, f)
+    H = amg.build_hierarchy(sy.A, coarse_max=100)
+    AP = (H.levels[1].A @ H.levels[1].P).tocsr()
+    assert H.levels[2].A.shape[0] > 512 and 4 * np.diff(AP.indptr).max() > 256
+    assert np.median(np.diff(H.levels[2].A.tocsr().indptr)) > 256
+    s = ppe.Solver(coarse_max=100)
+    s.set_mesh(m.n_cells, to_dev(m.owner, torch.int32), to_dev(m.neigh, torch.int32))
+    s.assemble(to_dev(c, torch.float64), to_dev(f, torch.float64))
+    assert s.n_levels() == len(H.levels)
+    for lvl, lev in enumerate(H.levels):
+        A = csr(*s.level_matrix(lvl), lev.A.shape)
+        # as test_hierarchy_matches_oracle: summation order only
+        assert A.nnz == lev.A.nnz and rel_max(A, lev.A) <= 1e-13, lvl
+    s.close()
