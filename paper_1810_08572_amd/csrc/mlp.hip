@@ -477,7 +477,16 @@ __global__ void __launch_bounds__(64 * kWaves) k_mlp_infer_bf16(
 // the output layer is an FP32 dot product with the last BF16 activations.
 // SiLU uses the hardware exp2 and reciprocal (about 1 ulp of FP32 each,
 // far below the BF16 rounding that follows).
-constexpr int kWavesM = 12;  // waves per workgroup, one workgroup per compute unit
+// Waves of a workgroup, one workgroup per compute unit.  A wave's tiles are its
+// rounds, and a round of twelve waves takes 4/3 of one of eight (two mid layers
+// and one: 14.0 and 10.3 us, three: 19.3 and 14.6), so twelve run where that
+// makes up for itself in fewer rounds: 80 k cells and four hidden layers 40 us
+// with twelve and 49 with eight, 100 k 58 and 49, 600 k 154 and 163.
+constexpr int kWavesM = 12, kWavesFew = 8;
+inline int infer_waves(int tiles, int cus) {
+  const auto rounds = [&](int waves) { return (tiles + cus * waves - 1) / (cus * waves); };
+  return 4 * rounds(kWavesM) < 3 * rounds(kWavesFew) ? kWavesM : kWavesFew;
+}
 
 __device__ __forceinline__ float silu_hw(float z) {
   const float e = __builtin_amdgcn_exp2f(-1.4426950408889634f * z);
@@ -556,9 +565,10 @@ __global__ void __launch_bounds__(64 * kWavesM) k_mlp_infer_mfma(
         xin[kt][v] = c < n && k < kIn ? x[(size_t)c * kIn + k] : 0.0f;
       }
   };
-  int tile = blockIdx.x * kWavesM + wv;
+  const int waves = blockDim.x / 64, all = gridDim.x * waves;
+  int tile = blockIdx.x * waves + wv;
   if (tile < ntile) fetch(tile);
-  for (; tile < ntile; tile += gridDim.x * kWavesM) {
+  for (; tile < ntile; tile += all) {
     const int c = tile * 32 + cell;
     // layer 1: B[k][cell] in three BF16 parts
     short4_t b1p[3][2];
@@ -574,7 +584,7 @@ __global__ void __launch_bounds__(64 * kWavesM) k_mlp_infer_mfma(
           xv = xv - bf2f(h);
         }
       }
-    if (tile + (int)gridDim.x * kWavesM < ntile) fetch(tile + gridDim.x * kWavesM);
+    if (tile + all < ntile) fetch(tile + all);
     float16_t acc[4];
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) {
@@ -1053,9 +1063,10 @@ ppe_status ppe_mlp_forward(ppe_mlp* m, int32_t n, const float* x, float* y, int 
       if (lds <= m->lds_max) {
         // one workgroup per compute unit holds the staged weights; waves
         // stride over the 32-cell tiles
-        int g = (tiles + kWavesM - 1) / kWavesM;
+        const int waves = infer_waves(tiles, m->cus);
+        int g = (tiles + waves - 1) / waves;
         if (g > m->cus) g = m->cus;
-        hipLaunchKernelGGL(k_mlp_infer_mfma, dim3(g), dim3(64 * kWavesM), lds, m->stream, n,
+        hipLaunchKernelGGL(k_mlp_infer_mfma, dim3(g), dim3(64 * waves), lds, m->stream, n,
                            n_mid, x, m->params.as<float>(), m->bf16.as<uint16_t>(), y);
       } else {  // deeper networks than the staged weights fit
         int g = (tiles + kWaves - 1) / kWaves;

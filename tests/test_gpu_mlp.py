@@ -114,6 +114,21 @@ def test_bf16_inference_depths(n, hidden):
     assert np.linalg.norm(y - ye) <= BF16_EMUL_RTOL * np.linalg.norm(ye)
 
 
+def test_bf16_inference_is_the_same_for_any_number_of_waves():
+    """A workgroup runs eight or twelve waves, whichever needs fewer rounds:
+    a cell's output does not depend on it, at and around the sizes where the
+    choice turns (32 cells x 256 compute units x 8 or 12 waves)."""
+    import torch
+
+    net, shapes, theta = _net(seed=6)
+    X = to_dev(np.random.default_rng(6).normal(size=(200000, 10)).astype(np.float32), torch.float32)
+    y = net.forward(X, bf16=True)
+    ye = _bf16_forward(theta, shapes, X[-3000:].cpu().numpy().astype(np.float64))
+    assert np.linalg.norm(y[-3000:].cpu().numpy() - ye) <= BF16_EMUL_RTOL * np.linalg.norm(ye)
+    for n in (257, 65536, 65537, 98304, 98305, 131073, 196609):
+        assert torch.equal(net.forward(X[:n].contiguous(), bf16=True), y[:n]), n
+
+
 def _bf16(a):
     """Round to the nearest BF16 (ties to even), returned as float64."""
     u = np.asarray(a, dtype=np.float32).view(np.uint32).astype(np.uint64)
