@@ -123,34 +123,36 @@ __device__ __forceinline__ bool vec4(const float* p, int ld) {
 
 // One layer over rows of a batch.  Forward (BACK = false): z = X W^T + b with
 // W [N][K]; z (if wanted) and silu(z) are stored.  Backward (BACK = true):
-// Z = (X W) silu'(Z) in place, W [K][N].  A workgroup takes 32 rows and 128
-// columns: 256 workgroups for 8,192 rows and a width up to 128, one per compute
-// unit, so its eight waves (16 rows and 32 columns each) are all there is to
-// cover the loads' and the epilogue's latency (four waves of 32 x 32: 11.5 us
-// for a width of 128, eight 9.6).
+// Z = (X W) silu'(Z) in place, W [K][N].  A workgroup takes ROWS rows and 4,096 /
+// ROWS columns.  32 x 128: 256 workgroups for 8,192 rows and a width up to 128,
+// one per compute unit, so its eight waves (16 rows and 32 columns each) are all
+// there is to cover the loads' and the epilogue's latency (four waves of 32 x 32:
+// 11.5 us for a width of 128, eight 9.6).  Narrower layers take taller tiles
+// (tile_rows), whose waves all have columns.
 // Operands of v_mfma_f32_16x16x4f32: lane l holds A[l % 16][l / 16] and
 // B[l / 16][l % 16]; accumulator r of lane l is C[4 (l / 16) + r][l % 16].
 typedef float float4_v __attribute__((ext_vector_type(4)));
 constexpr int kLayerT = 512;
-template <bool BACK>
+template <bool BACK, int ROWS>
 __global__ void __launch_bounds__(kLayerT) k_layer(int n, int N, int K,
                                                    const float* __restrict__ X,
                                                    const float* __restrict__ W,
                                                    const float* __restrict__ bias,
                                                    float* __restrict__ Z, float* __restrict__ H) {
+  constexpr int COLS = kTile * kTileN / ROWS, kAcross = COLS / 32;  // waves across
   // rows of X and (forward) of W are stored one word apart from a multiple of
   // the bank count: a tile's lanes read its rows at one depth
-  __shared__ float Xs[kTile][kTileK + 1];
-  __shared__ float Ws[kTileN * (kTileK + 1)];
+  __shared__ float Xs[ROWS][kTileK + 1];
+  __shared__ float Ws[COLS * (kTileK + 1)];
   const int t = threadIdx.x, lane = t % 64, wv = t / 64, c = lane % 16, kq = lane / 16;
-  const int64_t i0 = (int64_t)blockIdx.x * kTile;
-  const int iw = 16 * (wv / 4);                       // the wave's rows
-  const int j0 = blockIdx.y * kTileN, jw = 32 * (wv % 4);  // and columns
+  const int64_t i0 = (int64_t)blockIdx.x * ROWS;
+  const int iw = 16 * (wv / kAcross);                       // the wave's rows
+  const int j0 = blockIdx.y * COLS, jw = 32 * (wv % kAcross);  // and columns
   const bool live = j0 + jw < N;
-  const int rows = (int)min((int64_t)kTile, n - i0);
+  const int rows = (int)min((int64_t)ROWS, n - i0);
   const bool vx = vec4(X, K), vw = vec4(W, BACK ? N : K);
-  Staged<kTile, kTileK, kLayerT> xs;
-  Staged<BACK ? kTileK : kTileN, BACK ? kTileN : kTileK, kLayerT> ws;
+  Staged<ROWS, kTileK, kLayerT> xs;
+  Staged<BACK ? kTileK : COLS, BACK ? COLS : kTileK, kLayerT> ws;
   auto fetch = [&](int k0) {  // entries past the matrix are zeros
     const int kn = min(kTileK, K - k0);
     xs.fetch(X + i0 * K + k0, K, rows, kn, vx);
@@ -165,7 +167,7 @@ __global__ void __launch_bounds__(kLayerT) k_layer(int n, int N, int K,
     const int kn = min(kTileK, K - k0);
     __syncthreads();  // the last chunk's readers are done
     xs.put(&Xs[0][0], kTileK + 1);
-    ws.put(Ws, BACK ? kTileN : kTileK + 1);
+    ws.put(Ws, BACK ? COLS : kTileK + 1);
     __syncthreads();
     if (k0 + kTileK < K) fetch(k0 + kTileK);
     if (live) {
@@ -177,7 +179,7 @@ __global__ void __launch_bounds__(kLayerT) k_layer(int n, int N, int K,
 #pragma unroll
           for (int h = 0; h < 2; ++h) {
             const int j = jw + 16 * h + c;
-            const float b = BACK ? Ws[k * kTileN + j] : Ws[j * (kTileK + 1) + k];
+            const float b = BACK ? Ws[k * COLS + j] : Ws[j * (kTileK + 1) + k];
             acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc[h], 0, 0, 0);
           }
         }
@@ -842,6 +844,33 @@ ppe_status ws_features(ppe_solver* s, const double* dp_prev, const double* rhs,
   return PPE_OK;
 }
 
+// Rows of a layer's tile: as tall as its columns allow where the rows still give
+// every compute unit one (256 of them).  One million rows forward, 32 rows and as
+// below: width 1 235 and 87 us, three layers of 16 610 and 205, of 64 1,132 and
+// 593; 8,192 rows do not change (their tiles would leave compute units idle).
+int tile_rows(int n, int N) {
+  if (N <= 32 && n >= 128 * 256) return 128;
+  if (N <= 64 && n >= 64 * 256) return 64;
+  return kTile;
+}
+
+template <bool BACK>
+void layer(ppe_mlp* m, int n, int N, int K, const float* X, const float* W, const float* bias,
+           float* Z, float* H) {
+  const int rows = tile_rows(n, N), cols = kTile * kTileN / rows;
+  const dim3 grid((unsigned)((n + (int64_t)rows - 1) / rows), (N + cols - 1) / cols);
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(kLayerT), 0, m->stream, n, N, K, X, W, bias, Z, H);
+  };
+  if (rows == 128)
+    run(k_layer<BACK, 128>);
+  else if (rows == 64)
+    run(k_layer<BACK, 64>);
+  else
+    run(k_layer<BACK, kTile>);
+  PPE_LAUNCH_CHECK();
+}
+
 // The hidden layers of n rows: activations into m->act and, for the backward
 // pass, pre-activations into m->pre.  Returns the last hidden activations.
 const float* hidden_layers(ppe_mlp* m, int n, const float* x, bool keep_pre) {
@@ -851,12 +880,8 @@ const float* hidden_layers(ppe_mlp* m, int n, const float* x, bool keep_pre) {
   const float* P = m->params.as<float>();
   const float* h = x;
   for (int l = 0; l < m->n_hidden; ++l) {
-    const dim3 grid((unsigned)((n + (int64_t)kTile - 1) / kTile),
-                    (m->width + kTileN - 1) / kTileN);
-    hipLaunchKernelGGL(k_layer<false>, grid, dim3(kLayerT), 0, m->stream, n, m->width, m->dims[l], h,
-                       P + m->woff[l], P + m->boff[l], pre ? pre + l * len : nullptr,
-                       act + l * len);
-    PPE_LAUNCH_CHECK();
+    layer<false>(m, n, m->width, m->dims[l], h, P + m->woff[l], P + m->boff[l],
+                 pre ? pre + l * len : nullptr, act + l * len);
     h = act + l * len;
   }
   return h;
@@ -903,12 +928,8 @@ void loss_grad(ppe_mlp* m, int n, const float* x, const float* t, float* grad) {
   PPE_LAUNCH_CHECK();
   // pre[l] turns into the gradient of layer l's pre-activations, last to first
   for (int l = L - 1; l > 0; --l) {
-    const dim3 grid((unsigned)((n + (int64_t)kTile - 1) / kTile),
-                    (m->width + kTileN - 1) / kTileN);
-    hipLaunchKernelGGL(k_layer<true>, grid, dim3(kLayerT), 0, m->stream, n, m->width, m->width,
-                       pre + l * len, P + m->woff[l], (const float*)nullptr, pre + (l - 1) * len,
-                       (float*)nullptr);
-    PPE_LAUNCH_CHECK();
+    layer<true>(m, n, m->width, m->width, pre + l * len, P + m->woff[l], nullptr,
+                pre + (l - 1) * len, nullptr);
   }
   const int chunk = grad_chunk(m, n);
   const int nz = (int)(((int64_t)n + chunk - 1) / chunk);

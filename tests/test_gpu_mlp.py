@@ -83,6 +83,28 @@ def test_fp32_gradient_at_tile_edges(n, width, hidden):
     assert np.abs(y - y_ref).max() <= 1e-5 * max(1.0, np.abs(y_ref).max())
 
 
+# narrow layers take tiles of 64 and 128 rows from 16,384 and 32,768 rows on:
+# both sides of those lines and of the widths, ragged last tiles.  As above;
+# the oracle's sums over the rows are in FP64, ours in FP32 chunks of rows
+@pytest.mark.parametrize("n,width", [(16383, 64), (16385, 33), (16500, 64), (32767, 32),
+                                     (32769, 1), (33000, 32), (40001, 17), (32768, 65)])
+def test_fp32_narrow_layers(n, width):
+    import torch
+
+    net, shapes, theta = _net(seed=2, width=width, hidden=2)
+    rng = np.random.default_rng(n)
+    X = rng.normal(size=(n, 10)).astype(np.float32)
+    T = rng.normal(size=n).astype(np.float32)
+    Xd, Td = to_dev(X, torch.float32), to_dev(T, torch.float32)
+    y_ref, _, _ = omlp.forward(theta, shapes, X.astype(np.float64))
+    y = net.forward(Xd).cpu().numpy()
+    assert np.abs(y - y_ref).max() <= 1e-5 * max(1.0, np.abs(y_ref).max())
+    loss, g = net.loss_grad(Xd, Td)
+    l_ref, g_ref = omlp.loss_and_grad(theta, shapes, X.astype(np.float64), T.astype(np.float64))
+    assert abs(loss - l_ref) <= BWD_RTOL * l_ref
+    assert np.linalg.norm(g.cpu().numpy() - g_ref) <= BWD_RTOL * np.linalg.norm(g_ref)
+
+
 # 100003 cells: more 32-cell tiles than one launch's waves, so waves stride
 # over several tiles, with a ragged last tile
 @pytest.mark.parametrize("n", [1, 32, 1000, 12345, 100003])
