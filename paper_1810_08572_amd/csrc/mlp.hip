@@ -854,13 +854,22 @@ int tile_rows(int n, int N) {
   return kTile;
 }
 
+// Rows of one launch: a grid holds at most 2^32 threads along a dimension, and
+// 32 rows take 512.
+constexpr int kLayerRows = 1 << 27;
+
 template <bool BACK>
 void layer(ppe_mlp* m, int n, int N, int K, const float* X, const float* W, const float* bias,
            float* Z, float* H) {
   const int rows = tile_rows(n, N), cols = kTile * kTileN / rows;
-  const dim3 grid((unsigned)((n + (int64_t)rows - 1) / rows), (N + cols - 1) / cols);
   auto run = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, grid, dim3(kLayerT), 0, m->stream, n, N, K, X, W, bias, Z, H);
+    for (int64_t i = 0; i < n; i += kLayerRows) {
+      const int part = (int)std::min<int64_t>(n - i, kLayerRows);
+      const dim3 grid((unsigned)((part + (int64_t)rows - 1) / rows), (N + cols - 1) / cols);
+      hipLaunchKernelGGL(kernel, grid, dim3(kLayerT), 0, m->stream, part, N, K, X + i * K, W, bias,
+                         Z ? Z + i * N : nullptr, H ? H + i * N : nullptr);
+      PPE_LAUNCH_CHECK();
+    }
   };
   if (rows == 128)
     run(k_layer<BACK, 128>);
@@ -868,7 +877,6 @@ void layer(ppe_mlp* m, int n, int N, int K, const float* X, const float* W, cons
     run(k_layer<BACK, 64>);
   else
     run(k_layer<BACK, kTile>);
-  PPE_LAUNCH_CHECK();
 }
 
 // The hidden layers of n rows: activations into m->act and, for the backward

@@ -105,6 +105,31 @@ def test_fp32_narrow_layers(n, width):
     assert np.linalg.norm(g.cpu().numpy() - g_ref) <= BWD_RTOL * np.linalg.norm(g_ref)
 
 
+def test_fp32_more_rows_than_one_launch_holds():
+    """2^28 rows and a few: a layer's tiles are more than one grid takes (2^32
+    threads), so its rows go in parts of 2^27; checked at both ends and around
+    the parts' edges."""
+    import torch
+
+    import paper_1810_08572_amd as ppe
+
+    n = (1 << 28) + 7
+    shapes = omlp.layer_shapes(1, 33, 1)
+    theta = omlp.init_params(shapes, seed=8).astype(np.float32)
+    net = ppe.WarmStartNet(1, 33, 1)
+    net.set_params(to_dev(theta, torch.float32))
+    theta = theta.astype(np.float64)
+    X = torch.rand(n, 1, device=torch_dev(), generator=torch.Generator(torch_dev()).manual_seed(8))
+    y = net.forward(X)
+    for a in (0, (1 << 27) - 500, (1 << 28) - 500, n - 1000):
+        ref, _, _ = omlp.forward(theta, shapes, X[a:a + 1000].cpu().numpy().astype(np.float64))
+        err = np.abs(y[a:a + 1000].cpu().numpy() - ref).max()
+        assert err <= 1e-5 * max(1.0, np.abs(ref).max()), a
+    net.close()
+    del X, y
+    torch.cuda.empty_cache()
+
+
 # 100003 cells: more 32-cell tiles than one launch's waves, so waves stride
 # over several tiles, with a ragged last tile
 @pytest.mark.parametrize("n", [1, 32, 1000, 12345, 100003])
