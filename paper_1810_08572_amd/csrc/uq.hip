@@ -524,9 +524,11 @@ inline int wide_ld(int K) { return (K + kWideK - 1) / kWideK * kWideK; }
 inline int wide_rows(int R) { return (R + kWideRows - 1) / kWideRows * kWideRows; }
 
 // TILES: 16-row tiles of a workgroup (kRowTiles, or all of a smaller R's).
-// skip (may be NULL): C is left alone if it holds nonzero.
+// skip (may be NULL): C is left alone if it holds nonzero.  The first workgroup's
+// columns start at c0.
 template <int TILES>
 __global__ void __launch_bounds__(kBlock) k_small_times_wide(int R, int K, int lda, long long n,
+                                                             long long c0,
                                                              const double* __restrict__ A,
                                                              const double* __restrict__ B,
                                                              double* __restrict__ C,
@@ -536,7 +538,7 @@ __global__ void __launch_bounds__(kBlock) k_small_times_wide(int R, int K, int l
   constexpr int kA = 16 * TILES * kWideK / kBlock, kB = kWideK / 4;  // values per thread
   __shared__ double a[2][16 * TILES][kPitch];
   const int t = threadIdx.x, lane = t % kWave, i = lane % 16, kq = lane / 16;
-  const long long c = (long long)blockIdx.x * kWideCols + (t / kWave) * 16 + i;
+  const long long c = c0 + (long long)blockIdx.x * kWideCols + (t / kWave) * 16 + i;
   const int r0 = blockIdx.y * kWideRows;
   if (skip && *skip) return;
   const double* b0 = B + (c < n ? c : n - 1);  // columns past n repeat the last one, unstored
@@ -586,9 +588,11 @@ __global__ void __launch_bounds__(kBlock) k_small_times_wide(int R, int K, int l
 // A workgroup takes 64 outputs; its four waves take every fourth term each
 // (32,768 outputs alone would leave half the compute units without a
 // workgroup), and every coefficient is read once for all inputs: 7 us
-// at 56 terms and 3 inputs, 35 with a pass over the terms per input.
+// at 56 terms and 3 inputs, 35 with a pass over the terms per input.  The first
+// workgroup's outputs start at c0.
 template <int D>
 __global__ void __launch_bounds__(kBlock) k_pce_stats(int n_terms, int d, long long n,
+                                                      long long c0,
                                                       const double* __restrict__ W,
                                                       const int* __restrict__ mask,
                                                       double* __restrict__ mean,
@@ -599,7 +603,7 @@ __global__ void __launch_bounds__(kBlock) k_pce_stats(int n_terms, int d, long l
   __shared__ double part[kParts][kWave];
   const int lane = threadIdx.x % kWave;
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
-  const long long c = (long long)blockIdx.x * kWave + lane;
+  const long long c = c0 + (long long)blockIdx.x * kWave + lane;
   const double* col = W + (c < n ? c : n - 1);
   double v = 0.0, f[D], t[D];
 #pragma unroll
@@ -651,15 +655,22 @@ __global__ void __launch_bounds__(kBlock) k_pce_stats(int n_terms, int d, long l
   }
 }
 
+// Outputs of one launch: 64 of them take 256 threads, and a grid holds at most
+// 2^32 along a dimension.
+constexpr long long kOutPart = 1ll << 29;
+
 // C (R x n) = A (R x K) B (K x n), A padded as k_small_times_wide reads it.
 void small_times_wide(hipStream_t st, int R, int K, long long n, const double* A, const double* B,
                       double* C, const int* skip) {
   if (n == 0 || R == 0) return;
-  const long long gx = (n + kWideCols - 1) / kWideCols;
-  require(gx <= INT32_MAX, PPE_ERR_ARG, "too many outputs");
+  require((n + kBlock - 1) / kBlock <= INT32_MAX, PPE_ERR_ARG, "too many outputs");
   auto run = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3((unsigned)gx, (R + kWideRows - 1) / kWideRows), dim3(kBlock), 0,
-                       st, R, K, wide_ld(K), n, A, B, C, skip);
+    for (long long c0 = 0; c0 < n; c0 += kOutPart) {
+      const long long gx = (std::min(n - c0, kOutPart) + kWideCols - 1) / kWideCols;
+      hipLaunchKernelGGL(kernel, dim3((unsigned)gx, (R + kWideRows - 1) / kWideRows), dim3(kBlock),
+                         0, st, R, K, wide_ld(K), n, c0, A, B, C, skip);
+      PPE_LAUNCH_CHECK();
+    }
   };
   if (R <= 16)
     run(k_small_times_wide<1>);
@@ -669,7 +680,6 @@ void small_times_wide(hipStream_t st, int R, int K, long long n, const double* A
     run(k_small_times_wide<3>);
   else
     run(k_small_times_wide<kRowTiles>);
-  PPE_LAUNCH_CHECK();
 }
 
 // Queues P (K x M, rows of ldp) = R^-1 Q^T of V (M x K), both on the device;
@@ -901,17 +911,20 @@ ppe_status ppe_pce_stats(ppe_pce* q, int64_t n_out, const double* W, double* mea
     }
     int* md = q->mask_dev.get<int>(mask.size());
     PPE_HIP(hipMemcpyAsync(md, mask.data(), sizeof(int) * mask.size(), hipMemcpyHostToDevice, q->stream));
-    const long long g = (n_out + ppe::kWave - 1) / ppe::kWave;
-    require(g <= INT32_MAX, PPE_ERR_ARG, "too many outputs");
+    require((n_out + ppe::kBlock - 1) / ppe::kBlock <= INT32_MAX, PPE_ERR_ARG, "too many outputs");
     auto run = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, dim3((unsigned)g), dim3(ppe::kBlock), 0, q->stream, q->n_terms,
-                         q->d, (long long)n_out, W, md, mean, var, first, total);
+      for (long long c0 = 0; c0 < n_out; c0 += ppe::kOutPart) {
+        const long long g =
+            (std::min<long long>(n_out - c0, ppe::kOutPart) + ppe::kWave - 1) / ppe::kWave;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)g), dim3(ppe::kBlock), 0, q->stream, q->n_terms,
+                           q->d, (long long)n_out, c0, W, md, mean, var, first, total);
+        PPE_LAUNCH_CHECK();
+      }
     };
     if (q->d <= 4)
       run(ppe::k_pce_stats<4>);
     else
       run(ppe::k_pce_stats<16>);
-    PPE_LAUNCH_CHECK();
     PPE_HIP(hipStreamSynchronize(q->stream));
     return PPE_OK;
   });

@@ -183,3 +183,29 @@ def test_rank_deficient_fit_leaves_the_coefficients_alone():
     assert bool((W == 7.0).all())
     good = q.fit(q.nodes("tensor", 3)[0], to_dev(np.ones((27, 70)), torch.float64))
     assert abs(float(good[0, 0]) - 1.0) <= 1e-13
+
+
+def test_more_outputs_than_one_launch_holds():
+    """2^30 outputs and a few: more than one grid of the products and of the
+    statistics takes (2^32 threads), so they go in parts of 2^29.  One constant
+    term, so every result is its sample."""
+    import torch
+
+    import paper_1810_08572_amd as ppe
+
+    n = (1 << 30) + 5
+    q = ppe.PolynomialChaos(["uniform"], 0)
+    X = np.zeros((1, 1))
+    Y = torch.empty(1, n, dtype=torch.float64, device="cuda")
+    Y[0] = torch.arange(n, device="cuda", dtype=torch.int32)
+    W = q.fit(X, Y)
+    assert torch.equal(W, Y)
+    del Y
+    mean, var, first, total = q.stats(W)
+    assert torch.equal(mean, W[0])
+    assert not bool(var.any() or first.any() or total.any())
+    del mean, var, first, total
+    assert torch.equal(q.eval(X, W), W)
+    q.close()
+    del W
+    torch.cuda.empty_cache()
