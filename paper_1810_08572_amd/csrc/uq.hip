@@ -8,9 +8,10 @@
 // system V W = Y at M sample points (Eq. 28), for every output x at once.
 //
 // Host side (sizes of a few hundred): Gauss rules, tensor and Smolyak node
-// sets, the basis and V.  Device side: the projection P = R^-1 Q^T of a
-// Householder QR of V, W = P Y, the evaluation V_test W at test points, and
-// the per-output mean, variance and Sobol indices.
+// sets, the basis and V.  Device side: W = P Y, the evaluation V_test W at test
+// points, and the per-output mean, variance and Sobol indices.  The projection P
+// = R^-1 Q^T of a Householder QR of V is formed on the host for small sets and on
+// the device otherwise (host_projection).
 #include "common.h"
 
 #include <algorithm>
@@ -159,6 +160,50 @@ void add_tensor(NodeSet& S, const std::vector<int>& kinds, const std::vector<int
   }
 }
 
+// P = R^-1 Q^T (K rows of ldp) of V (M x K, row-major) by Householder QR on the
+// host, which takes small sets (host_projection).  Returns false, P unwritten,
+// if a column's remainder's norm is at most `tiny`.
+bool projection_host(int M, int K, const double* V, double tiny, double* P, int ldp) {
+  // rows are points, so that a reflection runs along contiguous columns
+  std::vector<double> A(V, V + (size_t)M * K), Q((size_t)M * K, 0.0), v((size_t)K * M), c(K), s(K);
+  for (int k = 0; k < K; ++k) {
+    double* vk = v.data() + (size_t)k * M;
+    double nn = 0.0;
+    for (int i = k; i < M; ++i) nn += A[(size_t)i * K + k] * A[(size_t)i * K + k];
+    const double nrm = std::sqrt(nn), akk = A[(size_t)k * K + k];
+    if (!(nrm > tiny)) return false;
+    for (int i = k; i < M; ++i) vk[i] = A[(size_t)i * K + k];
+    vk[k] -= akk > 0 ? -nrm : nrm;
+    c[k] = 1.0 / (nn + std::fabs(akk) * nrm);  // 2 / (v . v)
+    std::fill(s.begin() + k, s.end(), 0.0);
+    for (int i = k; i < M; ++i)
+      for (int j = k; j < K; ++j) s[j] += vk[i] * A[(size_t)i * K + j];
+    for (int i = k; i < M; ++i)
+      for (int j = k; j < K; ++j) A[(size_t)i * K + j] -= c[k] * s[j] * vk[i];
+  }
+  // Q's columns: the reflections of the identity's, last to first
+  for (int k = K - 1; k >= 0; --k) {
+    const double* vk = v.data() + (size_t)k * M;
+    Q[(size_t)k * K + k] = 1.0;
+    std::fill(s.begin() + k, s.end(), 0.0);
+    for (int i = k; i < M; ++i)
+      for (int j = k; j < K; ++j) s[j] += vk[i] * Q[(size_t)i * K + j];
+    for (int i = k; i < M; ++i)
+      for (int j = k; j < K; ++j) Q[(size_t)i * K + j] -= c[k] * s[j] * vk[i];
+  }
+  // R P = Q^T, all points at once
+  for (int i = K - 1; i >= 0; --i) {
+    double* p = P + (size_t)i * ldp;
+    for (int m = 0; m < M; ++m) p[m] = Q[(size_t)m * K + i];
+    for (int j = i + 1; j < K; ++j) {
+      const double r = A[(size_t)i * K + j], *pj = P + (size_t)j * ldp;
+      for (int m = 0; m < M; ++m) p[m] -= r * pj[m];
+    }
+    for (int m = 0; m < M; ++m) p[m] /= A[(size_t)i * K + i];
+  }
+  return true;
+}
+
 // ---- P = R^-1 Q^T on the device.  A fit at the paper's sizes (216 points, 56
 // terms) is a serial chain of K reflections of a matrix that one compute unit
 // holds, so one workgroup takes it all.  Up to 256 points and 64 terms
@@ -238,6 +283,14 @@ __device__ __forceinline__ void wave_all_sum4(double (&d)[4]) {
   d[1] = read_lane(v, 47);
   d[3] = read_lane(v, 63);
 }
+
+// Small sets are factorised on the host: it needs no dispatch and no upload of V,
+// and a reflection costs it 4 M K / 10^4 us where the device's chain takes 2.5 and
+// the dispatches 15 more.  Fits of 1,000 outputs, host and device: 2 x 2 20 and 33
+// us, 10 x 10 23 and 52, 60 x 20 39 and 82, 105 x 35 99 and 132, 84 x 56 136 and
+// 175; the two meet near 4,000 + 40 K values: 200 x 20 94 and 105, 168 x 28 118 and
+// 123, 210 x 35 186 and 155, 123 x 56 201 and 185.
+inline bool host_projection(int M, int K) { return (int64_t)M * K < 4000 + 40 * (int64_t)K; }
 
 // A workspace of a factorisation: the columns, R (K x K) and 2 / (v . v).
 inline size_t qr_words(int M, int K) { return (size_t)K * M + (size_t)K * K + K; }
@@ -518,8 +571,8 @@ constexpr int kRowTiles = 4, kWideRows = 16 * kRowTiles;  // most rows of a work
 constexpr int kWideCols = 16 * (kBlock / kWave);          // columns of a workgroup
 constexpr int kWideK = 32;                                // staged depth
 
-// A as this kernel reads it: rows of wide_ld(K) values, wide_rows(R) of them,
-// zero past K and past R.
+// A as this kernel reads it: rows of wide_ld(K) values, zero past K, and
+// wide_rows(R) of them, whatever stands past R (such rows are not stored).
 inline int wide_ld(int K) { return (K + kWideK - 1) / kWideK * kWideK; }
 inline int wide_rows(int R) { return (R + kWideRows - 1) / kWideRows * kWideRows; }
 
@@ -859,6 +912,17 @@ ppe_status ppe_pce_fit(ppe_pce* q, int32_t M, const double* xi, int64_t n_out, c
     if (!q->bad_h) PPE_HIP(hipHostMalloc(reinterpret_cast<void**>(&q->bad_h), sizeof(int)));
     const int K = q->n_terms, ldp = ppe::wide_ld(M);
     const size_t len = V.size(), plen = (size_t)ppe::wide_rows(K) * ldp;
+    if (ppe::host_projection(M, K)) {
+      std::vector<double> P((size_t)K * ldp, 0.0);
+      require(ppe::projection_host(M, K, V.data(), 1e-13 * vmax, P.data(), ldp), PPE_ERR_ARG,
+              "the Vandermonde matrix of these points is rank deficient");
+      double* Pd = q->a_dev.get<double>(plen);
+      PPE_HIP(hipMemcpyAsync(Pd, P.data(), sizeof(double) * P.size(), hipMemcpyHostToDevice,
+                             q->stream));
+      ppe::small_times_wide(q->stream, K, M, n_out, Pd, Y, W, nullptr);
+      PPE_HIP(hipStreamSynchronize(q->stream));
+      return PPE_OK;
+    }
     double* Pd = q->a_dev.get<double>(plen + len + 1);
     double* Vd = Pd + plen;
     int* bad = reinterpret_cast<int*>(Vd + len);

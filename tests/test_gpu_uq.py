@@ -209,3 +209,56 @@ def test_more_outputs_than_one_launch_holds():
     q.close()
     del W
     torch.cuda.empty_cache()
+
+
+# the factorisation runs on the host below 4,000 + 40 K values (points x terms):
+# both sides of that line, one term, as many points as terms
+@pytest.mark.parametrize("kinds,degree,M", [
+    (["uniform"], 0, 1), (["uniform"] * 2, 3, 10), (["uniform"] * 3, 3, 239),
+    (["uniform"] * 3, 3, 240), (["uniform"] * 3, 5, 111), (["uniform"] * 3, 5, 112),
+    (["uniform"] * 2, 9, 56), (["uniform"], 19, 241)])
+def test_fit_on_host_and_device(kinds, degree, M):
+    import torch
+
+    import paper_1810_08572_amd as ppe
+
+    q = ppe.PolynomialChaos(kinds, degree)
+    X, _ = latin_hypercube(kinds, M, seed=M)
+    Y = np.random.default_rng(M).normal(size=(M, 65))
+    V = uq.vandermonde([uq.UNIFORM] * len(kinds), uq.total_degree_indices(len(kinds), degree), X)
+    cond = np.linalg.cond(V)
+    W = q.fit(X, to_dev(Y, torch.float64)).cpu().numpy()
+    Wo = uq.fit(V, Y)
+    # as test_fit_eval_stats_at_tile_edges
+    assert np.abs(W - Wo).max() <= 1e-14 * (100 + cond ** 2) * np.abs(Wo).max()
+
+
+# twelve points: factorised on the host; 250: on the device; 300: from global memory
+@pytest.mark.parametrize("degree,M", [(2, 12), (5, 250), (5, 300)])
+def test_a_refused_fit_writes_no_coefficient(degree, M):
+    """Through the C entry point: points that repeat are refused as rank
+    deficient, the coefficients stay, and the next fit is whole."""
+    import ctypes
+
+    import torch
+
+    import paper_1810_08572_amd as ppe
+
+    q = ppe.PolynomialChaos(KINDS, degree)
+    lib, K, n = ppe.load_library(), q.n_terms, 70
+    few = np.random.default_rng(0).normal(size=((K + 1) // 2, 3))
+    X = np.ascontiguousarray(np.resize(few, (M, 3)))
+    Y = to_dev(np.ones((M, n)), torch.float64)
+    W = to_dev(np.full((K, n), 7.0), torch.float64)
+
+    def fit(pts):
+        return lib.ppe_pce_fit(q._h, len(pts), pts.ctypes.data_as(ctypes.c_void_p), n,
+                               ctypes.c_void_p(Y.data_ptr()), ctypes.c_void_p(W.data_ptr()))
+
+    assert fit(X) == ppe.PPE_ERR_ARG
+    torch.cuda.synchronize()
+    assert bool((W == 7.0).all())
+    good = np.ascontiguousarray(latin_hypercube(KINDS, M, seed=1)[0])
+    assert fit(good) == 0
+    # a constant field: coefficient 1 of the constant term, 0 elsewhere
+    assert float((W[0] - 1.0).abs().max()) <= 1e-10 and float(W[1:].abs().max()) <= 1e-10
