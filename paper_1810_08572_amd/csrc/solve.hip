@@ -1008,6 +1008,12 @@ __global__ void __launch_bounds__(kTileBlock) k_direction_t(
 // 432 us, 150 k rows' 1,069 -> 1,089, 260 k rows' 1,766 -> 1,846; the two sides
 // meet near 10^5 rows.
 constexpr int kFuseAdvance = 1 << 16;
+// It runs a workgroup of 512 threads per tile, the smoothing pass that it takes
+// over packs its rows: of many samples of a few cells each the tiles are mostly
+// idle.  2,000 samples of 3^3 cells 947 us with it and 847 without (FP32 values 911
+// and 889), 600 of 4^3 654 and 632 (686 and 688), 300 of 5^3 685 and 682 (732 and
+// 749), 100 of 6^3 627 and 647 (675 and 696): 100 rows per tile at least.
+constexpr int kAdvanceFill = 100;
 
 template <class M, int WM>
 __global__ void __launch_bounds__(kTileBlock) k_advance_t(
@@ -1961,7 +1967,8 @@ ppe_status pcg_solve(ppe_solver* s, const double* rhs, double* p_out, int use_x0
   // p alternates too: the fused pass reads the old one at every neighbour
   double* pb[2] = {s->vp.get<double>(na), s->vp2.get<double>(na)};
   // and r, where the update and the first two smoothing steps run as one pass
-  const bool advance = !s->prof && na <= kFuseAdvance && s->nlev >= 2 && !one_product(s, 0) &&
+  const bool advance = !s->prof && na <= kFuseAdvance &&
+                       na >= (int64_t)kAdvanceFill * nt && s->nlev >= 2 && !one_product(s, 0) &&
                        L0.fuse0 && !L0.c1.empty();
   double* rb[2] = {r, advance ? s->vr2.get<double>(na) : r};
   double* q = s->vq.get<double>(na);

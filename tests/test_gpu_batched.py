@@ -98,3 +98,30 @@ def test_zero_rhs_sample_and_bad_segments():
     with pytest.raises(ppe.PpeError) as e:
         s.set_segments(bad)
     assert e.value.status == ppe.PPE_ERR_ARG
+
+
+# 27 and 64 rows of a 512-thread tile: the passes of an iteration run one by one
+# (below 100 rows per tile); 216 rows: the residual's update takes the first
+# smoothing steps along
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("sides", [[3] * 180, [4] * 60, [3, 4] * 70, [6] * 30])
+def test_many_samples_of_a_few_cells(sides, precision):
+    import torch
+
+    meshes = [box_mesh((k,) * 3, jitter=0.1, seed=q) for q, k in enumerate(sides)]
+    u = concat_meshes(meshes)
+    c, fl = face_coeff(u, 2400.0), np.ones(u.n_cells)
+    b = np.concatenate([rhs_uniform(m.n_cells, seed=q, center_mask=np.ones(m.n_cells, bool))
+                        for q, m in enumerate(meshes)])
+    s = _solver(u, fl, c, precision=precision)
+    assert s.n_levels() >= 2
+    off = u.extra["cell_offsets"]
+    for _ in range(5):  # with captured iterations
+        p = s.solve(to_dev(b, torch.float64)).p.cpu().numpy()
+    for q, m in enumerate(meshes):
+        sy = assembly.masked_system(m.n_cells, m.owner, m.neigh, face_coeff(m, 2400.0),
+                                    np.ones(m.n_cells))
+        bq, pq = b[off[q]:off[q + 1]], p[off[q]:off[q + 1]]
+        assert assembly.relative_residual(sy, bq, pq) <= 1e-10, q
+        ref = direct.solve_dense(sy, bq)
+        assert np.linalg.norm(pq - ref) <= 1e-9 * np.linalg.norm(ref), q
