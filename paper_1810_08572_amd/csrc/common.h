@@ -253,11 +253,10 @@ struct ppe_solver {
   ppe::DevBuf vx, vr, vz, vp, vp2, vr2, vq, vzold, vb;
   ppe::DevBuf scal, partial, counter, flag;
   ppe::DevBuf tmp_i[4], tmp_d[2], tmp_l[2];
-  ppe::DevBuf sp_prod, sp_cnt, sp_ci, sp_v;  // sparse-product scratch
+  ppe::DevBuf sp_prod, sp_cnt, sp_ci, sp_v;  // sparse-product scratch (sp_v also coarse_operator's)
   // setup results read back once per hierarchy: the spectral bound of every
   // level (doubles [0, max_levels)), then the deferred setup error bits (int)
   ppe::DevBuf setup_out;
-  ppe::DevBuf cop_ws;  // coarse_operator's blocks of vectors
   ppe::DevBuf cols;  // column counts of the operator being transposed, its longest column
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   hipEvent_t tev0 = nullptr, tev1 = nullptr;  // autotuner timing

@@ -1637,7 +1637,9 @@ bool vcycle_t(ppe_solver* s, int l, const double* b, double* x, const PcgDot* do
 
 }  // namespace
 
-constexpr int kCopRows = 2048;                 // 33 MB of matrix at most
+// 33 MB of matrix at most, kept; forming it takes some 3.4 times as much in the
+// set-up products' scratch.
+constexpr int kCopRows = 2048;
 constexpr int64_t kCopOnce = int64_t(32) << 20;
 
 void drop_graph(ppe_solver* s) {
@@ -1776,9 +1778,18 @@ void block_rows(ppe_solver* s, const Csr& A, int ld, const double* X, const doub
   PPE_LAUNCH_CHECK();
 }
 
+// Rows of workspace block_vcycle takes from level l down: three blocks of a level
+// with a coarser one, and that one's right-hand side and correction.
+size_t block_rows_of(const ppe_solver* s, int l) {
+  size_t rows = 0;
+  for (int k = l; k < s->nlev - 1; ++k)
+    rows += 3 * (size_t)s->levels[k].n + 2 * (size_t)s->levels[k + 1].n;
+  return rows;
+}
+
 // X = M B with M the V-cycle from level l down and B a block of vectors (NULL:
 // the identity); the steps of vcycle_t, vector for vector.  ws: free
-// workspace, four blocks of this level and what the levels below take.
+// workspace, block_rows_of(s, l) rows.
 template <class M>
 void block_vcycle(ppe_solver* s, int l, int ld, const double* B, double* X, double* ws) {
   Level& L = s->levels[l];
@@ -1792,7 +1803,7 @@ void block_vcycle(ppe_solver* s, int l, int ld, const double* B, double* X, doub
   }
   const int deg = 1 + (int)L.c1.size();
   const M* sd = smooth_diag<M>(s, L);
-  double *D = ws, *u = ws + len, *w = ws + 2 * len, *r = ws + 3 * len;
+  double *D = ws, *u = ws + len, *w = ws + 2 * len;
   int step = 2;
   if (!B && deg >= 2) {
     hipLaunchKernelGGL(k_block_start<M>, dim3(n), dim3(kBlock), sizeof(double) * ld, s->stream, n,
@@ -1812,10 +1823,11 @@ void block_vcycle(ppe_solver* s, int l, int ld, const double* B, double* X, doub
     }
   };
   steps(step);
-  block_rows<B_RESID, M>(s, L.A, ld, u, B, sd, 0.0, 0.0, nullptr, r);
+  // the residual in w, which the next step writes after it has been restricted
+  block_rows<B_RESID, M>(s, L.A, ld, u, B, sd, 0.0, 0.0, nullptr, w);
   const size_t clen = (size_t)s->levels[l + 1].n * ld;
-  double *bc = ws + 4 * len, *ec = bc + clen;
-  block_rows<B_MUL, M>(s, L.R, ld, r, nullptr, nullptr, 0.0, 0.0, nullptr, bc);
+  double *bc = ws + 3 * len, *ec = bc + clen;
+  block_rows<B_MUL, M>(s, L.R, ld, w, nullptr, nullptr, 0.0, 0.0, nullptr, bc);
   block_vcycle<M>(s, l + 1, ld, bc, ec, ec + clen);
   block_rows<B_ADD, M>(s, L.P, ld, ec, nullptr, nullptr, 0.0, 0.0, nullptr, u);
   steps(1);
@@ -1839,9 +1851,7 @@ void coarse_operator(ppe_solver* s) {
     if (L.op_ok) return;
     if (L.n == 0 || L.n > kCopRows || L.A.nnz * (int64_t)L.n > most) continue;
     const int ld = (L.n + kWave - 1) / kWave * kWave;
-    size_t need = 0;
-    for (int k = l; k < s->nlev; ++k) need += (size_t)6 * s->levels[k].n * ld;
-    double* ws = s->cop_ws.get<double>(need);
+    double* ws = s->sp_v.get<double>(block_rows_of(s, l) * ld);  // idle after set-up
     double* op = L.op.get<double>((size_t)L.n * ld);
     if (s->opt.precision == PPE_MIXED)
       block_vcycle<float>(s, l, ld, nullptr, op, ws);

@@ -166,3 +166,23 @@ def test_products_without_memory_for_scratch_rows(most):
     p = s.solve(*_f64(b)).p.cpu().numpy()
     assert assembly.relative_residual(sy, b, p) <= 1e-10
     s.close()
+
+
+def test_workspace_of_the_dense_coarse_operator():
+    """Level 1 of this shifted system (1,861 rows) gets its V-cycle as one
+    matrix of 28 MB; forming it takes blocks of three vectors of that level and
+    two of the next per column, 100 MB and an eighth of slack, and no more."""
+    import torch
+
+    m = box_mesh((27, 27, 27), jitter=0.05, seed=1)
+    c = face_coeff(m, 2400.0)
+    few = Few(120 << 20)
+    s = ppe.Solver(allocator=few)
+    s.set_mesh(m.n_cells, to_dev(m.owner, torch.int32), to_dev(m.neigh, torch.int32))
+    cd, shift, b = _f64(c, np.full(m.n_cells, 0.5 * float(np.median(c))),
+                        np.random.default_rng(0).normal(size=m.n_cells))
+    s.assemble_shifted(cd, shift)
+    assert s.level_info(1)["n"] in range(1500, 2049)
+    assert few.refused == 0
+    assert s.solve(b).stats["rel_residual"] <= 1e-10
+    s.close()
