@@ -283,8 +283,9 @@ struct ppe_solver {
   bool shifted = false;  // the last assembly carried a diagonal shift (no pins)
   ppe::DevBuf prev_coeff;
   // autotuner choices per (level, FP32, quarter-octave bins of rows and of
-  // entries): {lpr_a, fuse0, lpr_r, lpr_p, fuse_p}
-  std::map<std::array<int, 4>, std::array<int, 5>> tune_cache;
+  // entries, whether the prolongation can be fused): {lpr_a, fuse0, lpr_r, lpr_p,
+  // fuse_p}
+  std::map<std::array<int, 5>, std::array<int, 5>> tune_cache;
 
   // HIP graph of two PCG iterations, captured once per system at most
   hipStream_t gstream = nullptr;

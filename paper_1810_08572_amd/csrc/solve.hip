@@ -2263,7 +2263,6 @@ template <class M>
 void tune_level(ppe_solver* s, int l) {
   Level& L = s->levels[l];
   const bool coarsest = l == s->nlev - 1;
-  if (L.n == 0 || one_product(s, l)) return;
   double* x = L.x.as<double>();
   double* b = L.b.as<double>();
   double* d = L.d.as<double>();
@@ -2331,10 +2330,13 @@ void autotune_levels(ppe_solver* s) {
   const bool f32 = s->opt.precision == PPE_MIXED;
   for (int l = 0; l < s->nlev; ++l) {
     Level& L = s->levels[l];
+    if (L.n == 0 || one_product(s, l)) continue;  // nothing to choose
     // shapes within a quarter octave of rows and of entries share choices, so
     // a slowly changing active set rarely triggers a new tuning
     auto bin = [](double v) { return (int)std::lround(4.0 * std::log2(v > 1.0 ? v : 1.0)); };
-    const std::array<int, 4> key{l, f32 ? 1 : 0, bin(L.n), bin((double)L.A.nnz)};
+    // (and a kept A P has a fused prolongation to choose, a stale one has not)
+    const std::array<int, 5> key{l, f32 ? 1 : 0, bin(L.n), bin((double)L.A.nnz),
+                                 prolong_can_fuse(s, L) ? 1 : 0};
     auto it = s->tune_cache.find(key);
     if (it != s->tune_cache.end()) {
       L.lpr_a = it->second[0];
