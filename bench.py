@@ -13,7 +13,8 @@ Headline workload: timesteps on the plate with ribs (1.5 M cells).
   residual.  One bench step is one timestep's whole hot path: masked
   assembly, AMG setup, then PCG (inputs already in device memory).
 
-Reported (one JSON line):
+Reported: one short JSON line with the headline, its roofline and the named
+variants' rates, and every leg in full in a file beside it (--detail):
 - value: FP64 AMG-PCG from a zero guess (the plain method), solves/s.
 - roofline: the solve kernel with the largest total time, from the
   library's per-dispatch event pairs during a re-run of the timed steps
@@ -61,6 +62,56 @@ C2_TRAIN = range(20, 80)
 
 def note(msg):
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
+
+
+# What the printed line keeps of a record: a line that a log of the last two
+# thousand characters still holds whole.
+LINE_CHARS = 1800
+LINE_ROOFLINE = ("bound", "kernel", "achieved", "peak", "unit", "frac", "traffic", "avg_launch_us",
+                 "launches")
+LINE_BASELINE = ("value", "unit", "cores", "kind", "host_cpu")
+LINE_VARIANTS = ("c5_plate.mixed_learned", "c5_plate.mixed_zero_guess", "c3_128cube.fp64",
+                 "c3_128cube.mixed", "c4_uq_batched", "c2_64cube.mixed_learned")
+
+
+def _short(v):
+    return float(f"{v:.6g}") if isinstance(v, float) else v
+
+
+def line_of(out, detail):
+    """The record as it is printed: the contract's fields and the
+    configuration, figures to six digits, the parts above of the roofline and
+    the host baseline, the named variants' rates, and the file that holds the
+    rest."""
+    line = {k: _short(v) for k, v in out.items() if not isinstance(v, dict)}
+    line["config"] = {k: _short(v) for k, v in out["config"].items()}
+    for part, keep in (("roofline", LINE_ROOFLINE), ("cpu_baseline", LINE_BASELINE)):
+        if part in out:
+            line[part] = {k: _short(out[part][k]) for k in keep if k in out[part]}
+    rates = {}
+    for name in LINE_VARIANTS:
+        leg = out.get("variants", {})
+        for k in name.split("."):
+            leg = leg.get(k, {}) if isinstance(leg, dict) else {}
+        rate = leg.get("value", leg.get("solves_per_s"))
+        if rate is not None:
+            rates[name] = _short(rate)
+    if rates:
+        line["variants"] = rates
+    if detail:
+        line["detail"] = os.path.basename(detail)
+    return json.dumps(line)
+
+
+def report(out, detail):
+    if detail:
+        try:
+            with open(detail, "w") as f:
+                json.dump(out, f, indent=1)
+        except OSError as e:
+            note(f"no detail file: {e}")
+            detail = ""
+    print(line_of(out, detail), flush=True)
 
 
 class Timesteps:
@@ -762,6 +813,8 @@ def main():
     ap.add_argument("--only", default="",
                     help="comma list of variant legs to run: c5, c3, c4, c2, projection, flow, "
                          "collocation (default: all)")
+    ap.add_argument("--detail", default=os.path.join(ROOT, "bench_detail.json"),
+                    help="file for the full record of every leg ('' for none)")
     ap.add_argument("--c3-only", action="store_true",
                     help="run only the 128^3 leg and print its JSON (for profiling it alone)")
     ap.add_argument("--copy-probe", action="store_true",
@@ -880,7 +933,7 @@ def main():
     if not args.no_cpu_baseline:
         note("timing the oracle on the host")
         out["cpu_baseline"] = cpu_baseline(wl, steps[0], base["first_iters"])
-    print(json.dumps(out), flush=True)
+    report(out, args.detail)
 
 
 if __name__ == "__main__":
