@@ -147,3 +147,31 @@ def test_all_solid_and_zero_rhs():
     s.assemble(to_dev(c, torch.float64), to_dev(f, torch.float64))
     r = s.solve(to_dev(np.zeros(m.n_cells), torch.float64))
     assert r.stats["iterations"] == 0 and not r.p.cpu().numpy().any()
+
+
+@pytest.mark.parametrize("shape,pits,wall", [((66, 32, 32), 63, False), ((66, 32, 32), 64, False),
+                                             ((66, 32, 32), 400, True), ((63, 32, 32), 400, True)])
+def test_component_search_on_both_sides_of_its_limits(shape, pits, wall):
+    """The round that joins whole trees runs above 65,536 cells and 64 trees.  A
+    flat floor is one tree and every pit of one cell in it another (a tree's root
+    has no liquid neighbour of a smaller index): counted here, so that the inputs
+    lie where the limits do."""
+    m = box_mesh(shape, jitter=0.0, seed=0)
+    g = m.grid_index
+    deep = np.zeros(shape[:2], bool)
+    xy = np.stack(np.meshgrid(np.arange(1, shape[0], 2), np.arange(1, shape[1], 2)), -1).reshape(-1, 2)
+    xy = xy[np.random.default_rng(3).permutation(len(xy))[:pits]]
+    deep[xy[:, 0], xy[:, 1]] = True
+    f = ((g[:, 2] >= 3) | ((g[:, 2] == 2) & deep[g[:, 0], g[:, 1]])).astype(float)
+    if wall:
+        f[g[:, 0] == shape[0] // 2] = 0.0
+    inner = m.neigh >= 0
+    o, n = m.owner[inner], m.neigh[inner]
+    both = (f[o] > 0) & (f[n] > 0)
+    has_smaller = np.zeros(m.n_cells, bool)
+    has_smaller[np.maximum(o, n)[both]] = True
+    trees = int(((f > 0) & ~has_smaller).sum())
+    assert (trees > 64) == (pits > 63) and (m.n_cells > 65536) == (shape[0] > 64)
+    s, sy = _check_bitwise(m, f, face_coeff(m, 2400.0))
+    assert len(sy.pins) == (2 if wall else 1)
+    s.close()
