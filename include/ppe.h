@@ -67,7 +67,8 @@ typedef enum { PPE_SMOOTH_CHEBYSHEV = 0, PPE_SMOOTH_L1JACOBI = 1 } ppe_smoother;
 /* Caller-provided device allocator (for example PyTorch's caching
  * allocator).  alloc returns a device pointer to at least `bytes` bytes of
  * the solver's device, usable in stream order on `stream` (the solver's
- * stream), or NULL on failure (the call then fails with PPE_ERR_OOM).
+ * stream), or NULL on failure (the call then fails with PPE_ERR_OOM, but for a
+ * workspace that it can do without).
  * free releases a pointer alloc returned; the library drains its streams
  * before calling it, so the block is idle.  ctx is passed through. */
 typedef void* (*ppe_alloc_fn)(size_t bytes, void* stream, void* ctx);

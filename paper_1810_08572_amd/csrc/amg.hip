@@ -390,8 +390,8 @@ __global__ void __launch_bounds__(kBlock) k_agg_second_ell(int n, int W, const i
 // holds, for every aggregate J reached from row i, the sum of a_ij pt_j
 // over that row's entries j in J.  The row's entries are taken in CSR order
 // (ascending column, the diagonal in its place) and each sum starts from 0
-// in that order: bitwise the general product's one-sub-group result.  COUNT:
-// distinct aggregates per row into counts; else the row, sorted by
+// in that order, as the general product's do (rows of P_tent have one entry):
+// bitwise its result.  COUNT: distinct aggregates per row into counts; else the row, sorted by
 // aggregate, at rp[i].
 template <int WM, bool COUNT>
 __global__ void __launch_bounds__(kBlock) k_coarsen_cols_ell(
@@ -447,10 +447,10 @@ __global__ void __launch_bounds__(kBlock) k_coarsen_cols_ell(
 // Finest level: AP = A P by rows, one thread per row from the ELL copy:
 // row i of AP merges the sorted rows of P selected by row i of A (its ELL
 // slots and the diagonal, at most WM + 1 of them), column by column.  A
-// column's products are added from 0 in CSR order of A's row, which is the
-// order the general product adds them in (one sub-group walks A's row in
-// order): bitwise its result.  COUNT: entries per row into counts; else the
-// row, sorted, at rp[i].
+// column's products are added from 0 in CSR order of A's row (the general product
+// may take the later entries of P's longer rows in a later turn, so the two agree
+// to rounding).  COUNT: entries per row into counts; else the row, sorted, at
+// rp[i].
 // The next entries of each list wait in registers, loaded kApU at a time: the
 // pass is bound by the accesses of 64 lanes to as many lines (one a cycle and
 // compute unit), and a row of P is three to four entries.  P's arrays
@@ -1234,9 +1234,11 @@ __global__ void __launch_bounds__(1024) k_spgemm_rows(
 // lanes across the selected row of B.  Sub-groups that meet in a column would
 // add in an order of their own, so the adds are issued one sub-group after
 // another; they return nothing, so nothing waits for them, and a wavefront's LDS
-// operations complete in issue order: a column is summed from 0 in the entry
-// order of A's row, the wavefronts' sums in theirs, whatever the timing.  The
-// row is written sorted by column to the scratch row at i cap, and counts[i] =
+// operations complete in issue order.  So a column is summed from 0 in an order
+// that A's and B's rows fix, whatever the timing: of each 64 / LPR entries of A's
+// row the first LPR columns of every selected row, in entry order, then the next
+// LPR of every one, and so on (the entry order itself where no selected row is
+// longer than LPR); then the wavefronts' sums in theirs.  The row is written sorted by column to the scratch row at i cap, and counts[i] =
 // its length; a row of more than cap columns sets *over and the host takes the
 // two passes of k_spgemm_rows (a wavefront stops after its first column without
 // a slot: for every later product it would probe all of a full table, which made
@@ -2427,7 +2429,7 @@ static void coarsen_cols_ell(ppe_solver* s, const Level& L, const int* agg, cons
 
 // AP = A P on the finest level from its ELL copy (k_ap_merge_ell): count,
 // scan with the longest row and the device value extra (one round trip),
-// fill.  AP is what the general product gives, entry for entry.
+// fill.
 static void ap_merge_ell(ppe_solver* s, const Level& L, const Csr& P, Csr& AP, int* flag,
                          const int* extra, int* extra_host) {
   const int n = L.n, W = L.W;
@@ -2547,9 +2549,10 @@ void build_hierarchy(ppe_solver* s) {
                  theta_l * theta_l, strong, st);
       }
       const uint32_t salt = level_salt(lvl);
-      // As many rounds before the first host check as this level needed last
-      // time, then a few at a time (on the finest level the later ones are
-      // k_mis_finish_ell's); a round after the set is complete changes nothing.
+      // As many rounds before the first host check as any set-up of this level has
+      // launched so far (mis_batch never falls), then a few at a time (on the finest
+      // level the later ones are k_mis_finish_ell's); a round after the set is
+      // complete changes nothing.
       // The roots are numbered before each check and their count read with it:
       // the numbering is kept once no node is left undecided.
       int* und = s->tmp_i[3].get<int>(1);

@@ -178,7 +178,7 @@ struct Level {
   bool fuse0 = true, fuse_p = true;
   double inv_theta = 0.0;
   std::vector<double> c1, c2;  // Chebyshev steps 2..degree
-  int mis_batch = 6;     // MIS-2 rounds before the first check (last assembly's count)
+  int mis_batch = 6;     // MIS-2 rounds before the first check: the most launched so far
   Csr Pt, Q;             // setup scratch: tentative P, A*P_tent
   Csr AP;                // A*P: built for the Galerkin product, then read by
                          // the prolongation fused with post-smoothing

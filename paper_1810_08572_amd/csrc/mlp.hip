@@ -47,8 +47,9 @@ __device__ __forceinline__ float dsilu_f(float z) {
 // A batch is a handful of thin products (8,192 rows, width 128: 1.7 GFLOP
 // with the gradients, 26 MB of activations), so what bounds it is the number
 // of dispatches and how many compute units each one fills.  Every product
-// runs on the FP32 matrix cores (v_mfma_f32_32x32x2f32: FP32 products and
-// sums, the vector ALUs' accuracy) in 32 x 32 tiles, one per wave, and takes
+// runs on the FP32 matrix cores (FP32 products and sums, the vector ALUs'
+// accuracy), a layer's as two v_mfma_f32_16x16x4f32 tiles side by side per wave,
+// the weight gradients as one v_mfma_f32_32x32x2f32 tile per wave, and takes
 // what follows it along: bias and SiLU with the forward layers, silu' with
 // the backward ones, the whole output layer with the loss.  The weight and
 // bias gradients of all layers are one dispatch over (tile, chunk of rows),
@@ -59,7 +60,7 @@ __device__ __forceinline__ float dsilu_f(float z) {
 // 3.87 ms.
 typedef float float16_t __attribute__((ext_vector_type(16)));
 
-constexpr int kTile = 32;  // rows and columns of one wave's product tile
+constexpr int kTile = 32;  // rows of a workgroup's tile; rows and columns of a gradient wave's
 constexpr int kTileN = 4 * kTile;  // columns of a workgroup's tile (4 waves)
 constexpr int kTileK = 64;         // depth staged in LDS at a time
 

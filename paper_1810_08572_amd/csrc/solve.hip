@@ -1287,11 +1287,11 @@ const M* smooth_diag(const ppe_solver* s, const Level& L) {
 // to what the autotuner picked on the 128^3 cube and the 1.5 M-cell plate
 // (FP64 and mixed): about 1.8 sqrt(row length) lanes for the smoothing steps
 // (8 for rows of 30 entries, 16 for 128, 32 for 219), three entries per lane
-// for the restriction and the plain prolongation, and about
-// 3 sqrt(row length) lanes for the fused prolongation (whose rows of A, P and
-// A P are read together).  The plain transfers go down to one lane per row
-// (the finest prolongation has three to four entries a row); the smoothing
-// and fused kernels keep at least four.  A level too small to give every
+// for the restriction and the plain prolongation, and two and a half entries of
+// A P per lane for the fused prolongation (prolong_lanes).  The plain transfers
+// go down to one lane per row (the finest prolongation has three to four entries
+// a row); the smoothing and fused kernels keep at least four.  A level too small
+// to give every
 // compute unit a block of 256 threads at that count takes 64 lanes.
 int lanes_near(double target, int lo = 4) {
   int best = lo;
@@ -2143,12 +2143,13 @@ ppe_status pcg_solve(ppe_solver* s, const double* rhs, double* p_out, int use_x0
   };
   // Two iterations (both rz slots) captured into a HIP graph once the system
   // has been solved often enough to expect as many solves again, then replayed
-  // while at least two iterations remain.  A solve of 2.8 k rows saves 95 us by
-  // it (651 -> 557) and the capture costs 150; at 150 k rows it saves 11 of
-  // 1,176 us and costs 320, at 370 k 36 of 1,941 and 475.  So a few solves
-  // where the launches count, many elsewhere: capturing at the second solve
-  // had cost the Picard passes of a time step, each a new diagonal, more than
-  // their replays gave.
+  // while at least two iterations remain.  A capture costs 60 to 600 us; what a
+  // replay saves depends on the host: where its launches are slow 75 us of 700 at
+  // 33 k rows, 56 of 770 at 64 k and nothing from 110 k on, where they keep ahead
+  // nothing anywhere, and above 64 k rows a replay costs 8 to 36 us more than the
+  // launches.  So a few solves first where the launches may count, many elsewhere:
+  // capturing at the second solve had cost the Picard passes of a time step, each a
+  // new diagonal, more than their replays gave.
   const int after = na <= 32768 ? 3 : 16;
   const bool graph = s->opt.use_graph && !s->prof && s->solves_since_assemble >= after;
   if (graph && !s->graph_ok) capture_iterations(s, [&]() { body(0); body(1); });
