@@ -1447,11 +1447,31 @@ __global__ void __launch_bounds__(kBlock) k_spgemm_compact(int n, int stride,
 // the coarsest level) is transposed without atomics on its few column
 // counters and without sorting: a one-workgroup count, then one workgroup
 // per column that collects the column's entries in storage order.
-// Every column's workgroup walks all entries twice, so the path pays only while
-// columns x entries is small: a 64^3 step's first coarse prolongator (605 x
-// 92 k) took 95 us here and takes about 30 on the general path.
+// Every column's workgroup walks all entries twice, while the general path's
+// rank sort compares every pair of a column's entries, so which is faster
+// depends on columns x entries against the square of the mean column:
+//
+//   columns x entries     over mean^2     narrow, us   general, us
+//   4.3 M (97 x 44 k)           21             56          126
+//   19 M (169 x 115 k)          42            105          271
+//   50 M (287 x 175 k)         135            147          243
+//   288 M (487 x 591 k)        195            461          809
+//   194 M (546 x 355 k)        457            409          273
+//   10.6 M (270 x 39 k)        503             42           27
+//   31 M (455 x 69 k)        1,370             67           28
+//
+// (kernel times on prolongators of boxes from 12^3 to 128^3, beams and plates,
+// with and without a shift; a line between 195 and 281 parts them all).  Up to
+// kNarrowWork columns x entries the narrow path's fewer launches make up for
+// what its kernels lose.
 constexpr int kNarrowCols = 1024;
 constexpr int64_t kNarrowWork = int64_t(8) << 20;
+constexpr int64_t kNarrowRatio = 256;
+inline bool narrow_pays(int64_t cols, int64_t nnz) {
+  if (cols <= 0 || nnz <= 0 || cols > kNarrowCols) return false;
+  // cols nnz / (nnz / cols)^2 = cols^3 / nnz
+  return cols * nnz <= kNarrowWork || cols * cols * cols <= kNarrowRatio * nnz;
+}
 constexpr int kNarrowU = 8;  // entries per lane whose loads are issued together
 
 // Column counts in LDS, then T's row pointers trp[0..m] (exclusive scan over
@@ -2182,7 +2202,7 @@ const int* transpose(ppe_solver* s, const Csr& A, Csr& T) {
   T.m = A.n;
   T.nnz = A.nnz;
   T.maxrow = 0;
-  if (T.n > 0 && T.n <= kNarrowCols && A.nnz > 0 && A.nnz * T.n <= kNarrowWork) {
+  if (narrow_pays(T.n, A.nnz)) {
     int* trp = T.rowptr.get<int>(T.n + 1);
     hipLaunchKernelGGL(k_narrow_count, dim3(1), dim3(1024), 0, s->stream, A.nnz, T.n, A.ci(), trp,
                        s->cols.get<int>(1));

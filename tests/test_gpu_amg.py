@@ -311,3 +311,43 @@ def test_products_whose_rows_outgrow_the_scratch():
         # as test_hierarchy_matches_oracle: summation order only
         assert A.nnz == lev.A.nnz and rel_max(A, lev.A) <= 1e-13, lvl
     s.close()
+
+
+@pytest.mark.parametrize("shape,shift,narrow", [((200, 20, 10), 0.0, True), ((200, 20, 10), 2.0, True),
+                                                ((40, 40, 40), 0.0, False), ((20, 20, 20), 0.0, False)])
+def test_transposes_on_both_sides_of_the_narrow_rule(shape, shift, narrow):
+    """Prolongators of at most 1,024 columns and over 8 M columns times
+    entries: transposed column by column up to 256 times the square of their
+    mean column, by the general path beyond.  The transpose is the left factor
+    of the next level's operator."""
+    import scipy.sparse as sp
+    import torch
+
+    import paper_1810_08572_amd as ppe
+
+    m = box_mesh(shape, jitter=0.1, seed=1)
+    f, c = np.ones(m.n_cells), face_coeff(m, 2400.0)
+    A = assembly.masked_system(m.n_cells, m.owner, m.neigh, c, f).A
+    s = ppe.Solver(coarse_max=100)
+    s.set_mesh(m.n_cells, to_dev(m.owner, torch.int32), to_dev(m.neigh, torch.int32))
+    if shift:
+        d = np.full(m.n_cells, shift * np.median(c))
+        k = m.neigh >= 0
+        o, q, v = m.owner[k], m.neigh[k], c[k]
+        A = sp.coo_matrix((np.concatenate([v, v, -v, -v, d]),
+                           (np.concatenate([o, q, o, q, np.arange(m.n_cells)]),
+                            np.concatenate([o, q, q, o, np.arange(m.n_cells)]))),
+                          shape=(m.n_cells, m.n_cells)).tocsr()
+        s.assemble_shifted(to_dev(c, torch.float64), to_dev(d, torch.float64))
+    else:
+        s.assemble(to_dev(c, torch.float64), to_dev(f, torch.float64))
+    H = amg.build_hierarchy(A, coarse_max=100)
+    sides = [P.shape[1] ** 3 <= 256 * P.nnz for P in (lev.P for lev in H.levels[:-1])
+             if P.shape[1] <= 1024 and P.shape[1] * P.nnz > 8 << 20]
+    assert sides == [narrow]
+    assert s.n_levels() == len(H.levels)
+    for lvl, lev in enumerate(H.levels):
+        got = csr(*s.level_matrix(lvl), lev.A.shape)
+        # as test_hierarchy_matches_oracle: summation order only
+        assert got.nnz == lev.A.nnz and rel_max(got, lev.A) <= 1e-13, lvl
+    s.close()
