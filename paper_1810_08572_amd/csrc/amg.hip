@@ -1238,9 +1238,9 @@ __global__ void __launch_bounds__(1024) k_spgemm_rows(
 // that A's and B's rows fix, whatever the timing: of each 64 / LPR entries of A's
 // row the first LPR columns of every selected row, in entry order, then the next
 // LPR of every one, and so on (the entry order itself where no selected row is
-// longer than LPR); then the wavefronts' sums in theirs.  The row is written sorted by column to the scratch row at i cap, and counts[i] =
-// its length; a row of more than cap columns sets *over and the host takes the
-// two passes of k_spgemm_rows (a wavefront stops after its first column without
+// longer than LPR); then the wavefronts' sums in theirs.  The row is written
+// sorted by column to the scratch row at i cap, and counts[i] = its length; a
+// row of more than cap columns sets *over and the host takes the two passes of k_spgemm_rows (a wavefront stops after its first column without
 // a slot: for every later product it would probe all of a full table, which made
 // the set-up of 100^3 cells with a shift, 22.5 k rows of 279 columns in 256
 // slots, 14.7 ms; 8.5 so, and 7.2 where the host foresees it).
